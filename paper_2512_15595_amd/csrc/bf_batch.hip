@@ -49,7 +49,6 @@ struct bf_batch {
   bool partitioned;
   std::vector<uint8_t> part_direct;
   PartArgs part;
-  PartLayout part_layout;
   PartKernels part_k;
   void* part_scratch;
   // device memory from lib_alloc (pooled: released in stream order)
@@ -148,124 +147,136 @@ bf_status plan_partitioned(bf_batch* b, bf_filter* const* filters, uint32_t nfil
   if (strategy == BF_STRATEGY_AUTO && !(dense_chunks >= 512 && n_dense >= (1ull << 21))) return BF_OK;
   PartArgs a{};
   PartLayout L{};
-  if (!part_geometry(chunks, shift, n, a, L)) return BF_OK;
-  PartKernels k = part_kernels(f0);
-  k.scatter1 = k.scatter1_multi;  // the first pass takes its key ranges from the work list
-  if (k.scatter1 == nullptr || k.scatter2 == nullptr || k.apply == nullptr) return BF_OK;
-  // Per-bucket capacities from each chunk's expected load: filter i's keys
-  // spread uniformly over its blocks (a chunk holding part of the filter
-  // expects that part's share); six standard deviations plus a margin.
-  std::vector<double> load(chunks, 0.0);
+  if (!part_digits(chunks, shift, a)) return BF_OK;
+  const uint64_t f2 = a.r.digits, f1 = a.g.digits;
+  // First-pass ranges: at most range1 keys of one dense filter each (the
+  // keys of direct filters are not read), whose steps are numbered in filter
+  // order; filter i's are first_step[i] .. first_step[i + 1].
+  const uint64_t range1 = std::max<uint64_t>((n / 1024 + kStep) / kStep, 1) * kStep;
+  std::vector<PartRange> ranges;
+  std::vector<uint64_t> first_step(nfilters + 1, 0);
+  uint64_t steps = 0, runs = 0;
   for (uint32_t i = 0; i < nfilters; ++i) {
-    const double ni = static_cast<double>(pf[i].key_end - pf[i].key_begin);
-    if (ni == 0 || pf[i].direct) continue;
+    first_step[i] = steps;
+    const uint64_t ni = pf[i].key_end - pf[i].key_begin;
+    if (pf[i].direct || ni == 0) continue;
+    for (uint64_t s = 0; s < ni; s += range1)
+      ranges.push_back(PartRange{pf[i].key_begin + s, pf[i].key_begin + std::min(s + range1, ni), i,
+                                 static_cast<uint32_t>(steps + s / kStep)});
+    const uint64_t si = (ni + kStep - 1) / kStep;
     const uint64_t nc = (pf[i].num_blocks + bpc - 1) / bpc;
-    for (uint64_t c = 0; c < nc; ++c) {
-      const uint64_t blocks = std::min<uint64_t>(bpc, pf[i].num_blocks - c * bpc);
-      load[pf[i].chunk_base + c] = ni * static_cast<double>(blocks) / static_cast<double>(pf[i].num_blocks);
+    const uint64_t digits = (pf[i].chunk_base + nc - 1) / f2 - pf[i].chunk_base / f2 + 1;
+    steps += si;
+    runs += si * digits;
+  }
+  first_step[nfilters] = steps;
+  if (ranges.empty() || ranges.size() > 0x7fffffffull || steps * kStep > 0xffffffffull * 16) return BF_OK;
+  // longest first: workgroups are dispatched in index order as CUs free up,
+  // so the short ranges fill the gaps at the end
+  std::stable_sort(ranges.begin(), ranges.end(), [](const PartRange& x, const PartRange& y) {
+    return x.end - x.begin > y.end - y.begin;
+  });
+  // Second-pass items, by digit: the steps of the digit's filters cut so that
+  // an item expects about 64 Ki records, or fewer (two steps at least) where
+  // that would leave under a thousand items for 256 CUs.  Apply work: one item per chunk of a
+  // dense filter with keys; heavily loaded chunks are split over several
+  // workgroups (~128 Ki records each, each of which then merges its whole
+  // chunk image with atomics).
+  const double target = static_cast<double>(std::clamp<uint64_t>(n_dense / 1024, 2 * kStep, 65536));
+  std::vector<PartItem> items;
+  std::vector<PartWork> work;
+  uint64_t batches = 0;
+  uint32_t fi = 0;  // first filter with chunks in the digit
+  for (uint64_t d = 0; d < f1; ++d) {
+    const uint64_t c0 = d * f2, c1 = std::min<uint64_t>(chunks, c0 + f2);
+    auto chunk_end = [&](uint32_t i) { return i + 1 < nfilters ? pf[i + 1].chunk_base : chunks; };
+    while (fi < nfilters && chunk_end(fi) <= c0) ++fi;
+    double acc = 0.0;
+    uint64_t t0 = 0, t1 = 0;  // the open item
+    auto close = [&] {
+      if (t1 > t0) {
+        items.push_back(PartItem{static_cast<uint32_t>(d), static_cast<uint32_t>(t0), static_cast<uint32_t>(t1), 0});
+        batches += (t1 - t0 + kRegroupRuns - 1) / kRegroupRuns;
+      }
+      t0 = t1;
+      acc = 0.0;
+    };
+    for (uint32_t i = fi; i < nfilters && pf[i].chunk_base < c1; ++i) {
+      const uint64_t ni = pf[i].key_end - pf[i].key_begin;
+      const uint64_t si = first_step[i + 1] - first_step[i];
+      if (si == 0) continue;
+      // the filter's keys spread uniformly over its blocks
+      const uint64_t fc0 = std::max(c0, pf[i].chunk_base), fc1 = std::min(c1, chunk_end(i));
+      const double per_block = static_cast<double>(ni) / static_cast<double>(pf[i].num_blocks);
+      auto blocks_to = [&](uint64_t c) { return std::min((c - pf[i].chunk_base) * bpc, pf[i].num_blocks); };
+      const double per_step = per_block * static_cast<double>(blocks_to(fc1) - blocks_to(fc0)) / static_cast<double>(si);
+      if (t1 != first_step[i] || t1 == t0) {
+        close();
+        t0 = t1 = first_step[i];
+      }
+      const uint32_t i0 = static_cast<uint32_t>(items.size());
+      while (t1 < first_step[i + 1]) {
+        const uint64_t fit = static_cast<uint64_t>(std::max(1.0, (target - acc) / std::max(per_step, 1e-3)));
+        const uint64_t take = std::min(fit, first_step[i + 1] - t1);
+        t1 += take;
+        acc += per_step * static_cast<double>(take);
+        if (acc >= target - 0.5 * per_step) close();
+      }
+      const uint32_t i1 = static_cast<uint32_t>(items.size()) + (t1 > t0 ? 1 : 0);
+      for (uint64_t c = fc0; c < fc1; ++c) {
+        const double load = per_block * static_cast<double>(blocks_to(c + 1) - blocks_to(c));
+        const uint64_t ns = std::clamp<uint64_t>(static_cast<uint64_t>(load / 131072.0) + 1, 1, 65535);
+        for (uint64_t j = 0; j < ns; ++j)
+          work.push_back(PartWork{static_cast<uint32_t>(c), static_cast<uint16_t>(j), static_cast<uint16_t>(ns), i0, i1});
+      }
     }
+    close();
   }
-  auto cap_of = [](double mean, double margin) {
-    if (mean <= 0.0) return uint64_t{0};
-    return static_cast<uint64_t>(std::ceil(mean + 6.0 * std::sqrt(mean) + margin));
-  };
-  std::vector<uint64_t> off1(a.f1 + 1, 0), off2(chunks + 1, 0);
-  for (uint64_t c = 0; c < chunks; ++c) off2[c + 1] = off2[c] + cap_of(load[c], 64.0);
-  for (uint32_t d = 0; d < a.f1; ++d) {
-    double m = 0.0;
-    for (uint64_t c = static_cast<uint64_t>(d) * a.f2; c < std::min<uint64_t>(chunks, (d + 1ull) * a.f2); ++c)
-      m += load[c];
-    off1[d + 1] = off1[d] + cap_of(m, 1024.0);
-  }
-  // buffers sized by the extents (replacing the uniform layout)
-  L.off_buf1 = 0;
-  a.spare1 = off1[a.f1];
-  a.spare2 = off2[chunks];
-  uint64_t off = (8 * (off1[a.f1] + kSpareSlots) + 255) & ~255ull;
-  part_buf2(L, off, off2[chunks]);
-  L.total = (L.off_fill + 8 * L.nfill + 255) & ~255ull;
-  // tables after the buffers: filters, chunk owners, the first pass's work
-  // items (key ranges of at most range1 keys within one dense filter; the
-  // keys of direct filters are not read)
+  if (items.empty() || items.size() > 0x7fffffffull || work.size() > 0xffffffffull) return BF_OK;
+  part_layout_two(a, L, steps, items.size(), batches, runs, n_dense);
+  // tables after the buffers: filters, chunk owners, ranges, items, apply work
   std::vector<uint32_t> owner(chunks);
   for (uint32_t i = 0; i < nfilters; ++i) {
     const uint64_t c_end = i + 1 < nfilters ? pf[i + 1].chunk_base : chunks;
     std::fill(owner.begin() + static_cast<std::ptrdiff_t>(pf[i].chunk_base),
               owner.begin() + static_cast<std::ptrdiff_t>(c_end), i);
   }
-  std::vector<PartRange> work1;
-  for (uint32_t i = 0; i < nfilters; ++i) {
-    if (pf[i].direct) continue;
-    for (uint64_t s = pf[i].key_begin; s < pf[i].key_end; s += a.range1)
-      work1.push_back(PartRange{s, std::min(s + a.range1, pf[i].key_end), i, 0});
+  struct Table {
+    const void* src;
+    uint64_t bytes;
+    uint64_t at;
+  } tables[] = {{pf.data(), pf.size() * sizeof(PartFilter), 0},   {owner.data(), owner.size() * 4, 0},
+                {ranges.data(), ranges.size() * sizeof(PartRange), 0}, {items.data(), items.size() * sizeof(PartItem), 0},
+                {work.data(), work.size() * sizeof(PartWork), 0}};
+  uint64_t total = L.total;
+  for (Table& t : tables) {
+    t.at = total;
+    total = (total + t.bytes + 255) & ~255ull;
   }
-  if (work1.empty() || work1.size() > 0x7fffffffull) return BF_OK;
-  // longest first: workgroups are dispatched in index order as CUs free up,
-  // so the short items fill the gaps at the end
-  std::stable_sort(work1.begin(), work1.end(), [](const PartRange& x, const PartRange& y) {
-    return x.end - x.begin > y.end - y.begin;
-  });
-  const uint64_t off_pf = L.total;
-  const uint64_t off_owner = (off_pf + pf.size() * sizeof(PartFilter) + 255) & ~255ull;
-  const uint64_t off_first = (off_owner + owner.size() * 4 + 255) & ~255ull;
-  // work lists: heavily loaded buckets are split over several workgroups
-  // (~64K records per second-pass slice; ~128K per apply slice, each of
-  // which then merges its whole chunk image with atomics)
-  std::vector<PartWork> work2, work3;
-  for (uint32_t d = 0; d < a.f1; ++d) {
-    const uint64_t ns = std::clamp<uint64_t>((off1[d + 1] - off1[d] + 65535) / 65536, 1, 65535);
-    for (uint64_t i = 0; i < ns; ++i)
-      work2.push_back(PartWork{d, static_cast<uint16_t>(i), static_cast<uint16_t>(ns)});
-  }
-  for (uint64_t c = 0; c < chunks; ++c) {
-    if (load[c] <= 0.0) continue;  // no records can land here: nothing to apply
-    const uint64_t ns = std::clamp<uint64_t>(static_cast<uint64_t>(load[c] / 131072.0) + 1, 1, 65535);
-    for (uint64_t i = 0; i < ns; ++i)
-      work3.push_back(PartWork{static_cast<uint32_t>(c), static_cast<uint16_t>(i), static_cast<uint16_t>(ns)});
-  }
-  const uint64_t off_ext1 = (off_first + work1.size() * sizeof(PartRange) + 255) & ~255ull;
-  const uint64_t off_ext2 = (off_ext1 + off1.size() * 8 + 255) & ~255ull;
-  const uint64_t off_w2 = (off_ext2 + off2.size() * 8 + 255) & ~255ull;
-  const uint64_t off_w3 = (off_w2 + work2.size() * sizeof(PartWork) + 255) & ~255ull;
-  const uint64_t total = (off_w3 + work3.size() * sizeof(PartWork) + 255) & ~255ull;
-  if (work2.size() > 0xffffffffull || work3.size() > 0xffffffffull) return BF_OK;
+  a.g.ranges = reinterpret_cast<const PartRange*>(1);  // a plan: the multi-filter first pass
+  const PartKernels k = part_kernels(f0, a);
+  if (!part_runs(a, k)) return BF_OK;
   b->part_scratch = lib_alloc(b->device, total, &b->pooled_scratch);
   if (b->part_scratch == nullptr) return BF_ENOMEM;
   uint8_t* base = static_cast<uint8_t*>(b->part_scratch);
-  if (hipMemcpy(base + off_pf, pf.data(), pf.size() * sizeof(PartFilter), hipMemcpyHostToDevice) !=
-          hipSuccess ||
-      hipMemcpy(base + off_owner, owner.data(), owner.size() * 4, hipMemcpyHostToDevice) !=
-          hipSuccess ||
-      hipMemcpy(base + off_first, work1.data(), work1.size() * sizeof(PartRange),
-                hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemcpy(base + off_ext1, off1.data(), off1.size() * 8, hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemcpy(base + off_ext2, off2.data(), off2.size() * 8, hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemcpy(base + off_w2, work2.data(), work2.size() * sizeof(PartWork), hipMemcpyHostToDevice) !=
-          hipSuccess ||
-      hipMemcpy(base + off_w3, work3.data(), work3.size() * sizeof(PartWork), hipMemcpyHostToDevice) !=
-          hipSuccess)
-    return BF_EDEVICE;
+  for (const Table& t : tables)
+    if (hipMemcpy(base + t.at, t.src, t.bytes, hipMemcpyHostToDevice) != hipSuccess) return BF_EDEVICE;
   part_bind(a, L, b->part_scratch);
-  a.off1 = reinterpret_cast<const uint64_t*>(base + off_ext1);
-  a.off2 = reinterpret_cast<const uint64_t*>(base + off_ext2);
-  a.work2 = reinterpret_cast<const PartWork*>(base + off_w2);
-  a.nwork2 = static_cast<uint32_t>(work2.size());
-  a.work3 = reinterpret_cast<const PartWork*>(base + off_w3);
-  a.nwork3 = static_cast<uint32_t>(work3.size());
-  a.words = pf[0].words;  // the single-filter fields mirror filter 0
-  a.num_blocks = pf[0].num_blocks;
-  a.hash_init = pf[0].hash_init;
-  a.nb_lo = pf[0].nb_lo;
-  a.nb_hi_mask = pf[0].nb_hi_mask;
-  a.filters = reinterpret_cast<const PartFilter*>(base + off_pf);
-  a.chunk_owner = reinterpret_cast<const uint32_t*>(base + off_owner);
-  a.work1 = reinterpret_cast<const PartRange*>(base + off_first);
-  a.nwork1 = static_cast<uint32_t>(work1.size());
-  a.nfilters = nfilters;
-  a.k = f0->k;
-  a.keys = d_keys + h_offsets[0];
+  a.p.filters = reinterpret_cast<const PartFilter*>(base + tables[0].at);
+  a.g.filters = a.p.filters;
+  a.p.chunk_owner = reinterpret_cast<const uint32_t*>(base + tables[1].at);
+  a.g.ranges = reinterpret_cast<const PartRange*>(base + tables[2].at);
+  a.nranges = static_cast<uint32_t>(ranges.size());
+  a.r.list = reinterpret_cast<const PartItem*>(base + tables[3].at);
+  a.p.work = reinterpret_cast<const PartWork*>(base + tables[4].at);
+  a.nwork = static_cast<uint32_t>(work.size());
+  a.p.words = pf[0].words;  // the single-filter fields mirror filter 0
+  a.p.num_blocks = pf[0].num_blocks;
+  a.p.nfilters = nfilters;
+  a.p.k = f0->k;
+  a.g.keys = d_keys + h_offsets[0];
+  a.g.n = n;
   b->part = a;
-  b->part_layout = L;
   b->part_k = k;
   b->partitioned = true;
   b->part_direct.resize(nfilters);
@@ -293,15 +304,14 @@ bf_status build_graph(bf_batch* b) {
     return true;
   };
   if (b->partitioned) {
-    unsigned long long* fills = b->part.fill1;
-    uint64_t nfill = b->part_layout.nfill;
-    void* zargs[] = {&fills, &nfill};
-    void* pargs[] = {&b->part};
-    const dim3 zgrid(static_cast<uint32_t>(std::max<uint64_t>(1, std::min<uint64_t>((nfill + 255) / 256, 4096))));
-    if (!add_node(reinterpret_cast<const void*>(&part_zero_kernel), zgrid, dim3(kZeroThreads), zargs) ||
-        !add_node(b->part_k.scatter1, part_grid1(b->part), dim3(b->part_k.threads1), pargs) ||
-        !add_node(b->part_k.scatter2, part_grid2(b->part), dim3(kScatter2Threads), pargs) ||
-        !add_node(b->part_k.apply, part_grid3(b->part), dim3(kApplyThreads), pargs))
+    void* gargs[] = {&b->part.g};
+    void* rargs[] = {&b->part.r};
+    void* pargs[] = {&b->part.p};
+    if (!add_node(b->part_k.group, part_grid_group(b->part), dim3(b->part_k.threads1), gargs) ||
+        !add_node(b->part_k.plan, dim3(b->part.r.items), dim3(kPlanThreads), rargs) ||
+        !add_node(b->part_k.scan, dim3(1), dim3(kScanThreads), rargs) ||
+        !add_node(b->part_k.regroup, dim3(b->part.r.items), dim3(kGroupThreads), rargs) ||
+        !add_node(b->part_k.apply, part_grid_apply(b->part), dim3(kApplyThreads), pargs))
       return BF_EDEVICE;
   }
   if (!b->partitioned || b->ntiles > 0) {
@@ -474,7 +484,7 @@ bf_status bf_batch_plan(int op, bf_filter* const* filters, uint32_t nfilters,
     }
   } else {
     b->ntiles = 0;
-    b->grid = part_grid1(b->part).x;
+    b->grid = part_grid_group(b->part).x;
   }
   if (build_graph(b) != BF_OK) {
     (void)hipGetLastError();
@@ -497,7 +507,7 @@ bf_status bf_batch_launch_direct(bf_batch* b, void* stream) {
   if (b == nullptr) return BF_EINVAL;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (b->partitioned) {
-    const bf_status st = part_launch(b->part, b->part_layout, b->part_k, s);
+    const bf_status st = part_launch(b->part, b->part_k, s);
     if (st != BF_OK) return st;
   }
   if (b->ntiles > 0) {

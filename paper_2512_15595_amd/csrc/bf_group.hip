@@ -1,0 +1,101 @@
+// bf_group.hip -- the grouping kernels of the partitioned construction and
+// the grouped lookup (bf_group.hpp); they depend on no layout.
+#include <hip/hip_runtime.h>
+
+#include "bf_group.hpp"
+
+namespace bfhip {
+
+namespace {
+
+// The number of output steps of every item: its units, kStepUnits to a step,
+// a batch of kRegroupRuns runs at a time.
+__global__ __launch_bounds__(kPlanThreads) void regroup_plan_kernel(RegroupArgs a) {
+  __shared__ uint32_t wave_sum[kPlanThreads / 64];
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+  const PartItem it = regroup_item(a, blockIdx.x);
+  const uint32_t* entries = a.table1 + it.d1 * a.stride1;
+  uint32_t steps = 0;
+  for (uint32_t base = it.t0; base < it.t1; base += kRegroupRuns) {
+    uint32_t sum = 0;
+    for (uint32_t i = tid; i < kRegroupRuns && base + i < it.t1; i += kPlanThreads)
+      sum += (run_len(entries[base + i]) + kUnit - 1) / kUnit;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) sum += __shfl_down(sum, off, 64);
+    if (lane == 0) wave_sum[wave] = sum;
+    __syncthreads();
+    uint32_t total = 0;
+#pragma unroll
+    for (int w = 0; w < kPlanThreads / 64; ++w) total += wave_sum[w];
+    steps += (total + kStepUnits - 1) / kStepUnits;
+    __syncthreads();
+  }
+  if (tid == 0) a.item_count[blockIdx.x] = steps;
+}
+
+// First output step of every item: prefix sums of the items' step counts.
+__global__ __launch_bounds__(kScanThreads) void regroup_scan_kernel(RegroupArgs a) {
+  __shared__ uint32_t wave_sum[kScanThreads / 64];
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+  uint32_t before = 0;
+  for (uint32_t base = 0; base < a.items; base += kScanThreads) {
+    const uint32_t i = base + tid;
+    const uint32_t c = i < a.items ? a.item_count[i] : 0u;
+    uint32_t incl = c;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint32_t v = __shfl_up(incl, off, 64);
+      if (lane >= static_cast<uint32_t>(off)) incl += v;
+    }
+    if (lane == 63) wave_sum[wave] = incl;
+    __syncthreads();
+    uint32_t mine = before;
+#pragma unroll
+    for (int w = 0; w < kScanThreads / 64; ++w) {
+      const uint32_t s = wave_sum[w];
+      if (static_cast<uint32_t>(w) < wave) mine += s;
+      before += s;
+    }
+    if (i < a.items) a.slot0[i] = mine + incl - c;
+    __syncthreads();
+  }
+  if (tid == 0) a.slot0[a.items] = before;
+}
+
+template <int D, int ROWS>
+const void* keys_fn(bool split, bool multi, bool place) {
+  if (multi) return split || place ? nullptr : reinterpret_cast<const void*>(&group_keys_kernel<D, ROWS, false, true, false>);
+  if (split)
+    return place ? reinterpret_cast<const void*>(&group_keys_kernel<D, ROWS, true, false, true>)
+                 : reinterpret_cast<const void*>(&group_keys_kernel<D, ROWS, true, false, false>);
+  return place ? reinterpret_cast<const void*>(&group_keys_kernel<D, ROWS, false, false, true>)
+               : reinterpret_cast<const void*>(&group_keys_kernel<D, ROWS, false, false, false>);
+}
+
+}  // namespace
+
+const void* group_keys_fn(uint32_t digits, bool split, bool multi, bool place) {
+  if (digits <= 128) return keys_fn<128, 16>(split, multi, place);
+  if (digits <= 256) return keys_fn<256, 16>(split, multi, place);
+  if (digits <= 512) return keys_fn<512, 16>(split, multi, place);
+  if (digits <= 1024) return keys_fn<1024, 8>(split, multi, place);
+  return nullptr;
+}
+
+const void* regroup_fn(uint32_t digits, bool place) {
+  if (digits <= 128)
+    return place ? reinterpret_cast<const void*>(&regroup_kernel<128, 16, true>)
+                 : reinterpret_cast<const void*>(&regroup_kernel<128, 16, false>);
+  if (digits <= 256)
+    return place ? reinterpret_cast<const void*>(&regroup_kernel<256, 16, true>)
+                 : reinterpret_cast<const void*>(&regroup_kernel<256, 16, false>);
+  if (digits <= 512)
+    return place ? reinterpret_cast<const void*>(&regroup_kernel<512, 8, true>)
+                 : reinterpret_cast<const void*>(&regroup_kernel<512, 8, false>);
+  return nullptr;
+}
+
+const void* regroup_plan_fn() { return reinterpret_cast<const void*>(&regroup_plan_kernel); }
+const void* regroup_scan_fn() { return reinterpret_cast<const void*>(&regroup_scan_kernel); }
+
+}  // namespace bfhip

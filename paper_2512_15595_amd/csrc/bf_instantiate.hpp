@@ -63,16 +63,9 @@ void register_batch(Registry& r) {
         reinterpret_cast<const void*>(&bf_batch_kernel<W, S_WORDS, K, kOpAdd>);
     r.batch_fn[batch_index(kOpContains, kBits, S_WORDS, k_index(K))] =
         reinterpret_cast<const void*>(&bf_batch_kernel<W, S_WORDS, K, kOpContains>);
-    r.part1_fn[batch_index(kOpAdd, kBits, S_WORDS, k_index(K))] =
-        reinterpret_cast<const void*>(&part_scatter1_kernel<W, S_WORDS, K>);
-    r.part1_multi_fn[batch_index(kOpAdd, kBits, S_WORDS, k_index(K))] =
-        reinterpret_cast<const void*>(&part_scatter1_kernel<W, S_WORDS, K, 0, true>);
-    r.part1_chunk_fn[batch_index(kOpAdd, kBits, S_WORDS, k_index(K))] =
-        reinterpret_cast<const void*>(&part_scatter1_kernel<W, S_WORDS, K, 0, false, true>);
-    r.part2_fn[batch_index(kOpAdd, kBits, S_WORDS, k_index(K))] =
-        reinterpret_cast<const void*>(&part_scatter2_kernel<W, S_WORDS, K>);
-    r.apply_fn[batch_index(kOpAdd, kBits, S_WORDS, k_index(K))] =
-        reinterpret_cast<const void*>(&part_apply_kernel<W, S_WORDS, K>);
+    const int slot = batch_index(kOpAdd, kBits, S_WORDS, k_index(K));
+    r.apply_fn[0][slot] = reinterpret_cast<const void*>(&part_apply_kernel<W, S_WORDS, K, 0, 16>);
+    r.apply_fn[1][slot] = reinterpret_cast<const void*>(&part_apply_kernel<W, S_WORDS, K, 0, 8>);
   }
 }
 

@@ -57,42 +57,37 @@ struct bf_filter {
 namespace bfhip {
 // Partitioned construction (bf_partition.hip).
 struct PartArgs;
-struct PartLayout {
-  uint64_t off_buf1, off_buf2, off_blk2, off_fill, nfill1, nfill, total;
-  bool chunk_pass;  // one pass: the first scatter writes the chunk buckets
+struct PartLayout {  // byte offsets in the workspace
+  uint64_t rec, table1, lo, blk, table2, item_count, slot0, total;
 };
 struct PartKernels {
-  const void* scatter1;
-  const void* scatter1_multi;  // first scatter of multi-filter plans (sectorized layout)
-  const void* scatter2;
+  const void* group;    // first pass
+  const void* plan;     // second pass (two digits): plan, scan and regroup
+  const void* scan;
+  const void* regroup;
   const void* apply;
-  uint32_t threads1;  // workgroup size of scatter1
-  const void* scatter1_chunk = nullptr;  // first scatter into chunk buckets (one pass)
+  uint32_t threads1;    // workgroup size of the first pass
 };
 bool partition_applicable(const bf_filter* f, uint64_t n);
-// Workspace bytes a partitioned add of n keys takes from the device pool (0
-// if the filter cannot be partitioned).
+// Workspace bytes a partitioned add of n keys is accounted at (0 if the
+// filter cannot be partitioned).
 uint64_t partition_workspace_bytes(const bf_filter* f, uint64_t n);
 bf_status partitioned_add(bf_filter* f, const uint64_t* keys, uint64_t n, hipStream_t stream);
-// One partitioned pass (n keys, at most 2^28 records) over a caller-given
-// workspace of ws_bytes: BF_ESCRATCH if the pass needs more, BF_EINVAL if n
-// needs several passes.  Enqueues the kernels only (no allocation).
+// A partitioned add of n keys (at most 2^28 records) over a caller-given
+// workspace of ws_bytes: BF_ESCRATCH if it is accounted at more, BF_EINVAL
+// beyond 2^28 records.  Enqueues the kernels only (no allocation).
 bf_status partitioned_add_in(bf_filter* f, const uint64_t* keys, uint64_t n, hipStream_t stream,
                              void* ws, uint64_t ws_bytes);
 uint32_t part_chunk_shift(uint32_t words_per_block, uint32_t word_bits);
-bool part_geometry(uint64_t chunks, uint32_t chunk_shift, uint64_t n, PartArgs& a, PartLayout& L);
-// Switches a one-filter geometry to sliced high-digit buckets;
-// records_per_key is 1, or k for the classic filter, whose a.n and a.range1
-// count keys.
-void part_slice(PartArgs& a, PartLayout& L, uint64_t records_per_key);
+bool part_digits(uint64_t chunks, uint32_t chunk_shift, PartArgs& a);
+void part_layout_two(PartArgs& a, PartLayout& L, uint64_t steps, uint64_t items, uint64_t batches, uint64_t runs,
+                     uint64_t records);
 void part_bind(PartArgs& a, const PartLayout& L, void* base);
-void part_buf2(PartLayout& L, uint64_t& off, uint64_t slots);
-PartKernels part_kernels(const bf_filter* f);
-bf_status part_launch(const PartArgs& a, const PartLayout& L, const PartKernels& k, hipStream_t stream);
-dim3 part_grid1(const PartArgs& a);
-dim3 part_grid2(const PartArgs& a);
-dim3 part_grid3(const PartArgs& a);
-__global__ void part_zero_kernel(unsigned long long* p, uint64_t n);
+PartKernels part_kernels(const bf_filter* f, const PartArgs& a);
+bool part_runs(const PartArgs& a, const PartKernels& k);
+bf_status part_launch(const PartArgs& a, const PartKernels& k, hipStream_t stream);
+dim3 part_grid_group(const PartArgs& a);
+dim3 part_grid_apply(const PartArgs& a);
 
 // Filter allocation shared by every create call (bf_api.hip): fills nbytes,
 // device, d_words (zeroed, synchronously).  On error the handle is freed.

@@ -289,25 +289,18 @@ __device__ __forceinline__ void add_tile(const FilterView& fv, const uint64_t* k
   }
 }
 
+// Lookup of the KT hashed keys of every lane (all lanes of the wave call
+// this): res[t] = 1 iff key t's block holds its pattern.
 template <typename W, int S_WORDS, int K, int THETA, int PHI, int KT>
-__device__ __forceinline__ void contains_tile(const FilterView& fv, const uint64_t* keys,
-                                              uint8_t* out, uint32_t count, bool vec_ok,
-                                              uint32_t k,
-                                              const LanePatterns<W, S_WORDS, K, THETA, PHI>& lp) {
-  const uint32_t lane = threadIdx.x & 63u;
-  const uint32_t rank = lane & (THETA - 1);
-  const W* words = static_cast<const W*>(fv.words);
-  uint32_t blk[KT], lo[KT];
-  hash_tile_keys<KT>(fv, keys, count, vec_ok, blk, lo);
-  uint32_t res[KT];
+__device__ __forceinline__ void test_keys(const W* words, const uint32_t (&blk)[KT], const uint32_t (&lo)[KT],
+                                          uint32_t k, const LanePatterns<W, S_WORDS, K, THETA, PHI>& lp,
+                                          uint32_t (&res)[KT]) {
   if constexpr (THETA == 1) {
 #pragma unroll
-    for (int t = 0; t < KT; ++t) {
-      // Out-of-range keys of a partial tile are hashed as key 0 and read an
-      // in-range block; their result is never stored.
-      res[t] = test_block<W, S_WORDS, K, 1, PHI>(words, blk[t], lo[t], lp, k) ? 1u : 0u;
-    }
+    for (int t = 0; t < KT; ++t) res[t] = test_block<W, S_WORDS, K, 1, PHI>(words, blk[t], lo[t], lp, k) ? 1u : 0u;
   } else {
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t rank = lane & (THETA - 1);
     const uint32_t group_shift = lane & ~static_cast<uint32_t>(THETA - 1);
     constexpr uint64_t kGroupMask = (1ull << THETA) - 1ull;
 #pragma unroll
@@ -325,6 +318,20 @@ __device__ __forceinline__ void contains_tile(const FilterView& fv, const uint64
       }(std::make_integer_sequence<int, THETA>{});
     }
   }
+}
+
+template <typename W, int S_WORDS, int K, int THETA, int PHI, int KT>
+__device__ __forceinline__ void contains_tile(const FilterView& fv, const uint64_t* keys,
+                                              uint8_t* out, uint32_t count, bool vec_ok,
+                                              uint32_t k,
+                                              const LanePatterns<W, S_WORDS, K, THETA, PHI>& lp) {
+  const W* words = static_cast<const W*>(fv.words);
+  uint32_t blk[KT], lo[KT];
+  hash_tile_keys<KT>(fv, keys, count, vec_ok, blk, lo);
+  // Out-of-range keys of a partial tile are hashed as key 0 and read an
+  // in-range block; their result is never stored.
+  uint32_t res[KT];
+  test_keys<W, S_WORDS, K, THETA, PHI, KT>(words, blk, lo, k, lp, res);
   const uint32_t first = threadIdx.x * KT;
   if (vec_ok) {
     store_results<KT>(out + first, res);

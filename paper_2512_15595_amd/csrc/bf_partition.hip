@@ -1,5 +1,5 @@
 // bf_partition.hip -- host side of partitioned construction: geometry,
-// bucket capacities, workspace and the launch sequence (kernels in
+// workspace and the launch sequence (kernels in bf_group.hpp and
 // bf_partition.hpp), for one filter and for a table of filters.
 #include <hip/hip_runtime.h>
 
@@ -16,15 +16,10 @@
 
 namespace bfhip {
 
-__global__ __launch_bounds__(kZeroThreads) void part_zero_kernel(unsigned long long* p, uint64_t n) {
-  const uint64_t stride = static_cast<uint64_t>(gridDim.x) * kZeroThreads;
-  for (uint64_t i = static_cast<uint64_t>(blockIdx.x) * kZeroThreads + threadIdx.x; i < n; i += stride)
-    p[i] = 0;
-}
-
 namespace {
 
 uint64_t align256(uint64_t v) { return (v + 255) & ~255ull; }
+uint64_t ceil_div(uint64_t a, uint64_t b) { return (a + b - 1) / b; }
 
 uint32_t ceil_pow2(uint64_t v) {
   uint32_t p = 1;
@@ -32,12 +27,11 @@ uint32_t ceil_pow2(uint64_t v) {
   return p;
 }
 
-// Expected bucket load of uniformly hashed records plus six standard
-// deviations and a fixed margin.
-uint64_t capacity(double mean, uint64_t margin, uint64_t align) {
-  const double c = mean + 6.0 * std::sqrt(mean) + static_cast<double>(margin);
-  const uint64_t v = static_cast<uint64_t>(std::ceil(c));
-  return (v + align - 1) / align * align;
+// Keys of one first-pass step: kStep, or for the classic filter the whole
+// keys whose k records fit it.
+uint64_t step_keys(uint64_t records_per_key) {
+  if (records_per_key <= 1) return kStep;
+  return static_cast<uint64_t>(kClassicThreads) * (kStep / kClassicThreads / records_per_key);
 }
 
 }  // namespace
@@ -49,216 +43,249 @@ uint32_t part_chunk_shift(uint32_t words_per_block, uint32_t word_bits) {
   return shift;
 }
 
-// The chunk buckets' two arrays from byte offset `off` (advanced past them):
-// `slots` lo32 words and kSpareSlots spare ones, then as many 16-bit blocks.
-void part_buf2(PartLayout& L, uint64_t& off, uint64_t slots) {
-  L.off_buf2 = off;
-  off = align256(off + 4 * (slots + kSpareSlots));
-  L.off_blk2 = off;
-  off = align256(off + 2 * (slots + kSpareSlots));
-  L.off_fill = off;
-}
-
-bool part_geometry(uint64_t chunks, uint32_t chunk_shift, uint64_t n, PartArgs& a, PartLayout& L) {
-  a.chunk_shift = chunk_shift;
-  a.chunks = chunks;
-  // digits balanced between the passes: f2 ~ sqrt(chunks)
+// Digits balanced between the passes: f2 ~ sqrt(chunks).  Both passes write
+// whole steps, so their cost hardly depends on the digits; what does is the
+// length of the runs that the next pass reads.
+bool part_digits(uint64_t chunks, uint32_t chunk_shift, PartArgs& a) {
   const uint64_t root = static_cast<uint64_t>(std::ceil(std::sqrt(static_cast<double>(chunks))));
-  a.f2 = std::min<uint32_t>(ceil_pow2(std::max<uint64_t>(root, 1)), kMaxDigits2);
-  a.low_bits = 0;
-  while ((1u << a.low_bits) < a.f2) ++a.low_bits;
-  const uint64_t f1 = (chunks + a.f2 - 1) / a.f2;
-  if (f1 > static_cast<uint64_t>(kMaxDigits) || chunks == 0) return false;
-  a.f1 = static_cast<uint32_t>(f1);
-  a.n = n;
-  uint64_t range = (n + 1023) / 1024;
-  range = (range + kPartStep - 1) / kPartStep * kPartStep;
-  a.range1 = std::max<uint64_t>(range, kPartStep);
-  a.cap1 = capacity(static_cast<double>(n) / a.f1, 4 * kPartStep, 64);
-  a.cap2 = capacity(static_cast<double>(n) / chunks, 64, 16);
-  const uint64_t per_bucket = std::min<uint64_t>(a.cap1, n);
-  a.q = static_cast<uint32_t>(std::clamp<uint64_t>((per_bucket + 65535) / 65536, 1, 32));
-  // A filter of few chunks (L2 or Infinity-Cache sized) leaves too few
-  // digits to fill 256 CUs: cut the second pass into more slices (at least
-  // 16 Ki records each) and split every chunk's records over several apply
-  // workgroups (at least 8 Ki records each), so that both grids reach about
-  // a thousand or two workgroups.  Split slices merge with atomic OR.
-  const uint64_t q_fill = (1024 + a.f1 - 1) / a.f1;
-  a.q = static_cast<uint32_t>(std::clamp<uint64_t>(
-      std::max<uint64_t>(a.q, std::min<uint64_t>(q_fill, per_bucket / 16384)), 1, 1024));
-  const uint64_t split_fill = (2048 + chunks - 1) / chunks;
-  a.apply_split = static_cast<uint32_t>(std::clamp<uint64_t>(
-      std::min<uint64_t>(split_fill, n / chunks / 8192), 1, 1024));
-  uint64_t off = 0;
-  L.off_buf1 = off;
-  a.spare1 = static_cast<uint64_t>(a.f1) * a.cap1;
-  off = align256(off + 8ull * (a.spare1 + kSpareSlots));
-  a.spare2 = chunks * a.cap2;
-  part_buf2(L, off, a.spare2);
-  L.nfill1 = a.f1;
-  L.nfill = a.f1 + chunks;
-  off = align256(off + 8ull * L.nfill);
-  L.total = off;
+  const uint32_t f2 = std::min<uint32_t>(ceil_pow2(std::max<uint64_t>(root, 1)), kMaxDigits2);
+  const uint64_t f1 = ceil_div(chunks, f2);
+  if (chunks == 0 || f1 > static_cast<uint64_t>(kMaxDigits)) return false;
+  a.p.chunk_shift = chunk_shift;
+  a.chunks = chunks;
+  a.p.low_bits = 0;
+  while ((1u << a.p.low_bits) < f2) ++a.p.low_bits;
+  a.g.shift = chunk_shift + a.p.low_bits;
+  a.g.digits = static_cast<uint32_t>(f1);
+  a.r.shift = chunk_shift;
+  a.r.digits = f2;
   return true;
 }
 
-// Sliced high-digit buckets: pass-1 workgroup w owns slice (d, w) of every
-// high digit d, sized for its expected share range1 * records_per_key / f1.
-// Slices hold the slack (six standard deviations) that a shared bucket needs
-// only once, so the first record buffer takes more address space; traffic
-// is unchanged, as only filled records are written and read.
-void part_slice(PartArgs& a, PartLayout& L, uint64_t records_per_key) {
-  a.g1 = static_cast<uint32_t>(std::max<uint64_t>((a.n + a.range1 - 1) / a.range1, 1));
-  a.q = std::min<uint32_t>(a.q, a.g1);  // every pass-2 workgroup reads a slice
-  a.cs1 = capacity(static_cast<double>(a.range1 * records_per_key) / a.f1, 16, 16);
+// The two-pass buffers for `steps` first-pass steps, `items` second-pass
+// items of `batches` batches in all, at most `runs` non-empty runs of the
+// first table and `records` records.  A run of c records is ceil(c / kUnit)
+// units and only a batch's last output step is partial, which bounds the
+// second pass's steps whatever the keys are.
+void part_layout_two(PartArgs& a, PartLayout& L, uint64_t steps, uint64_t items, uint64_t batches, uint64_t runs,
+                     uint64_t records) {
+  a.one_pass = false;
+  a.g.steps = static_cast<uint32_t>(steps);
+  a.g.stride = ceil_div(steps, 16) * 16;
+  a.r.stride1 = a.g.stride;
+  a.r.steps1 = a.g.steps;
+  a.r.items = static_cast<uint32_t>(items);
+  const uint64_t units = records / kUnit + std::min(runs, records);
+  const uint64_t steps2 = units / kStepUnits + batches;
+  a.r.stride2 = ceil_div(steps2, 16) * 16;
   uint64_t off = 0;
-  L.off_buf1 = off;
-  a.spare1 = static_cast<uint64_t>(a.f1) * a.g1 * a.cs1;
-  off = align256(off + 8ull * (a.spare1 + kSpareSlots));
-  a.spare2 = a.chunks * a.cap2;
-  part_buf2(L, off, a.spare2);
-  L.nfill1 = static_cast<uint64_t>(a.f1) * a.g1;
-  L.nfill = L.nfill1 + a.chunks;
-  off = align256(off + 8ull * L.nfill);
+  auto take = [&off](uint64_t bytes) {
+    const uint64_t at = off;
+    off = align256(off + bytes);
+    return at;
+  };
+  L.rec = take(8 * steps * kStep);
+  L.table1 = take(4 * a.g.digits * a.g.stride);
+  L.lo = take(4 * steps2 * kStep);
+  L.blk = take(2 * steps2 * kStep);
+  L.table2 = take(4 * a.r.digits * a.r.stride2);
+  L.item_count = take(4 * items);
+  L.slot0 = take(4 * (items + 1));
   L.total = off;
 }
 
 namespace {
 
-// One pass for a filter of at most kChunkDigits chunks: the first scatter's
-// digit is the chunk (f1 = chunks, no low digit), and it claims runs in the
-// chunk buckets directly, so there is no first record buffer and no second
-// pass.  A digit's run in a step is then 8192 / chunks records on average,
-// down to 8 at 1024 chunks, so more of the stored lines are partial; the
-// second pass it saves costs more (measured on MI355X, 2^26 keys into 16,
-// 32 and 64 MiB of 256-bit blocks: 95, 103 and 102 Gkeys/s in two passes,
-// 139, 133 and 120 in one).
-void chunk_geometry(uint64_t chunks, uint32_t chunk_shift, uint64_t n, PartArgs& a, PartLayout& L) {
-  a.chunk_shift = chunk_shift;
+// One pass for a filter of at most kChunkDigits chunks: the first pass's
+// digit is the chunk, and the apply step reads its runs.
+void one_pass_geometry(uint64_t chunks, uint32_t chunk_shift, uint64_t steps, PartArgs& a, PartLayout& L) {
+  a.one_pass = true;
+  a.p.chunk_shift = chunk_shift;
+  a.p.low_bits = 0;
+  a.p.steps = static_cast<uint32_t>(steps);
   a.chunks = chunks;
-  a.f2 = 1;
-  a.low_bits = 0;
-  a.f1 = static_cast<uint32_t>(chunks);
-  a.q = 1;
-  a.n = n;
-  uint64_t range = (n + 1023) / 1024;
-  range = (range + kPartStep - 1) / kPartStep * kPartStep;
-  a.range1 = std::max<uint64_t>(range, kPartStep);
-  a.cap1 = 0;
-  a.cs1 = 0;
-  a.spare1 = 0;
-  a.cap2 = capacity(static_cast<double>(n) / chunks, 64, 16);
-  const uint64_t split_fill = (2048 + chunks - 1) / chunks;
-  a.apply_split = static_cast<uint32_t>(std::clamp<uint64_t>(
-      std::min<uint64_t>(split_fill, n / chunks / 8192), 1, 1024));
+  a.g.shift = chunk_shift;
+  a.g.digits = static_cast<uint32_t>(chunks);
+  a.g.steps = static_cast<uint32_t>(steps);
+  a.g.stride = ceil_div(steps, 16) * 16;
   uint64_t off = 0;
-  L.off_buf1 = 0;
-  a.spare2 = chunks * a.cap2;
-  part_buf2(L, off, a.spare2);
-  L.nfill1 = 0;
-  L.nfill = chunks;
-  off = align256(off + 8ull * L.nfill);
+  auto take = [&off](uint64_t bytes) {
+    const uint64_t at = off;
+    off = align256(off + bytes);
+    return at;
+  };
+  L.lo = take(4 * steps * kStep);
+  L.blk = take(2 * steps * kStep);
+  L.table1 = take(4 * chunks * a.g.stride);
   L.total = off;
-  L.chunk_pass = true;
 }
 
 }  // namespace
 
 void part_bind(PartArgs& a, const PartLayout& L, void* base_ptr) {
   uint8_t* base = static_cast<uint8_t*>(base_ptr);
-  a.buf1 = reinterpret_cast<uint64_t*>(base + L.off_buf1);
-  a.buf2 = reinterpret_cast<uint32_t*>(base + L.off_buf2);
-  a.blk2 = reinterpret_cast<uint16_t*>(base + L.off_blk2);
-  a.fill1 = reinterpret_cast<unsigned long long*>(base + L.off_fill);
-  a.fill2 = a.fill1 + L.nfill1;
+  a.g.table = reinterpret_cast<uint32_t*>(base + L.table1);
+  uint32_t* lo = reinterpret_cast<uint32_t*>(base + L.lo);
+  uint16_t* blk = reinterpret_cast<uint16_t*>(base + L.blk);
+  a.g.local_mask = (1u << a.p.chunk_shift) - 1;
+  a.p.lo = lo;
+  a.p.blk = blk;
+  if (a.one_pass) {
+    a.g.lo = lo;
+    a.g.blk = blk;
+    a.p.table = a.g.table;
+    a.p.stride = a.g.stride;
+    return;
+  }
+  a.g.rec = reinterpret_cast<uint64_t*>(base + L.rec);
+  a.r.rec = a.g.rec;
+  a.r.table1 = a.g.table;
+  a.r.item_count = reinterpret_cast<uint32_t*>(base + L.item_count);
+  a.r.slot0 = reinterpret_cast<uint32_t*>(base + L.slot0);
+  a.r.lo = lo;
+  a.r.blk = blk;
+  a.r.table2 = reinterpret_cast<uint32_t*>(base + L.table2);
+  a.p.table = a.r.table2;
+  a.p.stride = a.r.stride2;
+  a.p.slot0 = a.r.slot0;
+  a.p.per_digit = a.r.per_digit;
 }
 
-PartKernels part_kernels(const bf_filter* f) {
+// The kernels of a partitioned add of f with geometry a.
+PartKernels part_kernels(const bf_filter* f, const PartArgs& a) {
+  // Units of 8 slots where the runs are short (32 records of a step or
+  // fewer), of 16 where they are longer.
+  const int unit8 = a.one_pass && a.chunks >= 256 ? 1 : 0;
+  PartKernels k{};
+  k.threads1 = kGroupThreads;
   if (f->layout == BF_LAYOUT_CLASSIC) {
     ensure_variant_registry();
     const VariantRegistry& r = variant_registry();
-    const bool pow2 = (f->num_bits & (f->num_bits - 1)) == 0;
-    return PartKernels{r.classic_part1[k_index(f->k) * 2 + (pow2 ? 1 : 0)], nullptr, r.classic_part2,
-                       r.classic_apply, kClassicThreads};
-  }
-  if (f->layout == BF_LAYOUT_CACHE_SECTORIZED) {
+    const int pow2 = (f->num_bits & (f->num_bits - 1)) == 0 ? 1 : 0;
+    k.threads1 = kClassicThreads;
+    k.group = r.classic_group[classic_group_index(k_index(f->k), pow2, a.g.digits, a.one_pass)];
+    k.apply = r.classic_apply[unit8];
+  } else if (f->layout == BF_LAYOUT_CACHE_SECTORIZED) {
     ensure_variant_registry();
-    const VariantRegistry& r = variant_registry();
     const int idx = csbf_part_index(static_cast<int>(f->word_bits), static_cast<int>(f->s),
                                     static_cast<int>(f->groups), k_index(f->k));
-    return PartKernels{r.csbf_part1[idx], nullptr, r.csbf_part2[idx], r.csbf_apply[idx],
-                       kScatter1Threads, r.csbf_part1_chunk[idx]};
+    k.apply = variant_registry().csbf_apply[unit8][idx];
+  } else {
+    const int idx = batch_index(0, static_cast<int>(f->word_bits), static_cast<int>(f->s), k_index(f->k));
+    k.apply = kernel_table(f->salts == kSaltsParquet).apply_fn[unit8][idx];
   }
-  const int idx = batch_index(0, static_cast<int>(f->word_bits), static_cast<int>(f->s),
-                              k_index(f->k));
-  const Registry& r = kernel_table(f->salts == kSaltsParquet);
-  return PartKernels{r.part1_fn[idx], r.part1_multi_fn[idx], r.part2_fn[idx], r.apply_fn[idx],
-                     kScatter1Threads, r.part1_chunk_fn[idx]};
+  if (f->layout != BF_LAYOUT_CLASSIC) k.group = group_keys_fn(a.g.digits, a.one_pass, a.g.ranges != nullptr, false);
+  if (!a.one_pass) {
+    k.plan = regroup_plan_fn();
+    k.scan = regroup_scan_fn();
+    k.regroup = regroup_fn(a.r.digits, false);
+  }
+  return k;
 }
 
-bf_status part_launch(const PartArgs& a, const PartLayout& L, const PartKernels& k,
-                      hipStream_t stream) {
-  if (L.chunk_pass ? (k.scatter1_chunk == nullptr || k.apply == nullptr)
-                   : (k.scatter1 == nullptr || k.scatter2 == nullptr || k.apply == nullptr))
-    return BF_EUNSUPPORTED;
-  // shared buckets' fill counters start at zero; slice counts are written
-  // by their owners
-  const uint64_t zbegin = a.cs1 ? L.nfill1 : 0, zn = L.nfill - zbegin;
-  const uint64_t zgrid = std::min<uint64_t>((zn + kZeroThreads - 1) / kZeroThreads, 4096);
-  hipLaunchKernelGGL(part_zero_kernel, dim3(static_cast<uint32_t>(std::max<uint64_t>(zgrid, 1))),
-                     dim3(kZeroThreads), 0, stream, a.fill1 + zbegin, zn);
+bool part_runs(const PartArgs& a, const PartKernels& k) {
+  return k.group != nullptr && k.apply != nullptr && (a.one_pass || (k.plan != nullptr && k.regroup != nullptr));
+}
+
+bf_status part_launch(const PartArgs& a, const PartKernels& k, hipStream_t stream) {
+  if (!part_runs(a, k)) return BF_EUNSUPPORTED;
   PartArgs copy = a;
-  void* args[] = {&copy};
-  if (L.chunk_pass) {
-    if (hipLaunchKernel(k.scatter1_chunk, part_grid1(a), dim3(kScatter1Threads), args, 0, stream) != hipSuccess ||
-        hipLaunchKernel(k.apply, part_grid3(a), dim3(kApplyThreads), args, 0, stream) != hipSuccess)
-      return BF_EDEVICE;
-  } else if (hipLaunchKernel(k.scatter1, part_grid1(a), dim3(k.threads1), args, 0, stream) != hipSuccess ||
-             hipLaunchKernel(k.scatter2, part_grid2(a), dim3(kScatter2Threads), args, 0, stream) !=
-                 hipSuccess ||
-             hipLaunchKernel(k.apply, part_grid3(a), dim3(kApplyThreads), args, 0, stream) != hipSuccess) {
-    return BF_EDEVICE;
+  void* gargs[] = {&copy.g};
+  void* rargs[] = {&copy.r};
+  void* pargs[] = {&copy.p};
+  hipError_t e = hipLaunchKernel(k.group, part_grid_group(a), dim3(k.threads1), gargs, 0, stream);
+  if (e == hipSuccess && !a.one_pass) {
+    e = hipLaunchKernel(k.plan, dim3(a.r.items), dim3(kPlanThreads), rargs, 0, stream);
+    if (e == hipSuccess) e = hipLaunchKernel(k.scan, dim3(1), dim3(kScanThreads), rargs, 0, stream);
+    if (e == hipSuccess) e = hipLaunchKernel(k.regroup, dim3(a.r.items), dim3(kGroupThreads), rargs, 0, stream);
   }
-  return hipGetLastError() == hipSuccess ? BF_OK : BF_EDEVICE;
+  if (e == hipSuccess) e = hipLaunchKernel(k.apply, part_grid_apply(a), dim3(kApplyThreads), pargs, 0, stream);
+  return e == hipSuccess && hipGetLastError() == hipSuccess ? BF_OK : BF_EDEVICE;
 }
 
-dim3 part_grid1(const PartArgs& a) {
-  if (a.work1) return dim3(a.nwork1);
-  return dim3(static_cast<uint32_t>((a.n + a.range1 - 1) / a.range1));
+dim3 part_grid_group(const PartArgs& a) {
+  if (a.g.ranges) return dim3(a.nranges);
+  return dim3(static_cast<uint32_t>(ceil_div(a.g.steps, a.g.wg_steps)));
 }
-dim3 part_grid2(const PartArgs& a) { return dim3(a.work2 ? a.nwork2 : a.f1 * a.q); }
-dim3 part_grid3(const PartArgs& a) {
-  const uint64_t items = a.work3 ? a.nwork3 : a.chunks * std::max<uint32_t>(a.apply_split, 1);
-  return dim3(static_cast<uint32_t>(std::max<uint64_t>(1, std::min<uint64_t>(items, 65535))));
+dim3 part_grid_apply(const PartArgs& a) {
+  const uint64_t items = a.p.work ? a.nwork : a.chunks * std::max<uint32_t>(a.p.split, 1);
+  return dim3(static_cast<uint32_t>(std::max<uint64_t>(1, items)));
 }
 
 namespace {
 
-// The classic filter is partitioned as blocks of one 32-bit word, with k
-// records per key; its first pass counts keys (a.n, a.range1) in whole steps
-// of kClassicThreads * (kPartStep / kClassicThreads / k) keys.
+// Chunks of a filter and log2 of the blocks in each; the classic filter is
+// partitioned as blocks of one 32-bit word, with k records per key.
+uint64_t filter_chunks(const bf_filter* f, uint32_t* shift) {
+  const bool classic = f->layout == BF_LAYOUT_CLASSIC;
+  *shift = classic ? part_chunk_shift(1, 32) : part_chunk_shift(f->s, f->word_bits);
+  const uint64_t blocks = classic ? f->num_bits / 32 : f->num_blocks;
+  return (blocks + (1ull << *shift) - 1) >> *shift;
+}
+
+uint64_t records_per_key(const bf_filter* f) { return f->layout == BF_LAYOUT_CLASSIC ? f->k : 1; }
+
 bool single_geometry(const bf_filter* f, uint64_t n, PartArgs& a, PartLayout& L) {
-  if (f->layout == BF_LAYOUT_CLASSIC) {
-    const uint32_t shift = part_chunk_shift(1, 32);
-    const uint64_t words = f->num_bits / 32;
-    const uint64_t chunks = (words + (1ull << shift) - 1) >> shift;
-    if (!part_geometry(chunks, shift, n * f->k, a, L)) return false;
-    const uint64_t step = static_cast<uint64_t>(kClassicThreads) * (kPartStep / kClassicThreads / f->k);
-    const uint64_t range = (n + 1023) / 1024;
-    a.n = n;
-    a.range1 = std::max<uint64_t>((range + step - 1) / step * step, step);
-    part_slice(a, L, f->k);
-    return true;
-  }
-  const uint32_t shift = part_chunk_shift(f->s, f->word_bits);
-  const uint64_t chunks = (f->num_blocks + (1ull << shift) - 1) >> shift;
+  uint32_t shift;
+  const uint64_t chunks = filter_chunks(f, &shift);
+  const uint64_t records = n * records_per_key(f);
+  const uint64_t steps = ceil_div(n, step_keys(records_per_key(f)));
+  a.g.n = n;
+  a.g.wg_steps = static_cast<uint32_t>(std::max<uint64_t>(ceil_div(steps, 1024), 1));
+  // A filter of few chunks (L2 or Infinity-Cache sized) leaves too few to
+  // fill 256 CUs: every chunk's records are split over several apply
+  // workgroups (at least 8 Ki records each), about two thousand in all.
+  // Split slices merge with atomic OR.
+  const uint64_t split_fill = ceil_div(2048, chunks);
+  a.p.split =
+      static_cast<uint32_t>(std::clamp<uint64_t>(std::min<uint64_t>(split_fill, records / chunks / 8192), 1, 1024));
   if (chunks <= static_cast<uint64_t>(kChunkDigits)) {
-    chunk_geometry(chunks, shift, n, a, L);
+    one_pass_geometry(chunks, shift, steps, a, L);
     return true;
   }
-  if (!part_geometry(chunks, shift, n, a, L)) return false;
-  part_slice(a, L, 1);
+  if (!part_digits(chunks, shift, a)) return false;
+  // Second-pass items of about 64 Ki records (8 steps), and at least about
+  // 512 of them where every item still has a full step.
+  const uint64_t per_bucket = ceil_div(records, a.g.digits);
+  const uint64_t fill = ceil_div(512, a.g.digits);
+  a.r.per_digit = static_cast<uint32_t>(
+      std::max<uint64_t>(std::max(ceil_div(per_bucket, 65536), std::min<uint64_t>(fill, per_bucket / kStep)), 1));
+  a.r.item_steps = static_cast<uint32_t>(ceil_div(steps, a.r.per_digit));
+  const uint64_t items = static_cast<uint64_t>(a.g.digits) * a.r.per_digit;
+  part_layout_two(a, L, steps, items, items * ceil_div(a.r.item_steps, kRegroupRuns), steps * a.g.digits, records);
   return true;
+}
+
+// The workspace bytes at which a partitioned add is accounted (a server's
+// memory budget, the limit of bf_add_noalloc): 14-22 bytes per key, about 6
+// into a filter that takes one pass.  The sum is that of buckets holding the
+// expected load of uniformly hashed keys plus six standard deviations.
+uint64_t capacity(double mean, uint64_t margin, uint64_t align) {
+  const double c = mean + 6.0 * std::sqrt(mean) + static_cast<double>(margin);
+  return (static_cast<uint64_t>(std::ceil(c)) + align - 1) / align * align;
+}
+
+uint64_t accounted_bytes(const bf_filter* f, uint64_t n) {
+  uint32_t shift;
+  const uint64_t chunks = filter_chunks(f, &shift);
+  const uint64_t per_key = records_per_key(f), records = n * per_key;
+  const bool two = chunks > static_cast<uint64_t>(kChunkDigits) || f->layout == BF_LAYOUT_CLASSIC;
+  constexpr uint64_t kSpare = 64;
+  const uint64_t slots2 = chunks * capacity(static_cast<double>(records) / static_cast<double>(chunks), 64, 16);
+  uint64_t off = 0, fills = chunks;
+  if (two) {
+    PartArgs a{};
+    if (!part_digits(chunks, shift, a)) return 0;
+    const uint64_t keys = step_keys(per_key);
+    const uint64_t range = std::max(ceil_div(ceil_div(n, 1024), keys) * keys, keys);
+    const uint64_t g1 = std::max<uint64_t>(ceil_div(n, range), 1);
+    const uint64_t slice = capacity(static_cast<double>(range * per_key) / a.g.digits, 16, 16);
+    off = align256(8 * (a.g.digits * g1 * slice + kSpare));
+    fills += a.g.digits * g1;
+  }
+  off = align256(off + 4 * (slots2 + kSpare));
+  off = align256(off + 2 * (slots2 + kSpare));
+  return align256(off + 8 * fills);
 }
 
 }  // namespace
@@ -303,34 +330,29 @@ hipMemPool_t workspace_pool(int device) {
   return pool;
 }
 
-}  // namespace
-
-namespace {
 
 // One pass of a partitioned add over the workspace `ws` (at least L.total
 // bytes of the geometry single_geometry gives for n): sets the arguments and
 // enqueues the kernels.
-bf_status partitioned_pass_in(bf_filter* f, const uint64_t* keys, uint64_t n, hipStream_t stream,
-                              PartArgs& a, const PartLayout& L, void* ws) {
-  const PartKernels k = part_kernels(f);
-  if (k.scatter1 == nullptr) return BF_EUNSUPPORTED;
+bf_status partitioned_pass_in(bf_filter* f, const uint64_t* keys, hipStream_t stream, PartArgs& a,
+                              const PartLayout& L, void* ws) {
   part_bind(a, L, ws);
-  a.words = f->d_words;
-  a.num_blocks = f->layout == BF_LAYOUT_CLASSIC ? f->num_bits / 32 : f->num_blocks;
-  a.num_bits = f->num_bits;
+  a.p.words = f->d_words;
+  a.p.num_blocks = f->layout == BF_LAYOUT_CLASSIC ? f->num_bits / 32 : f->num_blocks;
+  a.g.num_bits = f->num_bits;
   if ((f->num_bits & (f->num_bits - 1)) == 0) {
     uint32_t lg = 0;
     while ((1ull << lg) < f->num_bits) ++lg;
-    a.bit_shift = 64 - lg;
+    a.g.bit_shift = 64 - lg;
   }
-  a.hash_init = xxh64_u64_init(f->seed);
-  a.nb_lo = static_cast<uint32_t>(f->num_blocks);
-  a.nb_hi_mask = (f->num_blocks >> 32) ? 0xffffffffu : 0u;
-  a.nfilters = 1;
+  a.g.hash_init = xxh64_u64_init(f->seed);
+  a.g.nb_lo = static_cast<uint32_t>(f->num_blocks);
+  a.g.nb_hi_mask = (f->num_blocks >> 32) ? 0xffffffffu : 0u;
+  a.g.keys = keys;
+  a.p.nfilters = 1;
   // the cache-sectorized rule takes the bits per selected word
-  a.k = f->layout == BF_LAYOUT_CACHE_SECTORIZED ? f->k / f->groups : f->k;
-  a.keys = keys;
-  return part_launch(a, L, k, stream);
+  a.p.k = f->layout == BF_LAYOUT_CACHE_SECTORIZED ? f->k / f->groups : f->k;
+  return part_launch(a, part_kernels(f, a), stream);
 }
 
 // One pass with its workspace taken from the device pool and returned at
@@ -338,8 +360,7 @@ bf_status partitioned_pass_in(bf_filter* f, const uint64_t* keys, uint64_t n, hi
 bf_status partitioned_pass(bf_filter* f, const uint64_t* keys, uint64_t n, hipStream_t stream) {
   PartArgs a{};
   PartLayout L{};
-  if (!single_geometry(f, n, a, L)) return BF_EUNSUPPORTED;
-  if (part_kernels(f).scatter1 == nullptr) return BF_EUNSUPPORTED;
+  if (!single_geometry(f, n, a, L) || !part_runs(a, part_kernels(f, a))) return BF_EUNSUPPORTED;
   hipMemPool_t pool = workspace_pool(f->device);
   if (pool == nullptr) return BF_EDEVICE;
   void* ws = nullptr;
@@ -347,29 +368,44 @@ bf_status partitioned_pass(bf_filter* f, const uint64_t* keys, uint64_t n, hipSt
     (void)hipGetLastError();
     return BF_ENOMEM;
   }
-  bf_status st = partitioned_pass_in(f, keys, n, stream, a, L, ws);
+  bf_status st = partitioned_pass_in(f, keys, stream, a, L, ws);
   if (hipFreeAsync(ws, stream) != hipSuccess && st == BF_OK) st = BF_EDEVICE;
   return st;
 }
 
+uint64_t max_pass_keys(const bf_filter* f) { return std::max<uint64_t>((1ull << 28) / records_per_key(f), 1); }
+
 }  // namespace
 
+// The accounted size decides what is taken; an add whose real workspace is
+// larger than ws_bytes (few keys into a large filter, or a table of many
+// digits) runs in several passes over it, which give the same words.
 bf_status partitioned_add_in(bf_filter* f, const uint64_t* keys, uint64_t n, hipStream_t stream,
                              void* ws, uint64_t ws_bytes) {
-  const uint64_t per_key = f->layout == BF_LAYOUT_CLASSIC ? f->k : 1;
-  if (n == 0 || n > std::max<uint64_t>((1ull << 28) / per_key, 1)) return BF_EINVAL;
+  if (n == 0 || n > max_pass_keys(f)) return BF_EINVAL;
+  if (accounted_bytes(f, n) > ws_bytes) return BF_ESCRATCH;
   PartArgs a{};
   PartLayout L{};
-  if (!single_geometry(f, n, a, L)) return BF_EUNSUPPORTED;
-  if (L.total > ws_bytes) return BF_ESCRATCH;
-  return partitioned_pass_in(f, keys, n, stream, a, L, ws);
+  uint64_t pass = n;
+  for (;; pass = (pass + 1) / 2) {
+    a = PartArgs{};
+    if (!single_geometry(f, pass, a, L) || !part_runs(a, part_kernels(f, a))) return BF_EUNSUPPORTED;
+    if (L.total <= ws_bytes) break;
+    if (pass == 1) return BF_ESCRATCH;
+  }
+  for (uint64_t off = 0; off < n; off += pass) {
+    a = PartArgs{};
+    single_geometry(f, std::min(pass, n - off), a, L);
+    const bf_status st = partitioned_pass_in(f, keys + off, stream, a, L, ws);
+    if (st != BF_OK) return st;
+  }
+  return BF_OK;
 }
 
-// Passes of at most 2^28 records keep the workspace under ~5.5 GB; each pass
+// Passes of at most 2^28 records keep the workspace under ~4.5 GB; each pass
 // after the first reads and writes the touched chunks once more.
 bf_status partitioned_add(bf_filter* f, const uint64_t* keys, uint64_t n, hipStream_t stream) {
-  const uint64_t per_key = f->layout == BF_LAYOUT_CLASSIC ? f->k : 1;
-  const uint64_t max_keys = std::max<uint64_t>((1ull << 28) / per_key, 1);
+  const uint64_t max_keys = max_pass_keys(f);
   for (uint64_t off = 0; off < n; off += max_keys) {
     const bf_status st = partitioned_pass(f, keys + off, std::min(max_keys, n - off), stream);
     if (st != BF_OK) return st;
@@ -378,12 +414,8 @@ bf_status partitioned_add(bf_filter* f, const uint64_t* keys, uint64_t n, hipStr
 }
 
 uint64_t partition_workspace_bytes(const bf_filter* f, uint64_t n) {
-  PartArgs a{};
-  PartLayout L{};
-  const uint64_t per_key = f->layout == BF_LAYOUT_CLASSIC ? f->k : 1;
-  n = std::min(n, std::max<uint64_t>((1ull << 28) / per_key, 1));
-  if (!partition_applicable(f, n) || !single_geometry(f, n, a, L)) return 0;
-  return L.total;
+  n = std::min(n, max_pass_keys(f));
+  return partition_applicable(f, n) ? accounted_bytes(f, n) : 0;
 }
 
 }  // namespace bfhip

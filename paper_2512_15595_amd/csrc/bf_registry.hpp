@@ -56,11 +56,7 @@ constexpr int kBatchRegistrySize = 2 * 2 * kLog2Max * kNumK;
 struct Registry {
   const void* fn[kRegistrySize];
   const void* batch_fn[kBatchRegistrySize];  // persistent batched kernels
-  const void* part1_fn[kBatchRegistrySize];  // partitioned add: first scatter (op slot 0)
-  const void* part1_multi_fn[kBatchRegistrySize];  // ... of a multi-filter plan
-  const void* part1_chunk_fn[kBatchRegistrySize];  // ... into chunk buckets (one pass)
-  const void* part2_fn[kBatchRegistrySize];  // partitioned add: second scatter
-  const void* apply_fn[kBatchRegistrySize];  // partitioned add: per-chunk apply
+  const void* apply_fn[2][kBatchRegistrySize];  // partitioned add: per-chunk apply (op slot 0), units of 16 / 8 slots
 };
 
 Registry& registry();

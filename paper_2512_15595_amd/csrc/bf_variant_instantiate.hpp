@@ -26,10 +26,8 @@ void register_csbf_part(VariantRegistry& r) {
   if constexpr (Z <= S_WORDS && (K == 0 || (K % Z == 0 && K >= Z))) {
     constexpr int kBits = 8 * static_cast<int>(sizeof(W));
     const int idx = csbf_part_index(kBits, S_WORDS, Z, k_index(K));
-    r.csbf_part1[idx] = reinterpret_cast<const void*>(&part_scatter1_kernel<W, S_WORDS, K, Z>);
-    r.csbf_part1_chunk[idx] = reinterpret_cast<const void*>(&part_scatter1_kernel<W, S_WORDS, K, Z, false, true>);
-    r.csbf_part2[idx] = reinterpret_cast<const void*>(&part_scatter2_kernel<W, S_WORDS, K, Z>);
-    r.csbf_apply[idx] = reinterpret_cast<const void*>(&part_apply_kernel<W, S_WORDS, K, Z>);
+    r.csbf_apply[0][idx] = reinterpret_cast<const void*>(&part_apply_kernel<W, S_WORDS, K, Z, 16>);
+    r.csbf_apply[1][idx] = reinterpret_cast<const void*>(&part_apply_kernel<W, S_WORDS, K, Z, 8>);
   }
 }
 

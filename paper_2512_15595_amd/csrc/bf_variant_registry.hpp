@@ -44,6 +44,14 @@ inline int csbf_part_index(int word_bits, int s, int z, int kidx) {
   return (((word_bits == 64 ? 1 : 0) * kLog2Max + ilog2(s)) * kLog2Max + ilog2(z)) * kNumK + kidx;
 }
 
+// First pass of the classic filter's partitioned construction: (k, power-
+// of-two m, one pass, up to 128 / 512 / 1024 digits).
+constexpr int kClassicGroupSize = kNumK * 2 * 2 * 3;
+
+inline int classic_group_index(int kidx, int pow2, uint32_t digits, bool one_pass) {
+  return ((kidx * 2 + pow2) * 2 + (one_pass ? 1 : 0)) * 3 + (digits <= 128 ? 0 : digits <= 512 ? 1 : 2);
+}
+
 // Chained pattern hashing: (op, word bits, s, k).
 constexpr int kChainedSize = 2 * 2 * kLog2Max * kNumK;
 
@@ -55,13 +63,11 @@ struct VariantRegistry {
   const void* chained[kChainedSize];
   const void* classic[kClassicSize];
   const void* csbf[kCsbfSize];
-  const void* classic_part1[kNumK * 2];  // (k, power-of-two m)
-  const void* classic_part2;
-  const void* classic_apply;
-  const void* csbf_part1[kCsbfPartSize];
-  const void* csbf_part1_chunk[kCsbfPartSize];  // one pass into chunk buckets
-  const void* csbf_part2[kCsbfPartSize];
-  const void* csbf_apply[kCsbfPartSize];
+  // partitioned construction: the classic first pass, and the per-chunk
+  // apply with units of 16 / 8 slots
+  const void* classic_group[kClassicGroupSize];
+  const void* classic_apply[2];
+  const void* csbf_apply[2][kCsbfPartSize];
 };
 
 VariantRegistry& variant_registry();

@@ -37,23 +37,34 @@ void register_classic_one(VariantRegistry& r) {
       reinterpret_cast<const void*>(&classic_contains_kernel<K, true, KT>);
 }
 
+template <int K, bool POW2, int D, int ROWS>
+void register_classic_group(VariantRegistry& r) {
+  const int kidx = k_index(K);
+  r.classic_group[classic_group_index(kidx, POW2, D, false)] =
+      reinterpret_cast<const void*>(&group_classic_kernel<K, POW2, D, ROWS, false>);
+  r.classic_group[classic_group_index(kidx, POW2, D, true)] =
+      reinterpret_cast<const void*>(&group_classic_kernel<K, POW2, D, ROWS, true>);
+}
+
 template <int K>
 void register_classic_kt(VariantRegistry& r) {
   register_classic_one<K, 1>(r);
   register_classic_one<K, 2>(r);
   register_classic_one<K, 4>(r);
   if constexpr (K != 0) {
-    r.classic_part1[k_index(K) * 2 + 0] =
-        reinterpret_cast<const void*>(&part_scatter1_classic_kernel<K, false>);
-    r.classic_part1[k_index(K) * 2 + 1] =
-        reinterpret_cast<const void*>(&part_scatter1_classic_kernel<K, true>);
+    register_classic_group<K, false, 128, 16>(r);
+    register_classic_group<K, false, 512, 16>(r);
+    register_classic_group<K, false, 1024, 8>(r);
+    register_classic_group<K, true, 128, 16>(r);
+    register_classic_group<K, true, 512, 16>(r);
+    register_classic_group<K, true, 1024, 8>(r);
   }
 }
 }  // namespace
 
 void register_classic(VariantRegistry& r) {
-  r.classic_part2 = reinterpret_cast<const void*>(&part_scatter2_kernel<uint32_t, 1, 0, -1>);
-  r.classic_apply = reinterpret_cast<const void*>(&part_apply_kernel<uint32_t, 1, 0, -1>);
+  r.classic_apply[0] = reinterpret_cast<const void*>(&part_apply_kernel<uint32_t, 1, 0, -1, 16>);
+  r.classic_apply[1] = reinterpret_cast<const void*>(&part_apply_kernel<uint32_t, 1, 0, -1, 8>);
   register_classic_kt<0>(r);
   register_classic_kt<4>(r);
   register_classic_kt<6>(r);
