@@ -179,7 +179,14 @@ bf_status bf_destroy(bf_filter *f);
 bf_status bf_add(bf_filter *f, const uint64_t *d_keys, uint64_t n, void *stream);
 
 /* Bulk lookup: d_out[i] = 1 if keys[i] may be in the filter, 0 if it is
- * certainly absent (Sec. II-A-1).  d_out is a device array of n bytes. */
+ * certainly absent (Sec. II-A-1).  d_out is a device array of n bytes.
+ * A large lookup (from 4 M keys) of a sectorized filter beyond the L2 (8 MiB
+ * to 2 GiB) with the default mapping groups its keys by filter chunk and
+ * tests every chunk in LDS; it takes 10 (filters up to 64 MiB) to 20 bytes
+ * of workspace per key from the device's stream-ordered pool for the time of
+ * the call, 2^28 keys at a time.  Where there is no such memory, while the
+ * stream is being captured, and with a mapping set by bf_set_mapping, keys
+ * are looked up one by one and nothing is allocated.  Results are the same. */
 bf_status bf_contains(const bf_filter *f, const uint64_t *d_keys, uint64_t n,
                       uint8_t *d_out, void *stream);
 

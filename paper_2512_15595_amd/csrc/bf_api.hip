@@ -190,6 +190,21 @@ bf_status launch(bf_filter* f, int op, const uint64_t* keys, uint64_t n, uint8_t
   return BF_OK;
 }
 
+// Whether a bf_contains of n keys is grouped: with the default mapping (a
+// caller's mapping selects a direct kernel), and not while the stream is
+// being captured (a graph of the lookup then holds no allocation).
+bool groups_lookup(const bf_filter* f, uint64_t n, hipStream_t stream) {
+  if (!lookup_groups(f, n)) return false;
+  const bf_mapping_t& m = f->mapping[BF_OP_CONTAINS];
+  if (m.lanes_per_key || m.words_per_lane || m.keys_per_lane || m.max_workgroups || m.workgroup_threads) return false;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &cap) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return cap == hipStreamCaptureStatusNone;
+}
+
 bf_status clear_words(void* p, uint64_t nbytes, hipStream_t stream) {
   uint64_t nvec = nbytes / 16;
   uint64_t grid = (nvec + 255) / 256;
@@ -478,8 +493,15 @@ bf_status bf_contains(const bf_filter* f, const uint64_t* d_keys, uint64_t n, ui
   if (d_keys == nullptr || d_out == nullptr || reinterpret_cast<uintptr_t>(d_keys) % 8 != 0)
     return BF_EINVAL;
   bf_filter* g = const_cast<bf_filter*>(f);
-  return ordered_call(g, static_cast<hipStream_t>(stream), Access::kUse,
-                      [&] { return launch(g, BF_OP_CONTAINS, d_keys, n, d_out, stream); });
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  return ordered_call(g, s, Access::kUse, [&] {
+    if (groups_lookup(g, n, s)) {
+      bool taken = false;
+      const bf_status st = grouped_lookup(g, d_keys, n, d_out, s, &taken);
+      if (taken) return st;
+    }
+    return launch(g, BF_OP_CONTAINS, d_keys, n, d_out, stream);
+  });
 }
 
 bf_status bf_clear(bf_filter* f, void* stream) {

@@ -38,12 +38,13 @@ __device__ __forceinline__ uint32_t run_len(uint32_t e) { return e >> 16; }
 
 // Workgroups go to the 8 XCDs round-robin by index.  Readers of neighbouring
 // digits share the lines where their runs meet (a run is rarely a whole
-// number of 128-byte lines), so workgroup b takes the work item that puts G
-// consecutive ones on one XCD, whose L2 then fetches such a line once
+// number of 128-byte lines), so workgroup b takes the work item that puts 64
+// consecutive ones (fewer if there are few) on one XCD, whose L2 then fetches such a line once
 // (measured on MI355X: apply of 11.6 M keys into 512 chunks 72.8 -> 68.7 us;
 // no difference at 16,384 chunks, whose lines the Infinity Cache serves).
-__device__ __forceinline__ uint32_t xcd_item(uint32_t b, uint32_t n, uint32_t G) {
-  if (b >= n / (8 * G) * (8 * G)) return b;
+__device__ __forceinline__ uint32_t xcd_item(uint32_t b, uint32_t n) {
+  const uint32_t G = n >= 512 ? 64 : n / 8;
+  if (G == 0 || b >= n / (8 * G) * (8 * G)) return b;
   const uint32_t x = b & 7u, j = b >> 3;
   return (j / G * 8 + x) * G + j % G;
 }
@@ -59,22 +60,24 @@ struct GroupLds {
 };
 
 // Sorts one step: record j of this thread (valid_of(j)) has digit dg[j].
-// On return pos[j] is its place in the sorted step and l.start / l.rows[..
-// row] are set; the caller writes its records to l.stage[pos[j]], passes a
+// On return rank[j] is its number among the digit's records, so that its
+// place in the sorted step is l.start[dg[j]] + rank[j], and l.rows[.. row]
+// is set (a run's length there is at most `clip`: readers then see that many
+// of its records); the caller writes its records to l.stage, passes a
 // barrier and stores the step.  after_rank() runs before the first barrier
 // and after_count() behind it: loads issued there are in flight during the
 // rest of the step.
 // l.cnt is zero on entry and on return.  Two barriers.
 template <int D, int ROWS, int PER, typename ValidOf, typename AfterRank, typename AfterCount>
 __device__ __forceinline__ void group_positions(GroupLds<D, ROWS>& l, const uint32_t (&dg)[PER], ValidOf valid_of,
-                                                uint32_t row, uint32_t (&pos)[PER], AfterRank after_rank,
-                                                AfterCount after_count) {
+                                                uint32_t row, uint32_t clip, uint32_t (&rank)[PER],
+                                                AfterRank after_rank, AfterCount after_count) {
   constexpr int kDig = D / 64;
   const uint32_t tid = threadIdx.x;
 #pragma unroll
   for (int j = 0; j < PER; ++j) {
-    pos[j] = 0;
-    if (valid_of(j)) pos[j] = atomicAdd(&l.cnt[dg[j]], 1u);
+    rank[j] = 0;
+    if (valid_of(j)) rank[j] = atomicAdd(&l.cnt[dg[j]], 1u);
   }
   after_rank();
   __syncthreads();
@@ -98,14 +101,15 @@ __device__ __forceinline__ void group_positions(GroupLds<D, ROWS>& l, const uint
 #pragma unroll
     for (int i = 0; i < kDig; ++i) {
       l.start[tid * kDig + i] = run;
-      l.rows[(tid * kDig + i) * (ROWS + 1) + row] = run_entry(run, c[i]);
+      l.rows[(tid * kDig + i) * (ROWS + 1) + row] = run_entry(run, c[i] < clip ? c[i] : clip);
       run += c[i];
     }
   }
   __syncthreads();
-#pragma unroll
-  for (int j = 0; j < PER; ++j) pos[j] += l.start[dg[j]];
 }
+
+constexpr uint32_t kNoClip = kStep;
+constexpr uint32_t kNoPlace = 0xffffu;  // the place of a record beyond its run's clip
 
 // Writes the table rows [0, nrows) of l.rows for digits below ndigits, as
 // steps first .. first + nrows - 1 of a table of `stride` steps per digit.
@@ -336,7 +340,8 @@ struct GroupArgs {
   uint64_t* rec;        // records of steps * kStep slots: pairs ...
   uint32_t* lo;         // ... or split
   uint16_t* blk;
-  uint16_t* place;      // optional: each key's place in its sorted step
+  uint16_t* place;      // lookups: each key's place in its sorted step (kNoPlace: beyond clip)
+  uint32_t clip;        // lookups: records of a run that readers see
   const PartRange* ranges;    // multi-filter plans
   const PartFilter* filters;
   uint64_t num_bits;    // classic filter
@@ -388,7 +393,7 @@ __global__ __launch_bounds__(kGroupThreads) void group_keys_kernel(GroupArgs a) 
   uint64_t s = begin;
   for (uint32_t t = t0; t < t1; ++t, s += kStep) {
     const uint32_t valid = static_cast<uint32_t>(end - s < kStep ? end - s : kStep);
-    uint32_t blk[kGroupPer], lo[kGroupPer], dg[kGroupPer], pos[kGroupPer];
+    uint32_t blk[kGroupPer], lo[kGroupPer], dg[kGroupPer], rank[kGroupPer];
 #pragma unroll
     for (int j = 0; j < kGroupPer; ++j) {
       const uint64_t h = xxh64_u64(next[j], hinit);
@@ -398,12 +403,15 @@ __global__ __launch_bounds__(kGroupThreads) void group_keys_kernel(GroupArgs a) 
     }
     const uint32_t row = (t - t0) % ROWS;
     auto in = [&](int j) { return tid + j * kGroupThreads < valid; };
-    group_positions(l, dg, in, row, pos, [&] { if (t + 1 < t1) load(s + kStep); }, [] {});
+    group_positions(l, dg, in, row, PLACE ? a.clip : kNoClip, rank, [&] { if (t + 1 < t1) load(s + kStep); }, [] {});
 #pragma unroll
     for (int j = 0; j < kGroupPer; ++j) {
-      if (in(j)) l.stage[pos[j]] = static_cast<uint64_t>(blk[j]) << 32 | lo[j];
+      const uint32_t pos = l.start[dg[j]] + rank[j];
+      if (in(j)) l.stage[pos] = static_cast<uint64_t>(blk[j]) << 32 | lo[j];
       // a whole step of places may be written: the array has kStep per step
-      if constexpr (PLACE) a.place[static_cast<uint64_t>(t) * kStep + tid + j * kGroupThreads] = static_cast<uint16_t>(pos[j]);
+      if constexpr (PLACE)
+        a.place[static_cast<uint64_t>(t) * kStep + tid + j * kGroupThreads] =
+            static_cast<uint16_t>(rank[j] < a.clip ? pos : kNoPlace);
     }
     __syncthreads();
     if constexpr (SPLIT)
@@ -443,7 +451,8 @@ struct RegroupArgs {
   uint16_t* blk;
   uint32_t* table2;
   uint64_t stride2;
-  uint16_t* place;         // lookups: place of each slot's record in the sorted step
+  uint16_t* place;         // lookups: place of each slot's record in the sorted step (kNoPlace: beyond clip)
+  uint32_t clip;
   uint32_t* units;         // lookups: the units a step was read from
 };
 
@@ -451,7 +460,7 @@ struct RegroupArgs {
 __device__ __forceinline__ uint32_t regroup_item_of(const RegroupArgs& a, uint32_t b) {
   if (a.list != nullptr) return b;
   const uint32_t digits1 = a.items / a.per_digit;
-  const uint32_t i = xcd_item(b, a.items, digits1 < 64 ? digits1 : 64);
+  const uint32_t i = xcd_item(b, a.items);
   return i % digits1 * a.per_digit + i / digits1;
 }
 
@@ -536,7 +545,7 @@ __global__ __launch_bounds__(kGroupThreads) void regroup_kernel(RegroupArgs a) {
     load(0);
     for (uint32_t w = 0; w < windows; ++w, ++row) {
       uint64_t r[kGroupPer];
-      uint32_t dg[kGroupPer], pos[kGroupPer];
+      uint32_t dg[kGroupPer], rank[kGroupPer];
       const uint32_t ok = next_ok;
 #pragma unroll
       for (int j = 0; j < kGroupPer; ++j) {
@@ -544,13 +553,15 @@ __global__ __launch_bounds__(kGroupThreads) void regroup_kernel(RegroupArgs a) {
         dg[j] = static_cast<uint32_t>(r[j] >> 32) >> a.shift & mask;
       }
       auto in = [&](int j) { return (ok >> j & 1u) != 0; };
-      group_positions(l.g, dg, in, row % ROWS, pos, [&] { if (w + 1 < windows) find(w + 1); },
+      group_positions(l.g, dg, in, row % ROWS, PLACE ? a.clip : kNoClip, rank, [&] { if (w + 1 < windows) find(w + 1); },
                       [&] { if (w + 1 < windows) load(w + 1); });
       const uint64_t step = first + row;
 #pragma unroll
       for (int j = 0; j < kGroupPer; ++j) {
-        if (in(j)) l.g.stage[pos[j]] = r[j];
-        if constexpr (PLACE) a.place[step * kStep + tid + j * kGroupThreads] = static_cast<uint16_t>(pos[j]);
+        const uint32_t pos = l.g.start[dg[j]] + rank[j];
+        if (in(j)) l.g.stage[pos] = r[j];
+        if constexpr (PLACE)
+          a.place[step * kStep + tid + j * kGroupThreads] = static_cast<uint16_t>(rank[j] < a.clip ? pos : kNoPlace);
       }
       if constexpr (PLACE) {
         if (tid < kStepUnits) {

@@ -56,6 +56,10 @@ void register_parquet(Registry& r) {
       reinterpret_cast<const void*>(&part_apply_kernel<uint32_t, kParquetWords, kParquetK, kZParquet, 16>);
   r.apply_fn[1][slot] =
       reinterpret_cast<const void*>(&part_apply_kernel<uint32_t, kParquetWords, kParquetK, kZParquet, 8>);
+  const int look = batch_index(kOpContains, 32, kParquetWords, kIdxK);
+  r.lookup_fn[0][look] = reinterpret_cast<const void*>(&parquet_lookup_test_kernel<false>);
+  r.lookup_fn[1][look] = reinterpret_cast<const void*>(&parquet_lookup_test_kernel<true>);
+  r.return_fn[look] = reinterpret_cast<const void*>(&parquet_lookup_return_kernel);
 }
 
 }  // namespace bfhip

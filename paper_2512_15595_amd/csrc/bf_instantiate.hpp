@@ -5,6 +5,7 @@
 
 #include "bf_batch_kernels.hpp"
 #include "bf_kernels.hpp"
+#include "bf_lookup.hpp"
 #include "bf_partition.hpp"
 #include "bf_registry.hpp"
 
@@ -66,6 +67,12 @@ void register_batch(Registry& r) {
     const int slot = batch_index(kOpAdd, kBits, S_WORDS, k_index(K));
     r.apply_fn[0][slot] = reinterpret_cast<const void*>(&part_apply_kernel<W, S_WORDS, K, 0, 16>);
     r.apply_fn[1][slot] = reinterpret_cast<const void*>(&part_apply_kernel<W, S_WORDS, K, 0, 8>);
+    const int look = batch_index(kOpContains, kBits, S_WORDS, k_index(K));
+    r.lookup_fn[0][look] = reinterpret_cast<const void*>(&lookup_test_kernel<W, S_WORDS, K, false>);
+    r.return_fn[look] = reinterpret_cast<const void*>(&lookup_return_kernel<W, S_WORDS, K>);
+    // a runtime k over long blocks does not fit the registers of two workgroups per CU
+    if constexpr (K != 0 || S_WORDS * sizeof(W) <= 32)
+      r.lookup_fn[1][look] = reinterpret_cast<const void*>(&lookup_test_kernel<W, S_WORDS, K, true>);
   }
 }
 

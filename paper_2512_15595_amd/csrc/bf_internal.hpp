@@ -89,6 +89,18 @@ bf_status part_launch(const PartArgs& a, const PartKernels& k, hipStream_t strea
 dim3 part_grid_group(const PartArgs& a);
 dim3 part_grid_apply(const PartArgs& a);
 
+// The construction and lookup workspaces' memory pool of a device (nullptr
+// where there is none).
+hipMemPool_t workspace_pool(int device);
+
+// Grouped lookup (bf_lookup.hip): whether a lookup of n keys with the default
+// mapping is grouped, and the lookup itself (*taken false, and nothing
+// enqueued, where it has no kernel or no workspace: the caller looks up
+// directly).
+bool lookup_groups(const bf_filter* f, uint64_t n);
+bf_status grouped_lookup(const bf_filter* f, const uint64_t* keys, uint64_t n, uint8_t* out, hipStream_t stream,
+                         bool* taken);
+
 // Filter allocation shared by every create call (bf_api.hip): fills nbytes,
 // device, d_words (zeroed, synchronously).  On error the handle is freed.
 bf_status alloc_filter_words(bf_filter* f);

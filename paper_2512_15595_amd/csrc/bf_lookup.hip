@@ -1,0 +1,236 @@
+// bf_lookup.hip -- host side of the grouped lookup (bf_lookup.hpp): when it
+// is taken, its workspace and launches, and its return kernels, which depend
+// on no layout.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cmath>
+#include <cstdint>
+
+#include "bf_internal.hpp"
+#include "bf_lookup.hpp"
+#include "bf_partition.hpp"
+#include "bf_registry.hpp"
+
+namespace bfhip {
+
+namespace {
+
+// A second-pass step's results at the slots of the first pass that its
+// records were read from.
+__global__ __launch_bounds__(kReturnThreads) void return_slots_kernel(ReturnSlotsArgs a) {
+  __shared__ __attribute__((aligned(16))) uint8_t res[kStep];
+  __shared__ uint32_t units[kStepUnits];
+  static_assert(kStepUnits == kReturnThreads && kStep / 16 == kReturnThreads, "a unit and a vector per thread");
+  if (blockIdx.x >= *a.nsteps) return;
+  const uint32_t tid = threadIdx.x;
+  const uint64_t s = static_cast<uint64_t>(blockIdx.x) * kStep;
+  reinterpret_cast<u32x4*>(res)[tid] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(a.res + s) + tid);
+  units[tid] = a.units[static_cast<uint64_t>(blockIdx.x) * kStepUnits + tid];
+  uint16_t place[kStep / kReturnThreads];
+#pragma unroll
+  for (int j = 0; j < kStep / kReturnThreads; ++j) place[j] = __builtin_nontemporal_load(a.place + s + tid + j * kReturnThreads);
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < kStep / kReturnThreads; ++j) {
+    const uint32_t p = tid + j * kReturnThreads;
+    const uint32_t u = units[p / kUnit];
+    if (u != 0xffffffffu && p % kUnit <= (u & 15u)) 
+      a.out[(u >> 4) + p % kUnit] = place[j] == kNoPlace ? kUntested : res[place[j]];
+  }
+}
+
+uint64_t align256(uint64_t v) { return (v + 255) & ~255ull; }
+uint64_t ceil_div(uint64_t a, uint64_t b) { return (a + b - 1) / b; }
+
+struct Lookup {
+  GroupArgs g;
+  RegroupArgs r;
+  TestArgs t;
+  ReturnSlotsArgs slots;
+  ReturnArgs keys;
+  bool two;
+  uint64_t chunks;
+  uint64_t steps2;  // second-pass steps at most
+  uint64_t total;   // workspace bytes
+};
+
+// Blocks per test chunk, as a shift.
+uint32_t chunk_shift(const bf_filter* f, bool two) {
+  const uint64_t block = static_cast<uint64_t>(f->s) * f->word_bits / 8;
+  uint32_t shift = 0;
+  while ((block << (shift + 1)) <= static_cast<uint64_t>(test_chunk_bytes(two)) && shift < 16) ++shift;
+  return shift;
+}
+
+// Records of a run that its reader sees: five standard deviations over the
+// mean of uniformly hashed keys.
+uint32_t run_clip(uint32_t digits) {
+  const double mean = static_cast<double>(kStep) / digits;
+  return static_cast<uint32_t>(mean + 5.0 * std::sqrt(mean) + 8.0);
+}
+
+// Geometry and workspace of one pass of n keys (n <= kMaxPass): sets the
+// sizes of `x` and, given a base, the addresses.
+void layout(const bf_filter* f, uint64_t n, uint8_t* base, Lookup& x) {
+  const uint64_t steps = ceil_div(n, kStep);
+  const uint32_t shift = chunk_shift(f, x.two);
+  x.chunks = ceil_div(f->num_blocks, 1ull << shift);
+  uint32_t low = 0;
+  if (x.two)
+    while ((1ull << (2 * low)) < x.chunks) ++low;
+  x.g.n = n;
+  x.g.steps = static_cast<uint32_t>(steps);
+  x.g.wg_steps = static_cast<uint32_t>(std::max<uint64_t>(ceil_div(steps, 1024), 1));
+  x.g.shift = shift + low;
+  x.g.local_mask = (1u << shift) - 1;
+  x.g.digits = static_cast<uint32_t>(ceil_div(x.chunks, 1ull << low));
+  x.g.stride = ceil_div(steps, 16) * 16;
+  x.g.clip = run_clip(x.g.digits);
+  uint64_t off = 0;
+  auto take = [&off, base](uint64_t bytes) {
+    uint8_t* p = base + off;
+    off = align256(off + bytes);
+    return p;
+  };
+  x.g.place = reinterpret_cast<uint16_t*>(take(2 * steps * kStep));
+  x.g.table = reinterpret_cast<uint32_t*>(take(4 * x.g.digits * x.g.stride));
+  x.keys.place = x.g.place;
+  x.keys.n = n;
+  uint64_t slots = steps * kStep;
+  if (x.two) {
+    x.r.shift = shift;
+    x.r.digits = 1u << low;
+    x.r.clip = run_clip(x.r.digits);
+    const uint64_t per_bucket = ceil_div(n, x.g.digits);
+    x.r.per_digit = static_cast<uint32_t>(std::max<uint64_t>(
+        std::max(ceil_div(per_bucket, 65536), std::min<uint64_t>(ceil_div(512, x.g.digits), per_bucket / kStep)), 1));
+    x.r.item_steps = static_cast<uint32_t>(ceil_div(steps, x.r.per_digit));
+    x.r.steps1 = x.g.steps;
+    x.r.stride1 = x.g.stride;
+    x.r.items = x.g.digits * x.r.per_digit;
+    // as for a partitioned add: a run of c records takes ceil(c / kUnit) units
+    const uint64_t units = n / kUnit + std::min(steps * x.g.digits, n);
+    x.steps2 = units / kStepUnits + static_cast<uint64_t>(x.r.items) * ceil_div(x.r.item_steps, kRegroupRuns);
+    x.r.stride2 = ceil_div(x.steps2, 16) * 16;
+    const uint64_t slots2 = x.steps2 * kStep;
+    // the pairs are dead once regrouped: the results of both passes take their place
+    x.g.rec = reinterpret_cast<uint64_t*>(take(std::max(8 * slots, align256(slots2) + slots)));
+    uint8_t* res2 = reinterpret_cast<uint8_t*>(x.g.rec);
+    uint8_t* res1 = res2 + align256(slots2);
+    x.r.rec = x.g.rec;
+    x.r.table1 = x.g.table;
+    x.r.table2 = reinterpret_cast<uint32_t*>(take(4 * x.r.digits * x.r.stride2));
+    x.r.item_count = reinterpret_cast<uint32_t*>(take(4 * x.r.items));
+    x.r.slot0 = reinterpret_cast<uint32_t*>(take(4 * (x.r.items + 1)));
+    x.r.place = reinterpret_cast<uint16_t*>(take(2 * slots2));
+    x.r.units = reinterpret_cast<uint32_t*>(take(4 * x.steps2 * kStepUnits));
+    x.r.lo = reinterpret_cast<uint32_t*>(take(4 * slots2));
+    x.r.blk = reinterpret_cast<uint16_t*>(take(2 * slots2));
+    x.t.table = x.r.table2;
+    x.t.stride = x.r.stride2;
+    x.t.lo = x.r.lo;
+    x.t.blk = x.r.blk;
+    x.t.slot0 = x.r.slot0;
+    x.t.per_digit = x.r.per_digit;
+    x.t.low_bits = low;
+    x.t.res = res2;
+    x.slots.place = x.r.place;
+    x.slots.res = res2;
+    x.slots.out = res1;
+    x.slots.units = x.r.units;
+    x.slots.nsteps = x.r.slot0 + x.r.items;
+    x.keys.res = res1;
+  } else {
+    x.g.lo = reinterpret_cast<uint32_t*>(take(4 * slots));
+    x.g.blk = reinterpret_cast<uint16_t*>(take(2 * slots));
+    x.t.table = x.g.table;
+    x.t.stride = x.g.stride;
+    x.t.lo = x.g.lo;
+    x.t.blk = x.g.blk;
+    x.t.steps = x.g.steps;
+    x.t.res = take(slots);
+    x.keys.res = x.t.res;
+  }
+  // few chunks: each over several workgroups (at least 8 Ki records each)
+  const uint64_t fill = x.two ? 512 : 256;
+  x.t.split = static_cast<uint32_t>(
+      std::clamp<uint64_t>(std::min(ceil_div(fill, x.chunks), n / x.chunks / 8192), 1, 256));
+  x.total = off;
+}
+
+constexpr uint64_t kMaxPass = 1ull << 28;
+
+}  // namespace
+
+// Whether a lookup of n keys is grouped: where the measured break-even lies,
+// with about a fifth to spare.  One digit (up to 64 MiB): about 33 us and
+// 6.2-7.6 ps per key against 9.7, 13.7, 16.6 and 18.5 ps direct at 8, 16, 32
+// and 64 MiB (at 4 MiB, 6.4 ps, most lines still come from the L2: never).
+// Two digits: 60 us and 0.24 us per MiB (every chunk is read) and 10.5 ps
+// per key against 19.5.  Measured grouped / direct, us: 16 MiB 2^22 keys 54 /
+// 64; 8 MiB 2^24 128 / 169; 128 MiB 2^23 168 / 168 and 2^24 251 / 329; 1 GiB
+// 2^25 625 / 642 and 2^26 960 / 1274; 2 GiB 2^26 1176 / 1437.
+bool lookup_groups(const bf_filter* f, uint64_t n) {
+  if (f->layout != BF_LAYOUT_SECTORIZED || f->nbytes < (8ull << 20) || f->nbytes > (2ull << 30)) return false;
+  if (f->nbytes < (16ull << 20)) return n >= (1ull << 24);
+  if (f->nbytes <= (64ull << 20)) return n >= (1ull << 22);
+  return n >= (1ull << 23) + f->nbytes / 36;
+}
+
+bf_status grouped_lookup(const bf_filter* f, const uint64_t* keys, uint64_t n, uint8_t* out, hipStream_t stream,
+                         bool* taken) {
+  *taken = false;
+  const int idx = batch_index(kOpContains, static_cast<int>(f->word_bits), static_cast<int>(f->s), k_index(f->k));
+  Lookup x{};
+  x.two = ceil_div(f->num_blocks, 1ull << chunk_shift(f, false)) > static_cast<uint64_t>(kLookupDigits);
+  const uint64_t pass = std::min(n, kMaxPass);
+  layout(f, pass, nullptr, x);
+  const void* group = group_keys_fn(x.g.digits, !x.two, false, true);
+  const void* regroup = x.two ? regroup_fn(x.r.digits, true) : nullptr;
+  const void* test = kernel_table(f->salts == kSaltsParquet).lookup_fn[x.two ? 1 : 0][idx];
+  const void* ret = kernel_table(f->salts == kSaltsParquet).return_fn[idx];
+  if (group == nullptr || test == nullptr || ret == nullptr || (x.two && regroup == nullptr)) return BF_OK;
+  hipMemPool_t pool = workspace_pool(f->device);
+  void* ws = nullptr;
+  if (pool == nullptr || hipMallocFromPoolAsync(&ws, x.total, pool, stream) != hipSuccess) {
+    (void)hipGetLastError();
+    return BF_OK;  // no workspace: the direct lookup needs none
+  }
+  *taken = true;
+  hipError_t e = hipSuccess;
+  for (uint64_t at = 0; at < n && e == hipSuccess; at += pass) {
+    layout(f, std::min(pass, n - at), static_cast<uint8_t*>(ws), x);
+    x.g.keys = keys + at;
+    x.g.hash_init = xxh64_u64_init(f->seed);
+    x.g.nb_lo = static_cast<uint32_t>(f->num_blocks);
+    x.g.nb_hi_mask = (f->num_blocks >> 32) ? 0xffffffffu : 0u;
+    x.t.words = f->d_words;
+    x.t.nbytes = f->nbytes;
+    x.t.k = f->k;
+    x.keys.out = out + at;
+    x.keys.words = f->d_words;
+    x.keys.keys = x.g.keys;
+    x.keys.hash_init = x.g.hash_init;
+    x.keys.nb_lo = x.g.nb_lo;
+    x.keys.nb_hi_mask = x.g.nb_hi_mask;
+    x.keys.k = f->k;
+    auto run = [&](const void* fn, uint64_t grid, int threads, void* arg) {
+      void* args[] = {arg};
+      if (e == hipSuccess) e = hipLaunchKernel(fn, dim3(static_cast<uint32_t>(grid)), dim3(threads), args, 0, stream);
+    };
+    run(group, ceil_div(x.g.steps, x.g.wg_steps), kGroupThreads, &x.g);
+    if (x.two) {
+      run(regroup_plan_fn(), x.r.items, kPlanThreads, &x.r);
+      run(regroup_scan_fn(), 1, kScanThreads, &x.r);
+      run(regroup, x.r.items, kGroupThreads, &x.r);
+    }
+    run(test, x.chunks * x.t.split, kTestThreads, &x.t);
+    if (x.two) run(reinterpret_cast<const void*>(&return_slots_kernel), x.steps2, kReturnThreads, &x.slots);
+    run(ret, x.g.steps, kReturnThreads, &x.keys);
+  }
+  if (hipFreeAsync(ws, stream) != hipSuccess && e == hipSuccess) e = hipErrorUnknown;
+  return e == hipSuccess ? BF_OK : BF_EDEVICE;
+}
+
+}  // namespace bfhip

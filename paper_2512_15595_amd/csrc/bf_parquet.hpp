@@ -19,6 +19,7 @@
 #include "bf_batch_kernels.hpp"
 #include "bf_hash.hpp"
 #include "bf_kernels.hpp"
+#include "bf_lookup.hpp"
 #include "bf_partition.hpp"
 
 namespace bfhip {
@@ -60,6 +61,16 @@ __global__ __launch_bounds__(kBlockThreads) void parquet_contains_kernel(BfArgs 
   const LanePatterns<uint32_t, kParquetWords, kParquetK, THETA, PHI> lp((threadIdx.x & 63u) & (THETA - 1),
                                                                        ParquetSalts{});
   contains_keys<uint32_t, kParquetWords, kParquetK, THETA, PHI, KT>(a, lp);
+}
+
+// The chunk test of the grouped lookup and its return.
+template <bool TWO>
+__global__ __launch_bounds__(kTestThreads, TWO ? 8 : 4) void parquet_lookup_test_kernel(TestArgs a) {
+  test_chunk<uint32_t, kParquetWords, kParquetK, TWO, ParquetSalts>(a);
+}
+
+inline __global__ __launch_bounds__(kReturnThreads) void parquet_lookup_return_kernel(ReturnArgs a) {
+  return_keys<uint32_t, kParquetWords, kParquetK, ParquetSalts>(a);
 }
 
 // The persistent kernel of batched plans and servers over Parquet filters.

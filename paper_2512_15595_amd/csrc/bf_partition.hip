@@ -301,15 +301,15 @@ bool partition_applicable(const bf_filter* f, uint64_t n) {
   return n > 0 && n < (1ull << 40) && single_geometry(f, 1, a, L);
 }
 
-namespace {
-
 // The construction workspace comes from one stream-ordered memory pool per
 // device: taken at the start of a partitioned add and returned at its end
 // on the same stream, so an add never synchronizes the device and no filter
 // keeps a workspace.  The pool keeps its peak size reserved (release
 // threshold: never), so steady use does not remap memory.
+namespace {
 std::mutex g_pool_mu;
 std::map<int, hipMemPool_t> g_pools;
+}  // namespace
 
 hipMemPool_t workspace_pool(int device) {
   std::lock_guard<std::mutex> lk(g_pool_mu);
@@ -329,6 +329,8 @@ hipMemPool_t workspace_pool(int device) {
   g_pools[device] = pool;
   return pool;
 }
+
+namespace {
 
 
 // One pass of a partitioned add over the workspace `ws` (at least L.total

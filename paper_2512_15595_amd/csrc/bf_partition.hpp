@@ -202,7 +202,7 @@ __global__ __launch_bounds__(kClassicThreads) void group_classic_kernel(GroupArg
     const uint32_t vkeys = static_cast<uint32_t>(a.n - s < kStepKeys ? a.n - s : kStepKeys);
     bool ok[kKeys];
     uint64_t r[kPer];
-    uint32_t dg[kPer], pos[kPer];
+    uint32_t dg[kPer], rank[kPer];
 #pragma unroll
     for (int u = 0; u < kKeys; ++u) {
       const uint32_t idx = tid + u * kClassicThreads;
@@ -224,10 +224,10 @@ __global__ __launch_bounds__(kClassicThreads) void group_classic_kernel(GroupArg
     }
     const uint32_t row = (t - t0) % ROWS;
     auto in = [&](int j) { return j < kRecs && ok[j / K]; };
-    group_positions(l, dg, in, row, pos, [] {}, [] {});
+    group_positions(l, dg, in, row, kNoClip, rank, [] {}, [] {});
 #pragma unroll
     for (int j = 0; j < kPer; ++j)
-      if (in(j)) l.stage[pos[j]] = r[j];
+      if (in(j)) l.stage[l.start[dg[j]] + rank[j]] = r[j];
     __syncthreads();
     if constexpr (SPLIT)
       RecordSplit{a.lo, a.blk}.template store_step<kClassicThreads>(t, l.stage, a.local_mask);
@@ -255,7 +255,7 @@ __global__ __launch_bounds__(kApplyThreads, 8) void part_apply_kernel(ApplyArgs 
   const BlockRule<W, S_WORDS, K, Z> rule;
   const uint32_t blocks_per_chunk = 1u << a.chunk_shift;
   constexpr int kU = 2;  // records per lane: this many used while as many are loaded
-  const uint32_t item = xcd_item(blockIdx.x, gridDim.x, 64);
+  const uint32_t item = xcd_item(blockIdx.x, gridDim.x);
   uint32_t c = item;
   uint32_t si = 0, ns = 1;
   PartWork w{};
