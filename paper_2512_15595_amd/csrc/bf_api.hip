@@ -137,9 +137,9 @@ bf_status validate_mapping(const bf_filter* f, int op, const bf_mapping_t& m) {
 }
 
 bf_status launch(bf_filter* f, int op, const uint64_t* keys, uint64_t n, uint8_t* out,
-                 void* stream) {
+                 void* stream, CallMark* mark) {
   if (f->layout != BF_LAYOUT_SECTORIZED)
-    return variant_launch(f, op, keys, n, out, static_cast<hipStream_t>(stream));
+    return variant_launch(f, op, keys, n, out, static_cast<hipStream_t>(stream), mark);
   const Registry& reg = kernel_table(f->salts == kSaltsParquet);
   bf_mapping_t m = resolve_mapping(f, op, n);
   if (op == BF_OP_ADD && add_partitions(f, n))
@@ -184,8 +184,8 @@ bf_status launch(bf_filter* f, int op, const uint64_t* keys, uint64_t n, uint8_t
   a.nb_hi_mask = (f->num_blocks >> 32) ? 0xffffffffu : 0u;
   a.k = f->k;
   void* args[] = {&a};
-  hipError_t e = hipLaunchKernel(fn, dim3(static_cast<uint32_t>(grid)), dim3(wg), args, 0,
-                                 static_cast<hipStream_t>(stream));
+  const hipError_t e = launch_marked(fn, dim3(static_cast<uint32_t>(grid)), dim3(wg), args,
+                                     static_cast<hipStream_t>(stream), mark);
   if (e != hipSuccess) return BF_EDEVICE;
   return BF_OK;
 }
@@ -205,14 +205,17 @@ bool groups_lookup(const bf_filter* f, uint64_t n, hipStream_t stream) {
   return cap == hipStreamCaptureStatusNone;
 }
 
-bf_status clear_words(void* p, uint64_t nbytes, hipStream_t stream) {
+bf_status clear_words(void* p, uint64_t nbytes, hipStream_t stream, CallMark* mark = nullptr) {
   uint64_t nvec = nbytes / 16;
   uint64_t grid = (nvec + 255) / 256;
   if (grid < 1) grid = 1;
   if (grid > 65536) grid = 65536;
-  hipLaunchKernelGGL(clear_kernel, dim3(static_cast<uint32_t>(grid)), dim3(256), 0, stream,
-                     static_cast<uint8_t*>(p), nbytes);
-  return hipGetLastError() == hipSuccess ? BF_OK : BF_EDEVICE;
+  uint8_t* words = static_cast<uint8_t*>(p);
+  void* args[] = {&words, &nbytes};
+  return launch_marked(reinterpret_cast<const void*>(&clear_kernel), dim3(static_cast<uint32_t>(grid)), dim3(256), args,
+                       stream, mark) == hipSuccess
+             ? BF_OK
+             : BF_EDEVICE;
 }
 
 // Releases the filter's events after either waiting for its last use on
@@ -399,9 +402,9 @@ bool bfhip::add_partitions(const bf_filter* f, uint64_t n) {
 // bookkeeping, for batched plans and servers, which order their own launches
 // (bf_batch.h, bf_serve.h).  Arguments are already validated.
 bf_status bfhip::launch_unordered(bf_filter* f, int op, const uint64_t* keys, uint64_t n,
-                                  uint8_t* out, hipStream_t stream) {
+                                  uint8_t* out, hipStream_t stream, CallMark* mark) {
   if (n == 0) return BF_OK;
-  return launch(f, op, keys, n, out, stream);
+  return launch(f, op, keys, n, out, stream, mark);
 }
 
 extern "C" {
@@ -483,7 +486,7 @@ bf_status bf_add(bf_filter* f, const uint64_t* d_keys, uint64_t n, void* stream)
   if (d_keys == nullptr || reinterpret_cast<uintptr_t>(d_keys) % 8 != 0) return BF_EINVAL;
   hipStream_t s = static_cast<hipStream_t>(stream);
   const Access access = add_partitions(f, n) ? Access::kOwner : Access::kDirect;
-  return ordered_call(f, s, access, [&] { return launch(f, BF_OP_ADD, d_keys, n, nullptr, stream); });
+  return ordered_call(f, s, access, [&](CallMark& mark) { return launch(f, BF_OP_ADD, d_keys, n, nullptr, stream, &mark); });
 }
 
 bf_status bf_contains(const bf_filter* f, const uint64_t* d_keys, uint64_t n, uint8_t* d_out,
@@ -494,27 +497,27 @@ bf_status bf_contains(const bf_filter* f, const uint64_t* d_keys, uint64_t n, ui
     return BF_EINVAL;
   bf_filter* g = const_cast<bf_filter*>(f);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  return ordered_call(g, s, Access::kUse, [&] {
+  return ordered_call(g, s, Access::kUse, [&](CallMark& mark) {
     if (groups_lookup(g, n, s)) {
       bool taken = false;
       const bf_status st = grouped_lookup(g, d_keys, n, d_out, s, &taken);
       if (taken) return st;
     }
-    return launch(g, BF_OP_CONTAINS, d_keys, n, d_out, stream);
+    return launch(g, BF_OP_CONTAINS, d_keys, n, d_out, stream, &mark);
   });
 }
 
 bf_status bf_clear(bf_filter* f, void* stream) {
   if (f == nullptr) return BF_EINVAL;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  return ordered_call(f, s, Access::kUse, [&] { return clear_words(f->d_words, f->nbytes, s); });
+  return ordered_call(f, s, Access::kUse, [&](CallMark& mark) { return clear_words(f->d_words, f->nbytes, s, &mark); });
 }
 
 bf_status bf_export_words(const bf_filter* f, void* dst, uint64_t nbytes, void* stream) {
   if (f == nullptr || dst == nullptr || nbytes < f->nbytes) return BF_EINVAL;
   bf_filter* g = const_cast<bf_filter*>(f);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  return ordered_call(g, s, Access::kUse, [&] {
+  return ordered_call(g, s, Access::kUse, [&](CallMark&) {
     return hipMemcpyAsync(dst, g->d_words, g->nbytes, hipMemcpyDefault, s) == hipSuccess
                ? BF_OK
                : BF_EDEVICE;
@@ -524,7 +527,7 @@ bf_status bf_export_words(const bf_filter* f, void* dst, uint64_t nbytes, void* 
 bf_status bf_import_words(bf_filter* f, const void* src, uint64_t nbytes, void* stream) {
   if (f == nullptr || src == nullptr || nbytes != f->nbytes) return BF_EINVAL;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  return ordered_call(f, s, Access::kUse, [&] {
+  return ordered_call(f, s, Access::kUse, [&](CallMark&) {
     return hipMemcpyAsync(f->d_words, src, f->nbytes, hipMemcpyDefault, s) == hipSuccess
                ? BF_OK
                : BF_EDEVICE;

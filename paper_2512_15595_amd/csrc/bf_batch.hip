@@ -81,19 +81,32 @@ void free_plan(bf_batch* b) {
   delete b;
 }
 
-// Records that the plan's work was enqueued on `stream` (not for a stream
-// being captured: such a launch runs when the caller's graph does, which the
-// caller orders against the plan's destruction).
-bf_status mark_launch(bf_batch* b, hipStream_t stream) {
-  std::lock_guard<std::mutex> lk(b->mark_mu);
+// The mark of a launch of the plan on `stream`: the stream's event (none for
+// a stream being captured: such a launch runs when the caller's graph does,
+// which the caller orders against the plan's destruction).  mark_mu is held.
+CallMark begin_launch(bf_batch* b, hipStream_t stream) {
+  CallMark mark;
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(stream, &cap) == hipSuccess && cap != hipStreamCaptureStatusNone) return BF_OK;
-  hipEvent_t ev = nullptr;
+  if (hipStreamIsCapturing(stream, &cap) == hipSuccess && cap != hipStreamCaptureStatusNone) return mark;
   for (auto& m : b->marks)
-    if (m.first == stream) ev = m.second;
-  if (ev == nullptr && hipEventCreateWithFlags(&ev, hipEventDisableTiming) == hipSuccess)
-    b->marks.emplace_back(stream, ev);
-  if (ev == nullptr || hipEventRecord(ev, stream) != hipSuccess) {
+    if (m.first == stream) mark.event = m.second;
+  if (mark.event == nullptr) {
+    if (hipEventCreateWithFlags(&mark.event, hipEventDisableTiming) == hipSuccess) {
+      b->marks.emplace_back(stream, mark.event);
+    } else {
+      (void)hipGetLastError();
+      mark.event = nullptr;
+      b->unmarked = true;  // destroy waits for the device
+    }
+  }
+  return mark;
+}
+
+// Records the mark where no kernel of the launch signals it.
+bf_status end_launch(bf_batch* b, hipStream_t stream, const CallMark& mark) {
+  if (mark.signalled) return BF_OK;
+  if (mark.event == nullptr) return b->unmarked ? BF_EDEVICE : BF_OK;
+  if (hipEventRecord(mark.event, stream) != hipSuccess) {
     (void)hipGetLastError();
     b->unmarked = true;  // the work is enqueued: destroy must still wait for it
     return BF_EDEVICE;
@@ -499,23 +512,27 @@ bf_status bf_batch_launch(bf_batch* b, void* stream) {
   if (b == nullptr) return BF_EINVAL;
   if (b->ntiles == 0 && !b->partitioned) return BF_OK;
   hipStream_t s = static_cast<hipStream_t>(stream);
+  std::lock_guard<std::mutex> lk(b->mark_mu);
+  const CallMark mark = begin_launch(b, s);
   if (hipGraphLaunch(b->exec, s) != hipSuccess) return BF_EDEVICE;
-  return mark_launch(b, s);
+  return end_launch(b, s, mark);
 }
 
 bf_status bf_batch_launch_direct(bf_batch* b, void* stream) {
   if (b == nullptr) return BF_EINVAL;
+  if (b->ntiles == 0 && !b->partitioned) return BF_OK;
   hipStream_t s = static_cast<hipStream_t>(stream);
+  std::lock_guard<std::mutex> lk(b->mark_mu);
+  CallMark mark = begin_launch(b, s);
   if (b->partitioned) {
     const bf_status st = part_launch(b->part, b->part_k, s);
     if (st != BF_OK) return st;
   }
   if (b->ntiles > 0) {
     void* kargs[] = {&b->args};
-    if (hipLaunchKernel(b->fn, dim3(b->grid), dim3(kBlockThreads), kargs, 0, s) != hipSuccess)
-      return BF_EDEVICE;
+    if (launch_marked(b->fn, dim3(b->grid), dim3(kBlockThreads), kargs, s, &mark) != hipSuccess) return BF_EDEVICE;
   }
-  return b->partitioned || b->ntiles > 0 ? mark_launch(b, s) : BF_OK;
+  return end_launch(b, s, mark);
 }
 
 bf_status bf_batch_launch_per_filter(bf_batch* b, void* stream) {

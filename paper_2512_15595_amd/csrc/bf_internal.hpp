@@ -2,6 +2,7 @@
 // batched entry points.
 #pragma once
 
+#include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -116,8 +117,9 @@ void lib_free(int device, void* p, bool pooled);
 
 // bf_add / bf_contains work without the per-filter stream-order bookkeeping
 // (bf_api.hip), for plans and servers that order their own launches.
+struct CallMark;
 bf_status launch_unordered(bf_filter* f, int op, const uint64_t* keys, uint64_t n, uint8_t* out,
-                           hipStream_t stream);
+                           hipStream_t stream, CallMark* mark = nullptr);
 
 // The measured construction costs of f's layout (bf_tuned.hpp rows; nullptr
 // if none) and the density rule built on them (bf_api.hip).
@@ -147,9 +149,28 @@ inline hipEvent_t new_event() {
   return e;
 }
 
-// Runs `enqueue` (which enqueues one call's work on `stream`) in the stream
-// order of the filter: waits first as `access` requires, then records the
-// filter's last use on `stream`.  The filter's lock is held throughout, so
+// The event that marks the end of a call's work.  A call of one kernel hands
+// it to the launch, whose own completion then signals it; after anything
+// else it is recorded on the stream, which costs the queue a packet of its
+// own (measured on MI355X, a small kernel per call: 4.5 us per call against
+// 7.5 with a recorded event, 2.5 with none).
+struct CallMark {
+  hipEvent_t event = nullptr;  // null while the stream is being captured
+  bool signalled = false;      // by a launch of the call
+};
+
+// Launches `fn`; with a mark, as the call's only kernel, which signals it.
+inline hipError_t launch_marked(const void* fn, dim3 grid, dim3 block, void** args, hipStream_t stream,
+                                CallMark* mark) {
+  if (mark == nullptr || mark->event == nullptr) return hipLaunchKernel(fn, grid, block, args, 0, stream);
+  const hipError_t e = hipExtLaunchKernel(fn, grid, block, args, 0, stream, nullptr, mark->event, 0);
+  if (e == hipSuccess) mark->signalled = true;
+  return e;
+}
+
+// Runs `enqueue(mark)` (which enqueues one call's work on `stream`) in the
+// stream order of the filter: waits first as `access` requires, then marks
+// the filter's last use on `stream`.  The filter's lock is held throughout, so
 // the order decided here is the order enqueued.  Work captured into a HIP
 // graph is ordered by the capturing caller instead (events recorded outside
 // a capture cannot be waited on inside it).
@@ -160,7 +181,8 @@ bf_status ordered_call(bf_filter* f, hipStream_t stream, Access access, F&& enqu
     (void)hipGetLastError();
     cap = hipStreamCaptureStatusNone;
   }
-  if (cap != hipStreamCaptureStatusNone) return enqueue();
+  CallMark mark;
+  if (cap != hipStreamCaptureStatusNone) return enqueue(mark);
   FilterOrder& o = f->order;
   std::lock_guard<std::mutex> lk(o.mu);
   if (access == Access::kOwner) {
@@ -170,17 +192,18 @@ bf_status ordered_call(bf_filter* f, hipStream_t stream, Access access, F&& enqu
   } else if (access == Access::kDirect && o.part_pending) {
     if (hipStreamWaitEvent(stream, o.part_event, 0) != hipSuccess) return BF_EDEVICE;
   }
-  const bf_status st = enqueue();
-  if (st != BF_OK) return st;
-  hipEvent_t ev = nullptr;
   for (const StreamMark& m : o.marks)
-    if (m.stream == stream) ev = m.event;
-  if (ev == nullptr) {
-    ev = new_event();
-    if (ev == nullptr) return BF_EDEVICE;
-    o.marks.push_back(StreamMark{stream, ev});
+    if (m.stream == stream) mark.event = m.event;
+  const bool known = mark.event != nullptr;
+  if (!known && (mark.event = new_event()) == nullptr) return BF_EDEVICE;
+  hipEvent_t ev = mark.event;
+  const bf_status st = enqueue(mark);
+  if (st != BF_OK) {
+    if (!known) (void)hipEventDestroy(ev);
+    return st;
   }
-  if (hipEventRecord(ev, stream) != hipSuccess) return BF_EDEVICE;
+  if (!known) o.marks.push_back(StreamMark{stream, ev});
+  if (!mark.signalled && hipEventRecord(ev, stream) != hipSuccess) return BF_EDEVICE;
   if (access == Access::kOwner) {
     if (o.part_event == nullptr && (o.part_event = new_event()) == nullptr) return BF_EDEVICE;
     if (hipEventRecord(o.part_event, stream) != hipSuccess) return BF_EDEVICE;
@@ -198,5 +221,5 @@ bf_status ordered_call(bf_filter* f, hipStream_t stream, Access access, F&& enqu
 bf_mapping_t variant_resolve_mapping(const bf_filter* f, int op);
 bf_status variant_validate_mapping(const bf_filter* f, int op, const bf_mapping_t& m);
 bf_status variant_launch(bf_filter* f, int op, const uint64_t* keys, uint64_t n, uint8_t* out,
-                         hipStream_t stream);
+                         hipStream_t stream, CallMark* mark);
 }  // namespace bfhip

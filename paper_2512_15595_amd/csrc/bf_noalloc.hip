@@ -82,7 +82,7 @@ extern "C" bf_status bf_add_noalloc(bf_filter* f, const uint64_t* d_keys, uint64
   std::lock_guard<std::mutex> lk(d->mu);
   if (!captured && hipStreamWaitEvent(s, d->last, 0) != hipSuccess) return BF_EDEVICE;
   st = ordered_call(f, s, Access::kOwner,
-                    [&] { return partitioned_add_in(f, d_keys, n, s, d->ptr, kScratchBytes); });
+                    [&](CallMark&) { return partitioned_add_in(f, d_keys, n, s, d->ptr, kScratchBytes); });
   if (st != BF_OK) return st;
   if (!captured && hipEventRecord(d->last, s) != hipSuccess) return BF_EDEVICE;
   return BF_OK;

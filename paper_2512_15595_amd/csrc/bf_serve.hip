@@ -165,13 +165,20 @@ bool launch_group(bf_server* s, const std::vector<Pending>& group, uint64_t grou
     if (hipStreamWaitEvent(sc.s, e, 0) != hipSuccess) return false;
 
   bf_status st = BF_OK;
+  CallMark mark;
+  mark.event = get_event(s);
+  if (mark.event == nullptr) return false;
+  auto refused = [&] {
+    s->event_pool.push_back(mark.event);
+    return false;
+  };
   if (group.size() == 1) {
     const bf_request_t& r = group[0].r;
     bf_filter* f = s->filters[r.filter];
     // the server orders its filters' work itself (the waits above)
-    st = launch_unordered(f, op, r.d_keys, r.n, op == BF_OP_CONTAINS ? r.d_out : nullptr, sc.s);
+    st = launch_unordered(f, op, r.d_keys, r.n, op == BF_OP_CONTAINS ? r.d_out : nullptr, sc.s, &mark);
   } else {
-    if (sc.staged_valid && hipEventSynchronize(sc.staged) != hipSuccess) return false;
+    if (sc.staged_valid && hipEventSynchronize(sc.staged) != hipSuccess) return refused();
     uint64_t ntiles = 0;
     for (size_t i = 0; i < group.size(); ++i) {
       const bf_request_t& r = group[i].r;
@@ -204,7 +211,7 @@ bool launch_group(bf_server* s, const std::vector<Pending>& group, uint64_t grou
         hipMemcpyAsync(sc.d_tiles, sc.h_tiles, ntiles * sizeof(BatchTile), hipMemcpyHostToDevice,
                        sc.s) != hipSuccess ||
         hipEventRecord(sc.staged, sc.s) != hipSuccess)
-      return false;
+      return refused();
     sc.staged_valid = true;
     BatchArgs a{};
     a.filters = sc.d_desc;
@@ -213,13 +220,13 @@ bool launch_group(bf_server* s, const std::vector<Pending>& group, uint64_t grou
     a.k = s->filters[group[0].r.filter]->k;
     void* kargs[] = {&a};
     const uint64_t grid = std::min<uint64_t>(ntiles, static_cast<uint64_t>(s->cus) * 8);
-    if (hipLaunchKernel(s->batch_fn[op], dim3(static_cast<uint32_t>(grid)), dim3(kBlockThreads),
-                        kargs, 0, sc.s) != hipSuccess)
-      return false;
+    if (launch_marked(s->batch_fn[op], dim3(static_cast<uint32_t>(grid)), dim3(kBlockThreads), kargs, sc.s, &mark) !=
+        hipSuccess)
+      return refused();
   }
-  if (st != BF_OK) return false;
-  hipEvent_t ev = get_event(s);
-  if (ev == nullptr || hipEventRecord(ev, sc.s) != hipSuccess) return false;
+  if (st != BF_OK) return refused();
+  hipEvent_t ev = mark.event;
+  if (!mark.signalled && hipEventRecord(ev, sc.s) != hipSuccess) return refused();
 
   LaunchRec rec;
   rec.done = ev;

@@ -211,7 +211,7 @@ bf_status variant_validate_mapping(const bf_filter* f, int op, const bf_mapping_
 }
 
 bf_status variant_launch(bf_filter* f, int op, const uint64_t* keys, uint64_t n, uint8_t* out,
-                         hipStream_t stream) {
+                         hipStream_t stream, CallMark* mark) {
   ensure_variant_registry();
   if (op == BF_OP_ADD && add_partitions(f, n)) return partitioned_add(f, keys, n, stream);
   const bf_mapping_t m = variant_resolve_mapping(f, op);
@@ -245,7 +245,7 @@ bf_status variant_launch(bf_filter* f, int op, const uint64_t* keys, uint64_t n,
     if (g > hard_cap) g = hard_cap;
     if (m.max_workgroups != 0 && g > m.max_workgroups) g = m.max_workgroups;
     void* args[] = {&a};
-    e = hipLaunchKernel(fn, dim3(static_cast<uint32_t>(g)), dim3(kBlockThreads), args, 0, stream);
+    e = launch_marked(fn, dim3(static_cast<uint32_t>(g)), dim3(kBlockThreads), args, stream, mark);
   } else if (f->layout == BF_LAYOUT_CLASSIC) {
     const int pow2 = pow2_u64(f->num_bits) ? 1 : 0;
     const void* fn = variant_registry().classic[classic_index(op, kidx, static_cast<int>(kt), pow2)];
@@ -260,8 +260,7 @@ bf_status variant_launch(bf_filter* f, int op, const uint64_t* keys, uint64_t n,
     a.shift = pow2 ? static_cast<uint32_t>(64 - log2_u64(f->num_bits)) : 0u;
     a.k = f->k;
     void* args[] = {&a};
-    e = hipLaunchKernel(fn, dim3(static_cast<uint32_t>(grid)), dim3(kBlockThreads), args, 0,
-                        stream);
+    e = launch_marked(fn, dim3(static_cast<uint32_t>(grid)), dim3(kBlockThreads), args, stream, mark);
   } else {
     const int theta = kidx == 0 ? 1 : static_cast<int>(m.lanes_per_key);
     if (kidx == 0) kt = 1;
@@ -279,8 +278,7 @@ bf_status variant_launch(bf_filter* f, int op, const uint64_t* keys, uint64_t n,
     a.nb_hi_mask = (f->num_blocks >> 32) ? 0xffffffffu : 0u;
     a.k = f->k / f->groups;  // bits per selected word
     void* args[] = {&a};
-    e = hipLaunchKernel(fn, dim3(static_cast<uint32_t>(grid)), dim3(kBlockThreads), args, 0,
-                        stream);
+    e = launch_marked(fn, dim3(static_cast<uint32_t>(grid)), dim3(kBlockThreads), args, stream, mark);
   }
   return e == hipSuccess ? BF_OK : BF_EDEVICE;
 }
