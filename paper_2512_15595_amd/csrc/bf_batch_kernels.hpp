@@ -76,10 +76,130 @@ __device__ __forceinline__ void batch_tile(const BatchArgs& a, const BatchTile& 
   }
 }
 
+// Whether every size class looks a key up with one lane and the same number
+// of keys per lane: then the lookups' tile walk is pipelined.
+template <typename W, int S_WORDS, int K>
+constexpr bool batch_lookup_pipelines() {
+  constexpr MapSpec m0 = batch_map<W, S_WORDS, K, 1, 0>(), m1 = batch_map<W, S_WORDS, K, 1, 1>(),
+                    m2 = batch_map<W, S_WORDS, K, 1, 2>();
+  return m0.theta == 1 && m1.theta == 1 && m2.theta == 1 && m0.kt == m1.kt && m0.kt == m2.kt &&
+         S_WORDS * sizeof(W) <= 32;
+}
+
+// Lookups with the next tile's loads in flight: otherwise a workgroup pays a
+// tile's chain of dependent loads (tile, filter, keys, blocks) in full for
+// every 512 keys.  Tiles are read three turns ahead, filters two, keys one;
+// the keys are loaded behind this tile's blocks, because loads return in
+// order and a wait for the blocks then leaves the keys in flight.  Measured
+// on MI355X over 4,096 filters of 4 KiB..16 MiB and 2^28 keys: 3.01 -> 2.78 ms
+// (4 KiB filters 221 -> 250 G keys/s, 64 KiB 123 -> 139, 1 MiB 66 -> 65:
+// from 512 KiB on the blocks' fetches from beyond the L2 bound it).  Bringing
+// the next filter to the L2 one turn ahead, by vector or by scalar loads,
+// changed none of these.
+template <typename W, int S_WORDS, int K, typename SALTS>
+__device__ __forceinline__ void batch_lookup_tiles(const BatchArgs& a) {
+  constexpr int KT = static_cast<int>(batch_map<W, S_WORDS, K, 1, 0>().kt);
+  const LanePatterns<W, S_WORDS, K, 1, S_WORDS> lp(0, SALTS{});
+  const uint64_t g = gridDim.x;
+  uint64_t i = blockIdx.x;
+  if (i >= a.ntiles) return;
+  // Nothing writes the tiles and the filter table while the kernel runs:
+  // read as constants they take scalar loads, which the stores of the loop
+  // would otherwise forbid.
+  auto constant = [](const auto* p) {
+    using T = std::remove_cv_t<std::remove_pointer_t<decltype(p)>>;
+    using Word = const __attribute__((address_space(4))) uint32_t;
+    Word* w = (Word*)(p);
+    uint32_t raw[sizeof(T) / 4];
+#pragma unroll
+    for (uint32_t x = 0; x < sizeof(T) / 4; ++x) raw[x] = w[x];
+    return __builtin_bit_cast(T, raw);
+  };
+  const uint64_t last_tile = a.ntiles - 1;
+  auto tile_at = [&](uint64_t i) {
+    BatchTile t = constant(a.tiles + (i < last_tile ? i : last_tile));
+    t.meta = i <= last_tile ? t.meta : 0u;
+    return t;
+  };
+  auto filter_of = [&](const BatchTile& t) { return constant(a.filters + t.filter); };
+  auto global = [](auto* p) {
+    using T = std::remove_pointer_t<decltype(p)>;
+    return (T*)(__attribute__((address_space(1))) T*)(reinterpret_cast<uintptr_t>(p));
+  };
+  // One key per lane and load, whatever the alignment, and every load made on
+  // every path: the compiler can then count the loads that it need not wait
+  // for.  Lanes past the count repeat the last key, a slot without keys (the
+  // padding, the end of the walk) reads the filter table instead.
+  auto load = [&](const BatchTile& t, const BatchFilter& f, uint64_t (&key)[KT]) {
+    const uint32_t count = t.meta & kTileCountMask;
+    const uint64_t* keys = global(count != 0 ? f.keys + t.key_start : reinterpret_cast<const uint64_t*>(a.filters));
+    const uint32_t last = count != 0 ? count - 1 : 0;
+#pragma unroll
+    for (int q = 0; q < KT; ++q) {
+      const uint32_t x = q * kBlockThreads + threadIdx.x;
+      key[q] = __builtin_nontemporal_load(keys + (x < last ? x : last));
+    }
+  };
+  BatchTile t = tile_at(i), t1 = tile_at(i + g), t2 = tile_at(i + 2 * g);
+  BatchFilter f = filter_of(t), f1 = filter_of(t1);
+  uint64_t key[KT];
+  load(t, f, key);
+  // Opaque here, or the compiler merges this load with the loop's and moves
+  // both to the loop's head, where nothing hides them.
+#pragma unroll
+  for (int q = 0; q < KT; ++q) asm("" : "+v"(key[q]));
+  // A tile's results are stored behind the next tile's blocks: a wait for
+  // keys then never waits for a store that was just issued.
+  uint32_t res[KT] = {};
+  uint8_t* out = nullptr;
+  uint32_t out_count = 0;
+  auto store = [&] {
+#pragma unroll
+    for (int q = 0; q < KT; ++q) {
+      const uint32_t x = q * kBlockThreads + threadIdx.x;
+      if (x < out_count) __builtin_nontemporal_store(static_cast<uint8_t>(res[q]), out + x);
+    }
+  };
+  for (; i < a.ntiles; i += g) {
+    const BatchTile t3 = tile_at(i + 3 * g);
+    const BatchFilter f2 = filter_of(t2);
+    uint32_t lo[KT];
+    W v[KT][S_WORDS];
+#pragma unroll
+    for (int q = 0; q < KT; ++q) {
+      const uint64_t h = xxh64_u64(key[q], f.hash_init);
+      lo[q] = static_cast<uint32_t>(h);
+      load_words<W, S_WORDS>(global(static_cast<const W*>(f.words)) +
+                                 static_cast<uint64_t>(block_of(h, f.nb_lo, f.nb_hi_mask)) * S_WORDS, v[q]);
+    }
+    store();
+    load(t1, f1, key);
+#pragma unroll
+    for (int q = 0; q < KT; ++q) {
+      W miss = 0;
+#pragma unroll
+      for (int w = 0; w < S_WORDS; ++w) miss |= lp.word(0, w, lo[q], a.k) & ~v[q][w];
+      res[q] = miss == 0 ? 1u : 0u;
+    }
+    out = global(f.out) + t.key_start;
+    out_count = t.meta & kTileCountMask;
+    t = t1;
+    f = f1;
+    t1 = t2;
+    f1 = f2;
+    t2 = t3;
+  }
+  store();
+}
+
 // The tile walk, for the pattern multipliers SALTS (bf_hash.hpp's salts,
 // or another filter format's table).
 template <typename W, int S_WORDS, int K, int OP, typename SALTS>
 __device__ __forceinline__ void batch_tiles(const BatchArgs& a) {
+  if constexpr (OP == 1 && batch_lookup_pipelines<W, S_WORDS, K>()) {
+    batch_lookup_tiles<W, S_WORDS, K, SALTS>(a);
+    return;
+  }
   for (uint64_t i = blockIdx.x; i < a.ntiles; i += gridDim.x) {
     const BatchTile t = a.tiles[i];
     if ((t.meta & kTileCountMask) == 0) continue;  // padding slot

@@ -1,0 +1,62 @@
+"""Batched lookups at the edges of their tiles: counts around a tile's keys,
+filters without keys, more tiles than the persistent grid has turns in
+flight, keys and results at odd addresses; bit-exact against the CPU oracle.
+"""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+from gpu_helpers import log, to_device
+from oracle import parallel as oracle_par
+from paper_2512_15595_amd import workloads
+
+pytestmark = pytest.mark.gpu
+
+KIB = 1 << 10
+# (filter bytes, keys): the first filter has no keys (the padding slots name it)
+FILTERS = [(64, 0), (32, 1), (4 * KIB, 255), (96, 256), (300 * KIB, 257), (8 * KIB, 511), (64 * KIB, 512),
+           (5 << 20, 513), (16 * KIB, 0), (1 << 20, 1023), (160, 1024), (64 * KIB + 128, 1025),
+           (2 << 20, 20_011), (48 * KIB, 100_003), (128 * KIB, 65_537)]
+MANY = [(256 * KIB, 700_001), (32 * KIB, 1_300_003), (2 << 20, 2_200_005)]  # 8,205 tiles of 512 keys
+
+
+@pytest.mark.parametrize("s,S,k", [(8, 32, 8), (8, 32, 9), (1, 32, 4), (4, 64, 16), (16, 64, 16)])
+@pytest.mark.parametrize("many", [False, True])
+def test_batched_lookup_at_tile_edges(s, S, k, many):
+    from paper_2512_15595_amd import bf
+
+    shapes = FILTERS + (MANY if many else [])
+    block = s * S // 8
+    blocks = [max(1, nbytes // block) for nbytes, _ in shapes]
+    counts = [n for _, n in shapes]
+    offsets = np.concatenate([[0], np.cumsum(counts)])
+    total = int(offsets[-1])
+    log(f"batched lookup edges s={s} S={S} k={k}: {len(shapes)} filters, {total} keys")
+    g = workloads.rng(s + S + k)
+    keys = g.integers(0, 2**64, size=total, dtype=np.uint64)
+    # three quarters of the bits set: both results occur
+    words = [g.integers(0, 256, size=nb * block, dtype=np.uint8) | g.integers(0, 256, size=nb * block, dtype=np.uint8)
+             for nb in blocks]
+    want = np.concatenate([oracle_par.contains(words[i], nb, s, S, k, i, keys[offsets[i]:offsets[i + 1]])
+                           for i, nb in enumerate(blocks) if counts[i] > 0])
+    filters = [bf.BloomFilter(nb, s, S, k, i) for i, nb in enumerate(blocks)]
+    try:
+        for f, w in zip(filters, words):
+            f.load_words(torch.from_numpy(w).to("cuda"))
+        d = to_device(keys, offset_elems=1)
+        out = torch.full((total + 32,), 7, dtype=torch.uint8, device="cuda")
+        plan = bf.BatchPlan(bf.BF_OP_CONTAINS, filters, d, offsets, out[3:total + 3])
+        try:
+            for launch in (plan.launch, plan.launch_direct):
+                out.fill_(7)
+                launch()
+                got = out.cpu().numpy()
+                assert np.array_equal(got[3:total + 3], want)
+                assert (got[:3] == 7).all() and (got[total + 3:] == 7).all()
+        finally:
+            plan.close()
+    finally:
+        for f in filters:
+            f.close()
