@@ -190,13 +190,15 @@ bf_status launch(bf_filter* f, int op, const uint64_t* keys, uint64_t n, uint8_t
   return BF_OK;
 }
 
+bool default_mapping(const bf_mapping_t& m) {
+  return !m.lanes_per_key && !m.words_per_lane && !m.keys_per_lane && !m.max_workgroups && !m.workgroup_threads;
+}
+
 // Whether a bf_contains of n keys is grouped: with the default mapping (a
 // caller's mapping selects a direct kernel), and not while the stream is
 // being captured (a graph of the lookup then holds no allocation).
 bool groups_lookup(const bf_filter* f, uint64_t n, hipStream_t stream) {
-  if (!lookup_groups(f, n)) return false;
-  const bf_mapping_t& m = f->mapping[BF_OP_CONTAINS];
-  if (m.lanes_per_key || m.words_per_lane || m.keys_per_lane || m.max_workgroups || m.workgroup_threads) return false;
+  if (!lookup_groups(f, n) || !default_mapping(f->mapping[BF_OP_CONTAINS])) return false;
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(stream, &cap) != hipSuccess) {
     (void)hipGetLastError();
@@ -501,6 +503,11 @@ bf_status bf_contains(const bf_filter* f, const uint64_t* d_keys, uint64_t n, ui
     if (groups_lookup(g, n, s)) {
       bool taken = false;
       const bf_status st = grouped_lookup(g, d_keys, n, d_out, s, &taken);
+      if (taken) return st;
+    }
+    if (lookup_fits_lds(g, n) && default_mapping(g->mapping[BF_OP_CONTAINS])) {
+      bool taken = false;
+      const bf_status st = resident_lookup(g, d_keys, n, d_out, s, &mark, &taken);
       if (taken) return st;
     }
     return launch(g, BF_OP_CONTAINS, d_keys, n, d_out, stream, &mark);

@@ -86,6 +86,26 @@ constexpr bool batch_lookup_pipelines() {
          S_WORDS * sizeof(W) <= 32;
 }
 
+// An object that nothing writes while the kernel runs (tiles, the filter
+// table): read as a constant it takes scalar loads, which a kernel's stores
+// would otherwise forbid.
+template <typename T>
+__device__ __forceinline__ T read_constant(const T* p) {
+  using Word = const __attribute__((address_space(4))) uint32_t;
+  Word* w = (Word*)(p);
+  uint32_t raw[sizeof(T) / 4];
+#pragma unroll
+  for (uint32_t x = 0; x < sizeof(T) / 4; ++x) raw[x] = w[x];
+  return __builtin_bit_cast(T, raw);
+}
+
+// A pointer to global memory that came from such an object: without the cast
+// its accesses would be flat ones, whose waits cover the scalar loads too.
+template <typename T>
+__device__ __forceinline__ T* as_global(T* p) {
+  return (T*)(__attribute__((address_space(1))) T*)(reinterpret_cast<uintptr_t>(p));
+}
+
 // Lookups with the next tile's loads in flight: otherwise a workgroup pays a
 // tile's chain of dependent loads (tile, filter, keys, blocks) in full for
 // every 512 keys.  Tiles are read three turns ahead, filters two, keys one;
@@ -103,36 +123,20 @@ __device__ __forceinline__ void batch_lookup_tiles(const BatchArgs& a) {
   const uint64_t g = gridDim.x;
   uint64_t i = blockIdx.x;
   if (i >= a.ntiles) return;
-  // Nothing writes the tiles and the filter table while the kernel runs:
-  // read as constants they take scalar loads, which the stores of the loop
-  // would otherwise forbid.
-  auto constant = [](const auto* p) {
-    using T = std::remove_cv_t<std::remove_pointer_t<decltype(p)>>;
-    using Word = const __attribute__((address_space(4))) uint32_t;
-    Word* w = (Word*)(p);
-    uint32_t raw[sizeof(T) / 4];
-#pragma unroll
-    for (uint32_t x = 0; x < sizeof(T) / 4; ++x) raw[x] = w[x];
-    return __builtin_bit_cast(T, raw);
-  };
   const uint64_t last_tile = a.ntiles - 1;
   auto tile_at = [&](uint64_t i) {
-    BatchTile t = constant(a.tiles + (i < last_tile ? i : last_tile));
+    BatchTile t = read_constant(a.tiles + (i < last_tile ? i : last_tile));
     t.meta = i <= last_tile ? t.meta : 0u;
     return t;
   };
-  auto filter_of = [&](const BatchTile& t) { return constant(a.filters + t.filter); };
-  auto global = [](auto* p) {
-    using T = std::remove_pointer_t<decltype(p)>;
-    return (T*)(__attribute__((address_space(1))) T*)(reinterpret_cast<uintptr_t>(p));
-  };
+  auto filter_of = [&](const BatchTile& t) { return read_constant(a.filters + t.filter); };
   // One key per lane and load, whatever the alignment, and every load made on
   // every path: the compiler can then count the loads that it need not wait
   // for.  Lanes past the count repeat the last key, a slot without keys (the
   // padding, the end of the walk) reads the filter table instead.
   auto load = [&](const BatchTile& t, const BatchFilter& f, uint64_t (&key)[KT]) {
     const uint32_t count = t.meta & kTileCountMask;
-    const uint64_t* keys = global(count != 0 ? f.keys + t.key_start : reinterpret_cast<const uint64_t*>(a.filters));
+    const uint64_t* keys = as_global(count != 0 ? f.keys + t.key_start : reinterpret_cast<const uint64_t*>(a.filters));
     const uint32_t last = count != 0 ? count - 1 : 0;
 #pragma unroll
     for (int q = 0; q < KT; ++q) {
@@ -169,7 +173,7 @@ __device__ __forceinline__ void batch_lookup_tiles(const BatchArgs& a) {
     for (int q = 0; q < KT; ++q) {
       const uint64_t h = xxh64_u64(key[q], f.hash_init);
       lo[q] = static_cast<uint32_t>(h);
-      load_words<W, S_WORDS>(global(static_cast<const W*>(f.words)) +
+      load_words<W, S_WORDS>(as_global(static_cast<const W*>(f.words)) +
                                  static_cast<uint64_t>(block_of(h, f.nb_lo, f.nb_hi_mask)) * S_WORDS, v[q]);
     }
     store();
@@ -181,7 +185,7 @@ __device__ __forceinline__ void batch_lookup_tiles(const BatchArgs& a) {
       for (int w = 0; w < S_WORDS; ++w) miss |= lp.word(0, w, lo[q], a.k) & ~v[q][w];
       res[q] = miss == 0 ? 1u : 0u;
     }
-    out = global(f.out) + t.key_start;
+    out = as_global(f.out) + t.key_start;
     out_count = t.meta & kTileCountMask;
     t = t1;
     f = f1;

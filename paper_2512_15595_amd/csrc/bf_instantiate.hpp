@@ -8,6 +8,7 @@
 #include "bf_lookup.hpp"
 #include "bf_partition.hpp"
 #include "bf_registry.hpp"
+#include "bf_resident.hpp"
 
 namespace bfhip {
 
@@ -68,6 +69,10 @@ void register_batch(Registry& r) {
     r.apply_fn[0][slot] = reinterpret_cast<const void*>(&part_apply_kernel<W, S_WORDS, K, 0, 16>);
     r.apply_fn[1][slot] = reinterpret_cast<const void*>(&part_apply_kernel<W, S_WORDS, K, 0, 8>);
     const int look = batch_index(kOpContains, kBits, S_WORDS, k_index(K));
+    if constexpr (lookup_resides<W, S_WORDS>()) {
+      r.resident_fn[0][look] = reinterpret_cast<const void*>(&bf_resident_kernel<W, S_WORDS, K, 0>);
+      r.resident_fn[1][look] = reinterpret_cast<const void*>(&bf_resident_kernel<W, S_WORDS, K, 1>);
+    }
     r.lookup_fn[0][look] = reinterpret_cast<const void*>(&lookup_test_kernel<W, S_WORDS, K, false>);
     r.return_fn[look] = reinterpret_cast<const void*>(&lookup_return_kernel<W, S_WORDS, K>);
     // a runtime k over long blocks does not fit the registers of two workgroups per CU

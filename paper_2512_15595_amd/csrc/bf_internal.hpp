@@ -102,6 +102,13 @@ bool lookup_groups(const bf_filter* f, uint64_t n);
 bf_status grouped_lookup(const bf_filter* f, const uint64_t* keys, uint64_t n, uint8_t* out, hipStream_t stream,
                          bool* taken);
 
+// The same for a lookup whose filter fits the LDS (bf_resident.hpp); it takes
+// no workspace.
+struct CallMark;
+bool lookup_fits_lds(const bf_filter* f, uint64_t n);
+bf_status resident_lookup(const bf_filter* f, const uint64_t* keys, uint64_t n, uint8_t* out, hipStream_t stream,
+                          CallMark* mark, bool* taken);
+
 // Filter allocation shared by every create call (bf_api.hip): fills nbytes,
 // device, d_words (zeroed, synchronously).  On error the handle is freed.
 bf_status alloc_filter_words(bf_filter* f);

@@ -11,6 +11,7 @@
 #include "bf_lookup.hpp"
 #include "bf_partition.hpp"
 #include "bf_registry.hpp"
+#include "bf_resident.hpp"
 
 namespace bfhip {
 
@@ -176,6 +177,46 @@ bool lookup_groups(const bf_filter* f, uint64_t n) {
   if (f->nbytes < (16ull << 20)) return n >= (1ull << 24);
   if (f->nbytes <= (64ull << 20)) return n >= (1ull << 22);
   return n >= (1ull << 23) + f->nbytes / 36;
+}
+
+// The line for lookups in LDS, each side measured on MI355X with 32-byte
+// blocks and k = 8 (us, direct against LDS): 2^20 keys 7.4 against 7.0..7.6 at
+// every size; 2^21 keys 8.2 against 7.8 in 4 KiB, 9.4 against 9.0 in 16 KiB,
+// 10.7 against 9.7 in 64 KiB, 11.5 against 9.7 in 128 KiB; 2^22 keys 14.8
+// against 13.9, 15.4 against 15.2, 18.3 against 15.2, 19.7 against 16.0; 2^26
+// keys 243 against 207, 222 against 178, 277 against 174, 293 against 205.
+// 4-byte blocks lose 0.3 us at 2^21 keys in 16 KiB, hence the two lines.
+bool lookup_fits_lds(const bf_filter* f, uint64_t n) {
+  return f->layout == BF_LAYOUT_SECTORIZED && f->nbytes <= kResidentBytes[1] &&
+         n >= (f->nbytes > (16u << 10) ? 1ull << 21 : 1ull << 22);
+}
+
+bf_status resident_lookup(const bf_filter* f, const uint64_t* keys, uint64_t n, uint8_t* out, hipStream_t stream,
+                          CallMark* mark, bool* taken) {
+  *taken = false;
+  const int big = f->nbytes > kResidentBytes[0];
+  const int idx = batch_index(kOpContains, static_cast<int>(f->word_bits), static_cast<int>(f->s), k_index(f->k));
+  const void* fn = kernel_table(f->salts == kSaltsParquet).resident_fn[big][idx];
+  if (fn == nullptr) return BF_OK;
+  ResidentArgs a{};
+  a.f.words = f->d_words;
+  a.f.hash_init = xxh64_u64_init(f->seed);
+  a.f.nb_lo = static_cast<uint32_t>(f->num_blocks);
+  a.f.keys = keys;
+  a.f.out = out;
+  a.n = n;
+  a.k = f->k;
+  // whole turns of the workgroups that 256 CUs hold
+  const uint64_t slots = big ? 256 : 512;
+  const uint64_t turns = ceil_div(n, slots * kResidentKeys);
+  a.per = static_cast<uint32_t>(ceil_div(ceil_div(n, slots * turns), 2048ull) * 2048);  // of whole loop turns
+  const uint64_t grid = ceil_div(n, static_cast<uint64_t>(a.per));
+  if (grid > 0x7fffffffu) return BF_OK;
+  void* kargs[] = {&a};
+  *taken = true;
+  return launch_marked(fn, dim3(static_cast<uint32_t>(grid)), dim3(kResidentThreads), kargs, stream, mark) == hipSuccess
+             ? BF_OK
+             : BF_EDEVICE;
 }
 
 bf_status grouped_lookup(const bf_filter* f, const uint64_t* keys, uint64_t n, uint8_t* out, hipStream_t stream,

@@ -17,6 +17,7 @@
 #include <stdint.h>
 
 #include "bf_batch_kernels.hpp"
+#include "bf_resident.hpp"
 #include "bf_hash.hpp"
 #include "bf_kernels.hpp"
 #include "bf_lookup.hpp"
@@ -77,6 +78,11 @@ inline __global__ __launch_bounds__(kReturnThreads) void parquet_lookup_return_k
 template <int OP>
 __global__ __launch_bounds__(kBlockThreads) void parquet_batch_kernel(BatchArgs a) {
   batch_tiles<uint32_t, kParquetWords, kParquetK, OP, ParquetSalts>(a);
+}
+
+template <int BIG>
+__global__ __launch_bounds__(kResidentThreads, BIG ? 4 : 8) void parquet_resident_kernel(ResidentArgs a) {
+  resident_lookup<uint32_t, kParquetWords, kParquetK, BIG, ParquetSalts>(a);
 }
 
 }  // namespace bfhip

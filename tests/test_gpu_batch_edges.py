@@ -1,6 +1,7 @@
 """Batched lookups at the edges of their tiles: counts around a tile's keys,
 filters without keys, more tiles than the persistent grid has turns in
-flight, keys and results at odd addresses; bit-exact against the CPU oracle.
+flight, keys and results at odd addresses; and lookups in filters that fit the
+LDS, at the edges of their sizes; bit-exact against the CPU oracle.
 """
 from __future__ import annotations
 
@@ -18,7 +19,8 @@ KIB = 1 << 10
 # (filter bytes, keys): the first filter has no keys (the padding slots name it)
 FILTERS = [(64, 0), (32, 1), (4 * KIB, 255), (96, 256), (300 * KIB, 257), (8 * KIB, 511), (64 * KIB, 512),
            (5 << 20, 513), (16 * KIB, 0), (1 << 20, 1023), (160, 1024), (64 * KIB + 128, 1025),
-           (2 << 20, 20_011), (48 * KIB, 100_003), (128 * KIB, 65_537)]
+           (2 << 20, 20_011), (48 * KIB, 100_003), (80 * KIB, 32_768), (80 * KIB + 256, 32_769), (96 * KIB, 4_000),
+           (128 * KIB, 65_537), (160 * KIB, 2_049), (160 * KIB + 256, 6_000), (164, 5_000)]
 MANY = [(256 * KIB, 700_001), (32 * KIB, 1_300_003), (2 << 20, 2_200_005)]  # 8,205 tiles of 512 keys
 
 
@@ -60,3 +62,32 @@ def test_batched_lookup_at_tile_edges(s, S, k, many):
     finally:
         for f in filters:
             f.close()
+
+
+@pytest.mark.parametrize("s,S,k", [(8, 32, 8), (8, 32, 9), (1, 32, 4), (4, 64, 16)])
+@pytest.mark.parametrize("nbytes,n", [(68, (1 << 22) + 1), (16 * KIB, (1 << 22) + 4_095), (17 * KIB + 36, 1 << 21),
+                                      (80 * KIB, (1 << 21) + 2_049), (80 * KIB + 64, 1 << 22),
+                                      (160 * KIB, 17_000_001), (160 * KIB + 64, 1 << 21)])
+def test_lookup_in_lds_equals_the_oracle(s, S, k, nbytes, n):
+    """The direct lookup's bytes too (a mapping of the caller's takes it)."""
+    from paper_2512_15595_amd import bf
+
+    block = s * S // 8
+    nb = max(1, nbytes // block)
+    log(f"lookup in LDS s={s} S={S} k={k}: {nb * block} bytes, {n} keys")
+    g = workloads.rng(nb + s)
+    keys = g.integers(0, 2**64, size=n, dtype=np.uint64)
+    words = g.integers(0, 256, size=nb * block, dtype=np.uint8) | g.integers(0, 256, size=nb * block, dtype=np.uint8)
+    f = bf.BloomFilter(nb, s, S, k, nb)
+    try:
+        f.load_words(torch.from_numpy(words).to("cuda"))
+        d = to_device(keys, offset_elems=1)
+        out = torch.full((n + 32,), 7, dtype=torch.uint8, device="cuda")
+        f.contains(d, out=out[3:n + 3])
+        got = out.cpu().numpy()
+        assert np.array_equal(got[3:n + 3], oracle_par.contains(words, nb, s, S, k, nb, keys))
+        assert (got[:3] == 7).all() and (got[n + 3:] == 7).all()
+        f.set_mapping(bf.BF_OP_CONTAINS, 1, s, 1)
+        assert torch.equal(f.contains(d), out[3:n + 3])
+    finally:
+        f.close()
