@@ -1226,7 +1226,7 @@ def main() -> int:
     # reported by the HBM bytes it moves (counters) against the 1 GiB copy
     add_traffic = committed_traffic("add", n) if add_partitioned else None
     roofline_add = {"bound": "hbm", "strategy": "partitioned" if add_partitioned else "direct",
-                    "kernels": ("part_scatter1 + part_scatter2 + part_apply" if add_partitioned
+                    "kernels": ("group_keys + plan + scan + regroup + part_apply" if add_partitioned
                                 else "bf_add_kernel"),
                     "avg_launch_ms": round(ms["add"], 4), "unit": "GB/s",
                     "algorithmic_bytes_per_key": 8 + 2 * block_bytes,

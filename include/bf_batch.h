@@ -10,14 +10,17 @@
  * together on one XCD (the filter stays hot in that XCD's L2), picks each
  * tile's execution mapping (paper Sec. IV-A: lanes per key, words per lane,
  * keys per lane) by the filter's size class from the autotuned table, and
- * records one persistent kernel launch in a HIP graph.
+ * records one persistent kernel launch in a HIP graph.  Filters of up to
+ * 160 KiB with many keys run in LDS instead, by launches of their own before
+ * that one (lookup plans, and add plans with the automatic strategy); their
+ * items count as tiles in bf_batch_info.
  *
  * An add plan with enough keys on filters that are dense (at least their
  * bytes / 80 keys each: the per-filter form of the BF_STRATEGY_AUTO rule in
  * bf.h) and at least 512 chunks among them is instead planned as one
  * partitioned construction over the dense filters: the filters' blocks are
  * laid end to end in one block space, one radix partition groups their keys
- * by 64 KiB chunk, and each chunk is updated in LDS (four kernels in the
+ * by 64 KiB chunk, and each chunk is updated in LDS (five kernels in the
  * graph); the keys of the sparse filters go to the tiled launch, recorded
  * after them, so no sparse filter's words are streamed.  Filter 0's add
  * strategy (bf_set_mapping_ex) can force BF_STRATEGY_DIRECT (tiles only) or

@@ -191,7 +191,8 @@ bf_status launch(bf_filter* f, int op, const uint64_t* keys, uint64_t n, uint8_t
 }
 
 bool default_mapping(const bf_mapping_t& m) {
-  return !m.lanes_per_key && !m.words_per_lane && !m.keys_per_lane && !m.max_workgroups && !m.workgroup_threads;
+  return !m.lanes_per_key && !m.words_per_lane && !m.keys_per_lane && !m.max_workgroups && !m.workgroup_threads &&
+         !m.atomic_bits && m.strategy == BF_STRATEGY_AUTO;
 }
 
 // Whether a bf_contains of n keys is grouped: with the default mapping (a
@@ -488,7 +489,14 @@ bf_status bf_add(bf_filter* f, const uint64_t* d_keys, uint64_t n, void* stream)
   if (d_keys == nullptr || reinterpret_cast<uintptr_t>(d_keys) % 8 != 0) return BF_EINVAL;
   hipStream_t s = static_cast<hipStream_t>(stream);
   const Access access = add_partitions(f, n) ? Access::kOwner : Access::kDirect;
-  return ordered_call(f, s, access, [&](CallMark& mark) { return launch(f, BF_OP_ADD, d_keys, n, nullptr, stream, &mark); });
+  return ordered_call(f, s, access, [&](CallMark& mark) {
+    if (add_fits_lds(f, n) && default_mapping(f->mapping[BF_OP_ADD])) {
+      bool taken = false;
+      const bf_status st = resident_call(f, BF_OP_ADD, d_keys, n, nullptr, s, &mark, &taken);
+      if (taken) return st;
+    }
+    return launch(f, BF_OP_ADD, d_keys, n, nullptr, stream, &mark);
+  });
 }
 
 bf_status bf_contains(const bf_filter* f, const uint64_t* d_keys, uint64_t n, uint8_t* d_out,
@@ -507,7 +515,7 @@ bf_status bf_contains(const bf_filter* f, const uint64_t* d_keys, uint64_t n, ui
     }
     if (lookup_fits_lds(g, n) && default_mapping(g->mapping[BF_OP_CONTAINS])) {
       bool taken = false;
-      const bf_status st = resident_lookup(g, d_keys, n, d_out, s, &mark, &taken);
+      const bf_status st = resident_call(g, BF_OP_CONTAINS, d_keys, n, d_out, s, &mark, &taken);
       if (taken) return st;
     }
     return launch(g, BF_OP_CONTAINS, d_keys, n, d_out, stream, &mark);

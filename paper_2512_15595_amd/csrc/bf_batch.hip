@@ -124,6 +124,53 @@ bf_status end_launch(bf_batch* b, hipStream_t stream, const CallMark& mark) {
   return BF_OK;
 }
 
+// Whether a filter of the plan with n keys runs in LDS (bf_resident.hpp).
+// It is copied or merged once per item; below one key per 32 bytes that would
+// move more than the keys' blocks.  Lookups, with 131,072 keys per filter of
+// 32-byte blocks, in G keys/s: 4 KiB 250 from the caches, 370 from LDS;
+// 64 KiB 135, 371; 128 KiB (one workgroup per CU) 120, 278.
+bool resides(const bf_batch* b, const bf_filter* f, uint64_t n) {
+  const int big = f->nbytes > kResidentBytes[0];
+  return b->resident[big].fn != nullptr && f->nbytes <= kResidentBytes[big] &&
+         n * (b->op == BF_OP_ADD ? 8 : 32) >= f->nbytes;
+}
+
+uint64_t resident_keys_of(const bf_batch* b, bf_filter* const* filters, uint32_t nfilters, const uint64_t* h_offsets) {
+  uint64_t keys = 0;
+  for (uint32_t i = 0; i < nfilters; ++i) {
+    const uint64_t n = h_offsets[i + 1] - h_offsets[i];
+    if (resides(b, filters[i], n)) keys += n;
+  }
+  return keys;
+}
+
+// Whether the plan is faster with its small filters in LDS.  A lookup plan's
+// tiles of one filter stay on one XCD, which tests about 12 keys per ns; the
+// launches in LDS test 330 and cost 15 us.  So plans whose largest filter
+// does not fit the LDS and bounds them gain nothing (256 filters, 2^24 keys,
+// a fifth of them in one: 254 us from the caches, 282 with LDS), nor do small
+// ones (1,024 filters, 2^21 keys: 33 us, 43); 2^23 keys take 103 us and 99,
+// 2^24 205 and 184.  Add plans gain from 1.5 M such keys on (1,024 filters of
+// Zipf counts: 2^21 keys 133 us without, 141 with; 2^22 keys 296, 202).
+bool resides_pays(const bf_batch* b, bf_filter* const* filters, uint32_t nfilters, const uint64_t* h_offsets) {
+  const uint64_t keys = resident_keys_of(b, filters, nfilters, h_offsets);
+  if (b->op == BF_OP_ADD) return keys >= 3u << 19;
+  if (keys == 0) return false;
+  std::vector<std::pair<uint64_t, bool>> counts(nfilters);
+  for (uint32_t i = 0; i < nfilters; ++i) {
+    const uint64_t n = h_offsets[i + 1] - h_offsets[i];
+    counts[i] = {n, resides(b, filters[i], n)};
+  }
+  std::sort(counts.begin(), counts.end(), [](const auto& x, const auto& y) { return x.first > y.first; });
+  uint64_t all[kXcds] = {}, rest[kXcds] = {};
+  for (const auto& [n, in_lds] : counts) {
+    *std::min_element(all, all + kXcds) += n;
+    if (!in_lds) *std::min_element(rest, rest + kXcds) += n;
+  }
+  const double caches = *std::max_element(all, all + kXcds) / 12.0;
+  return *std::max_element(rest, rest + kXcds) / 12.0 + keys / 330.0 + 15000.0 < caches;
+}
+
 // Partitioned construction for an add plan: the filters' blocks are laid
 // end to end in one global block space (each filter starting on a chunk
 // boundary), so one radix partition groups every key of every filter by
@@ -158,7 +205,7 @@ bf_status plan_partitioned(bf_batch* b, bf_filter* const* filters, uint32_t nfil
     pf[i].key_end = h_offsets[i + 1] - h_offsets[0];
     const uint64_t ni = pf[i].key_end - pf[i].key_begin;
     const uint64_t nc = (f->num_blocks + bpc - 1) / bpc;
-    pf[i].direct = !forced && !dense_enough(xr, f->nbytes, ni, true) ? 1u : 0u;
+    pf[i].direct = !forced && (!dense_enough(xr, f->nbytes, ni, true) || resides(b, f, ni)) ? 1u : 0u;
     if (!pf[i].direct) {
       n_dense += ni;
       dense_chunks += nc;
@@ -379,19 +426,21 @@ bf_status build_tiles(bf_batch* b, bf_filter* const* filters, uint32_t nfilters,
   std::vector<std::vector<BatchTile>> queue(kXcds);
   std::vector<uint64_t> load(kXcds, 0);
   std::vector<BatchTile> items[2];
+  // Each item copies a filter or merges an image into it, so items are as long
+  // as keeps the launch's tail short: adds of 2^22 keys in 1,024 filters take
+  // 0.26 ms with 65,536 keys per item and 0.20 with 8,192; of 2^28 keys in
+  // 4,096 filters 3.30 with 32,768, 3.26 with 65,536, 3.28 with 131,072.
+  const uint64_t resident_keys = resident_keys_of(b, filters, nfilters, h_offsets);
+  const uint64_t item_keys = op == BF_OP_ADD ? std::clamp<uint64_t>(resident_keys / 2048, 8192, 65536)
+                                             : std::clamp<uint64_t>(resident_keys / 2048, 4096, kResidentKeys);
   for (uint32_t i : order) {
     const uint64_t n = h_offsets[i + 1] - h_offsets[i];
     if (n == 0 || (only != nullptr && !(*only)[i])) continue;
     const bf_filter* f = filters[i];
     const int cls = size_class_of(f->nbytes);
-    // A filter that fits the LDS is copied there once per item; below one key
-    // per 32 bytes the copy would read more than the lookups' blocks.
-    // Measured with 131,072 keys per filter of 32-byte blocks, in G keys/s:
-    // 4 KiB 250 from the caches, 370 from LDS; 64 KiB 135, 371; 128 KiB (one
-    // workgroup per CU) 120, 278.
-    const int big = f->nbytes > kResidentBytes[0];
-    if (b->resident[big].fn != nullptr && f->nbytes <= kResidentBytes[big] && n * 32 >= f->nbytes) {
-      const uint64_t parts = (n + kResidentKeys - 1) / kResidentKeys;
+    if (resides(b, f, n)) {
+      const int big = f->nbytes > kResidentBytes[0];
+      const uint64_t parts = (n + item_keys - 1) / item_keys;
       for (uint64_t p = 0; p < parts; ++p) {
         const uint64_t from = n * p / parts;
         items[big].push_back({h_offsets[i] + from, i, static_cast<uint32_t>(n * (p + 1) / parts - from)});
@@ -514,11 +563,13 @@ bf_status bf_batch_plan(int op, bf_filter* const* filters, uint32_t nfilters,
   b->d_keys = d_keys;
   b->d_out = d_out;
   b->fn = fn;
-  if (op == BF_OP_CONTAINS)
+  // (the caller's strategy of an add plan stands)
+  if (op == BF_OP_CONTAINS || f0->mapping[BF_OP_ADD].strategy == BF_STRATEGY_AUTO)
     for (int big = 0; big < 2; ++big)
       b->resident[big].fn = kernel_table(f0->salts == kSaltsParquet)
                                 .resident_fn[big][batch_index(op, static_cast<int>(f0->word_bits),
                                                               static_cast<int>(f0->s), k_index(f0->k))];
+  if (!resides_pays(b, filters, nfilters, h_offsets)) b->resident[0].fn = b->resident[1].fn = nullptr;
   b->device = f0->device;
 
   if (op == BF_OP_ADD) {

@@ -57,6 +57,8 @@ void register_parquet(Registry& r) {
   r.apply_fn[1][slot] =
       reinterpret_cast<const void*>(&part_apply_kernel<uint32_t, kParquetWords, kParquetK, kZParquet, 8>);
   const int look = batch_index(kOpContains, 32, kParquetWords, kIdxK);
+  r.resident_fn[0][slot] = reinterpret_cast<const void*>(&parquet_resident_add_kernel<0>);
+  r.resident_fn[1][slot] = reinterpret_cast<const void*>(&parquet_resident_add_kernel<1>);
   r.resident_fn[0][look] = reinterpret_cast<const void*>(&parquet_resident_kernel<0>);
   r.resident_fn[1][look] = reinterpret_cast<const void*>(&parquet_resident_kernel<1>);
   r.lookup_fn[0][look] = reinterpret_cast<const void*>(&parquet_lookup_test_kernel<false>);

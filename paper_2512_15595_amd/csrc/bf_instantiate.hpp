@@ -70,6 +70,8 @@ void register_batch(Registry& r) {
     r.apply_fn[1][slot] = reinterpret_cast<const void*>(&part_apply_kernel<W, S_WORDS, K, 0, 8>);
     const int look = batch_index(kOpContains, kBits, S_WORDS, k_index(K));
     if constexpr (lookup_resides<W, S_WORDS>()) {
+      r.resident_fn[0][slot] = reinterpret_cast<const void*>(&bf_resident_add_kernel<W, S_WORDS, K, 0>);
+      r.resident_fn[1][slot] = reinterpret_cast<const void*>(&bf_resident_add_kernel<W, S_WORDS, K, 1>);
       r.resident_fn[0][look] = reinterpret_cast<const void*>(&bf_resident_kernel<W, S_WORDS, K, 0>);
       r.resident_fn[1][look] = reinterpret_cast<const void*>(&bf_resident_kernel<W, S_WORDS, K, 1>);
     }

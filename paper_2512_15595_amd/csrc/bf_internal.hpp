@@ -102,12 +102,13 @@ bool lookup_groups(const bf_filter* f, uint64_t n);
 bf_status grouped_lookup(const bf_filter* f, const uint64_t* keys, uint64_t n, uint8_t* out, hipStream_t stream,
                          bool* taken);
 
-// The same for a lookup whose filter fits the LDS (bf_resident.hpp); it takes
-// no workspace.
+// The same for lookups and adds whose filter fits the LDS (bf_resident.hpp);
+// they take no workspace.
 struct CallMark;
 bool lookup_fits_lds(const bf_filter* f, uint64_t n);
-bf_status resident_lookup(const bf_filter* f, const uint64_t* keys, uint64_t n, uint8_t* out, hipStream_t stream,
-                          CallMark* mark, bool* taken);
+bool add_fits_lds(const bf_filter* f, uint64_t n);
+bf_status resident_call(const bf_filter* f, int op, const uint64_t* keys, uint64_t n, uint8_t* out,
+                        hipStream_t stream, CallMark* mark, bool* taken);
 
 // Filter allocation shared by every create call (bf_api.hip): fills nbytes,
 // device, d_words (zeroed, synchronously).  On error the handle is freed.

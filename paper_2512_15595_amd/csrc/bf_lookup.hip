@@ -191,11 +191,22 @@ bool lookup_fits_lds(const bf_filter* f, uint64_t n) {
          n >= (f->nbytes > (16u << 10) ? 1ull << 21 : 1ull << 22);
 }
 
-bf_status resident_lookup(const bf_filter* f, const uint64_t* keys, uint64_t n, uint8_t* out, hipStream_t stream,
-                          CallMark* mark, bool* taken) {
+// Adds in LDS: a workgroup merges its image into the filter, which pays from
+// 8 keys per byte on.  us against the direct adds, 32-byte blocks, k = 8:
+// 4 KiB 2^15 keys 17.7 against 11.7, 2^20 299 against 16; 16 KiB 2^17 18.4
+// against 12.4; 64 KiB 2^18 18.7 against 17.6, 2^19 28.5 against 20.6; 128 KiB
+// 2^19 28.8 against 28.8, 2^20 48 against 34, 2^22 90 against 78; 2^24 keys,
+// which were partitioned, 161..193 against 58..125.  8-byte words and k = 16
+// lose at 4 keys per byte (64 KiB 2^18 19.8 against 23.8), not at 8.
+bool add_fits_lds(const bf_filter* f, uint64_t n) {
+  return f->layout == BF_LAYOUT_SECTORIZED && f->nbytes <= kResidentBytes[1] && n >= 8 * f->nbytes;
+}
+
+bf_status resident_call(const bf_filter* f, int op, const uint64_t* keys, uint64_t n, uint8_t* out,
+                        hipStream_t stream, CallMark* mark, bool* taken) {
   *taken = false;
   const int big = f->nbytes > kResidentBytes[0];
-  const int idx = batch_index(kOpContains, static_cast<int>(f->word_bits), static_cast<int>(f->s), k_index(f->k));
+  const int idx = batch_index(op, static_cast<int>(f->word_bits), static_cast<int>(f->s), k_index(f->k));
   const void* fn = kernel_table(f->salts == kSaltsParquet).resident_fn[big][idx];
   if (fn == nullptr) return BF_OK;
   ResidentArgs a{};
@@ -210,6 +221,8 @@ bf_status resident_lookup(const bf_filter* f, const uint64_t* keys, uint64_t n, 
   const uint64_t slots = big ? 256 : 512;
   const uint64_t turns = ceil_div(n, slots * kResidentKeys);
   a.per = static_cast<uint32_t>(ceil_div(ceil_div(n, slots * turns), 2048ull) * 2048);  // of whole loop turns
+  // an add's workgroup has a key for every 8 bytes that it merges, at least
+  if (op == kOpAdd) a.per = std::max(a.per, static_cast<uint32_t>(ceil_div(f->nbytes / 8, 2048ull) * 2048));
   const uint64_t grid = ceil_div(n, static_cast<uint64_t>(a.per));
   if (grid > 0x7fffffffu) return BF_OK;
   void* kargs[] = {&a};

@@ -81,6 +81,11 @@ __global__ __launch_bounds__(kBlockThreads) void parquet_batch_kernel(BatchArgs 
 }
 
 template <int BIG>
+__global__ __launch_bounds__(kResidentThreads, BIG ? 4 : 8) void parquet_resident_add_kernel(ResidentArgs a) {
+  resident_add<uint32_t, kParquetWords, kParquetK, BIG, kZParquet>(a);
+}
+
+template <int BIG>
 __global__ __launch_bounds__(kResidentThreads, BIG ? 4 : 8) void parquet_resident_kernel(ResidentArgs a) {
   resident_lookup<uint32_t, kParquetWords, kParquetK, BIG, ParquetSalts>(a);
 }

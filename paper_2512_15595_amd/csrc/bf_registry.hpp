@@ -56,7 +56,7 @@ constexpr int kBatchRegistrySize = 2 * 2 * kLog2Max * kNumK;
 struct Registry {
   const void* fn[kRegistrySize];
   const void* batch_fn[kBatchRegistrySize];  // persistent batched kernels
-  const void* resident_fn[2][kBatchRegistrySize];  // lookups in filters that fit the LDS: two / one per CU (op slot 1)
+  const void* resident_fn[2][kBatchRegistrySize];  // filters that fit the LDS: two / one per CU
   const void* apply_fn[2][kBatchRegistrySize];  // partitioned add: per-chunk apply (op slot 0), units of 16 / 8 slots
   const void* lookup_fn[2][kBatchRegistrySize];  // grouped lookup: chunk test of one / two digits (op slot 1)
   const void* return_fn[kBatchRegistrySize];  // ... and the results' return (op slot 1)

@@ -1,7 +1,7 @@
 """Batched lookups at the edges of their tiles: counts around a tile's keys,
 filters without keys, more tiles than the persistent grid has turns in
 flight, keys and results at odd addresses; and lookups in filters that fit the
-LDS, at the edges of their sizes; bit-exact against the CPU oracle.
+LDS, and adds into them, at the edges of their sizes; bit-exact against the CPU oracle.
 """
 from __future__ import annotations
 
@@ -91,3 +91,105 @@ def test_lookup_in_lds_equals_the_oracle(s, S, k, nbytes, n):
         assert torch.equal(f.contains(d), out[3:n + 3])
     finally:
         f.close()
+
+
+@pytest.mark.parametrize("s,S,k", [(8, 32, 8), (8, 32, 9), (1, 32, 4), (2, 32, 4), (4, 64, 16)])
+@pytest.mark.parametrize("nbytes,n", [(68, 5_000), (4 * KIB, 32_769), (17 * KIB + 36, 8 * 18 * KIB), (80 * KIB, 655_360),
+                                      (80 * KIB + 64, 2_000_001), (160 * KIB, 1_310_720), (160 * KIB + 64, 1 << 21)])
+def test_add_in_lds_equals_the_oracle(s, S, k, nbytes, n):
+    """On a filter that holds bits already; half of the keys are one key."""
+    from paper_2512_15595_amd import bf
+
+    block = s * S // 8
+    nb = max(1, nbytes // block)
+    log(f"add in LDS s={s} S={S} k={k}: {nb * block} bytes, {n} keys")
+    g = workloads.rng(nb + s)
+    keys = g.integers(0, 2**64, size=n, dtype=np.uint64)
+    keys[::2] = 77
+    old = np.zeros(nb * block, dtype=np.uint8)
+    old[::7] = 129
+    f = bf.BloomFilter(nb, s, S, k, nb)
+    try:
+        f.load_words(torch.from_numpy(old).to("cuda"))
+        f.add(to_device(keys, offset_elems=1))
+        got = f.words().cpu().numpy().view(np.uint8)
+        assert np.array_equal(got, oracle_par.filter_words(nb, s, S, k, nb, keys).view(np.uint8) | old)
+    finally:
+        f.close()
+
+
+@pytest.mark.parametrize("s,S,k", [(8, 32, 8), (8, 32, 9), (1, 32, 4), (4, 64, 16)])
+def test_batched_add_in_lds_equals_the_oracle(s, S, k):
+    """Small filters in LDS (one of them twice in the plan), larger ones by
+    the partitioned construction or directly."""
+    from paper_2512_15595_amd import bf
+
+    shapes = [(4 * KIB, 200_001), (64 * KIB, 65_537), (0, 0), (80 * KIB, 700_000), (80 * KIB + 256, 10_000),
+              (160 * KIB, 900_001), (160 * KIB + 256, 30_000), (68, 3), (1 << 20, 400_000), (4 * KIB, 5_000)]
+    block = s * S // 8
+    blocks = [max(1, nbytes // block) for nbytes, _ in shapes]
+    offsets = np.concatenate([[0], np.cumsum([n for _, n in shapes])])
+    keys = workloads.rng(s + S).integers(0, 2**64, size=int(offsets[-1]), dtype=np.uint64)
+    log(f"batched add in LDS s={s} S={S} k={k}: {len(shapes)} filters, {keys.size} keys")
+    filters = [bf.BloomFilter(nb, s, S, k, i) for i, nb in enumerate(blocks)]
+    filters[-1].close()
+    filters[-1] = filters[0]
+    share = [keys[offsets[i]:offsets[i + 1]] for i in range(len(shapes))]
+    share[0] = np.concatenate([share[0], share[-1]])
+    try:
+        d = to_device(keys, offset_elems=1)
+        for mode in ("launch", "launch_direct"):
+            for f in filters:
+                f.clear()
+            plan = bf.BatchPlan(bf.BF_OP_ADD, filters, d, offsets)
+            try:
+                getattr(plan, mode)()
+                got = [f.words().cpu().numpy().view(np.uint8) for f in filters]
+            finally:
+                plan.close()
+            for i, nb in enumerate(blocks[:-1]):
+                want = (oracle_par.filter_words(nb, s, S, k, i, share[i]).view(np.uint8) if share[i].size
+                        else np.zeros(nb * block, dtype=np.uint8))
+                assert np.array_equal(got[i], want), f"filter {i}"
+    finally:
+        for f in filters[:-1]:
+            f.close()
+
+
+@pytest.mark.parametrize("s,S,k", [(8, 32, 8), (8, 32, 9), (1, 32, 4), (4, 64, 16)])
+def test_batched_lookup_in_lds_equals_the_oracle(s, S, k):
+    """Enough keys in small filters that the plan tests them in LDS (the rule
+    of bf_batch.hip: 2^23 keys over 96 filters of like counts)."""
+    from paper_2512_15595_amd import bf
+
+    block = s * S // 8
+    sizes = [68, 4 * KIB, 17 * KIB + 36, 80 * KIB, 80 * KIB + 64, 160 * KIB, 160 * KIB + 64, 300 * KIB] * 12
+    blocks = [max(1, nbytes // block) for nbytes in sizes]
+    counts = [87_000 + 37 * i for i in range(len(sizes))]
+    offsets = np.concatenate([[0], np.cumsum(counts)])
+    total = int(offsets[-1])
+    log(f"batched lookup in LDS s={s} S={S} k={k}: {len(sizes)} filters, {total} keys")
+    g = workloads.rng(s + S + k)
+    keys = g.integers(0, 2**64, size=total, dtype=np.uint64)
+    words = [g.integers(0, 256, size=nb * block, dtype=np.uint8) | g.integers(0, 256, size=nb * block, dtype=np.uint8)
+             for nb in blocks]
+    want = np.concatenate([oracle_par.contains(words[i], nb, s, S, k, i, keys[offsets[i]:offsets[i + 1]])
+                           for i, nb in enumerate(blocks)])
+    filters = [bf.BloomFilter(nb, s, S, k, i) for i, nb in enumerate(blocks)]
+    try:
+        for f, w in zip(filters, words):
+            f.load_words(torch.from_numpy(w).to("cuda"))
+        out = torch.full((total + 32,), 7, dtype=torch.uint8, device="cuda")
+        plan = bf.BatchPlan(bf.BF_OP_CONTAINS, filters, to_device(keys, offset_elems=1), offsets, out[3:total + 3])
+        try:
+            for launch in (plan.launch, plan.launch_direct):
+                out.fill_(7)
+                launch()
+                got = out.cpu().numpy()
+                assert np.array_equal(got[3:total + 3], want)
+                assert (got[:3] == 7).all() and (got[total + 3:] == 7).all()
+        finally:
+            plan.close()
+    finally:
+        for f in filters:
+            f.close()
