@@ -36,7 +36,8 @@ METRIC = "Gkeys/s add+contains, 1 GiB blocked BF, % random-gather bound; p99 ser
 PEAK_HBM_GBS = 8000.0
 PROFILE_DIR = os.path.join(ROOT, "profiles")
 # the timed kernels (lookups; direct and partitioned adds) and their mappings
-KERNEL_SOURCES = ["bf_kernels.hpp", "bf_hash.hpp", "bf_tuned_defaults.inc", "bf_partition.hpp"]
+KERNEL_SOURCES = ["bf_kernels.hpp", "bf_hash.hpp", "bf_tuned_defaults.inc", "bf_group.hpp", "bf_partition.hpp",
+                  "bf_lookup.hpp"]
 
 
 def log(msg: str) -> None:
@@ -1211,13 +1212,16 @@ def main() -> int:
         dom, per_key, dom_ms = "contains", 8 + block_bytes + 1, ms["contains"]
     achieved = per_key * n / (dom_ms * 1e-3) / 1e9
     traffic = committed_traffic(dom, n)
-    roofline = {"bound": "hbm", "kernel": f"bf_{dom}_kernel", "achieved": round(achieved, 1),
+    # the default lookup groups many keys in a filter of 8 MiB..2 GiB by chunk
+    grouped = dom == "contains" and not mc and (8 << 20) <= filter_bytes <= (2 << 30) and n >= (1 << 24) + filter_bytes // 36
+    roofline = {"bound": "hbm", "kernel": ("group_keys + regroup + lookup_test + return_slots + lookup_return" if grouped
+                                           else f"bf_{dom}_kernel"), "achieved": round(achieved, 1),
                 "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": round(achieved / PEAK_HBM_GBS, 4),
                 "traffic": traffic, "algorithmic_bytes_per_key": per_key,
                 "avg_launch_ms": round(dom_ms, 4)}
     if traffic:
-        # every random block read fetches a whole 128-byte line: what the
-        # memory system moves, against the HBM peak
+        # what the memory system moves, against the HBM peak (a direct lookup's
+        # random block read fetches a whole 128-byte line)
         roofline["traffic_gbs"] = round(traffic / (dom_ms * 1e-3) / 1e9, 1)
         roofline["traffic_frac_of_peak"] = round(traffic / (dom_ms * 1e-3) / 1e9 / PEAK_HBM_GBS, 4)
 
