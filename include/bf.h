@@ -72,7 +72,9 @@ typedef int32_t bf_status;
 typedef struct bf_filter bf_filter; /* opaque handle, owns the device words */
 
 /* Construction strategies (bf_mapping_t.strategy, add only). */
-#define BF_STRATEGY_AUTO 0        /* partitioned for dense batches, else direct */
+#define BF_STRATEGY_AUTO 0        /* partitioned for dense batches, else direct;
+                                     many keys in a filter of up to 160 KiB:
+                                     an image in LDS, merged with atomic OR */
 #define BF_STRATEGY_DIRECT 1      /* one atomic OR group per key into the filter */
 #define BF_STRATEGY_PARTITIONED 2 /* keys grouped by filter chunk; each chunk is
                                      updated in LDS and stored back */
@@ -186,7 +188,9 @@ bf_status bf_add(bf_filter *f, const uint64_t *d_keys, uint64_t n, void *stream)
  * of workspace per key from the device's stream-ordered pool for the time of
  * the call, 2^28 keys at a time.  Where there is no such memory, while the
  * stream is being captured, and with a mapping set by bf_set_mapping, keys
- * are looked up one by one and nothing is allocated.  Results are the same. */
+ * are looked up one by one and nothing is allocated.  From 2 M keys on a
+ * filter of up to 160 KiB (blocks of up to 32 bytes, default mapping) is
+ * copied to LDS and tested there, without workspace.  Results are the same. */
 bf_status bf_contains(const bf_filter *f, const uint64_t *d_keys, uint64_t n,
                       uint8_t *d_out, void *stream);
 
