@@ -24,7 +24,10 @@
  * graph); the keys of the sparse filters go to the tiled launch, recorded
  * after them, so no sparse filter's words are streamed.  Filter 0's add
  * strategy (bf_set_mapping_ex) can force BF_STRATEGY_DIRECT (tiles only) or
- * BF_STRATEGY_PARTITIONED (every filter partitioned).  Launches of a plan
+ * BF_STRATEGY_PARTITIONED (every filter partitioned).  A plan may name a
+ * filter more than once and its filters' words may overlap: one of such
+ * entries at most is partitioned, the others' keys go to the tiled launch,
+ * whose atomic ORs merge.  Launches of a plan
  * (all three forms) are ordered by the caller against other work on its
  * filters -- stream order or events; they take no part in the per-filter
  * stream order of bf.h calls.

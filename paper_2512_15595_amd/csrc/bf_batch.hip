@@ -171,6 +171,26 @@ bool resides_pays(const bf_batch* b, bf_filter* const* filters, uint32_t nfilter
   return *std::max_element(rest, rest + kXcds) / 12.0 + keys / 330.0 + 15000.0 < caches;
 }
 
+// A chunk of a partitioned construction is read, updated in LDS and written
+// back by the workgroups of its plan entry, so no two entries may own the
+// same words: where entries' words overlap (a filter named twice, two views
+// of one buffer) one of them stays and the others' keys are left to the
+// direct launch, which runs behind the construction and merges by atomic OR.
+void leave_overlaps_direct(bf_filter* const* filters, std::vector<PartFilter>& pf) {
+  std::vector<uint32_t> order;
+  for (uint32_t i = 0; i < pf.size(); ++i)
+    if (!pf[i].direct && pf[i].key_end > pf[i].key_begin) order.push_back(i);
+  auto begin = [&](uint32_t i) { return reinterpret_cast<uintptr_t>(pf[i].words); };
+  std::stable_sort(order.begin(), order.end(), [&](uint32_t x, uint32_t y) { return begin(x) < begin(y); });
+  uintptr_t end = 0;  // of the words that are owned
+  for (uint32_t i : order) {
+    if (begin(i) < end)
+      pf[i].direct = 1;
+    else
+      end = begin(i) + filters[i]->nbytes;
+  }
+}
+
 // Partitioned construction for an add plan: the filters' blocks are laid
 // end to end in one global block space (each filter starting on a chunk
 // boundary), so one radix partition groups every key of every filter by
@@ -204,13 +224,14 @@ bf_status plan_partitioned(bf_batch* b, bf_filter* const* filters, uint32_t nfil
     pf[i].key_begin = h_offsets[i] - h_offsets[0];
     pf[i].key_end = h_offsets[i + 1] - h_offsets[0];
     const uint64_t ni = pf[i].key_end - pf[i].key_begin;
-    const uint64_t nc = (f->num_blocks + bpc - 1) / bpc;
     pf[i].direct = !forced && (!dense_enough(xr, f->nbytes, ni, true) || resides(b, f, ni)) ? 1u : 0u;
-    if (!pf[i].direct) {
-      n_dense += ni;
-      dense_chunks += nc;
-    }
-    chunks += nc;
+    chunks += (f->num_blocks + bpc - 1) / bpc;
+  }
+  leave_overlaps_direct(filters, pf);
+  for (uint32_t i = 0; i < nfilters; ++i) {
+    if (pf[i].direct) continue;
+    n_dense += pf[i].key_end - pf[i].key_begin;
+    dense_chunks += (pf[i].num_blocks + bpc - 1) / bpc;
   }
   const uint64_t n = h_offsets[nfilters] - h_offsets[0];
   if (n == 0 || chunks * bpc > (1ull << 32)) return BF_OK;  // global blocks must fit 32 bits

@@ -193,3 +193,43 @@ def test_batched_lookup_in_lds_equals_the_oracle(s, S, k):
     finally:
         for f in filters:
             f.close()
+
+
+@pytest.mark.parametrize("forced", [False, True])
+@pytest.mark.parametrize("mode", ["launch", "launch_direct"])
+def test_partitioned_plan_over_overlapping_words(mode, forced):
+    """A dense filter named twice and two overlapping views of one buffer: no
+    two workgroups of the construction may write back the same chunk."""
+    from paper_2512_15595_amd import bf
+
+    mib = 1 << 20
+    words = torch.zeros(96 * mib, dtype=torch.uint8, device="cuda")
+    # (first byte, bytes, keys); entry 2 is entry 0 again
+    spec = [(0, 40 * mib, 1_500_001), (48 * mib, 48 * mib, 1_600_003), None, (64 * mib, 16 * mib, 300_007)]
+    log(f"plan over overlapping words mode={mode} forced={forced}")
+    filters = []
+    for i, x in enumerate(spec):
+        filters.append(filters[0] if x is None else
+                       bf.BloomFilterView(words[x[0]:x[0] + x[1]], x[1] // 32, 8, 32, 8, i))
+    spec[2] = (0, 40 * mib, 900_001)
+    offsets = np.concatenate([[0], np.cumsum([n for _, _, n in spec])])
+    keys = workloads.rng(17).integers(0, 2**64, size=int(offsets[-1]), dtype=np.uint64)
+    want = np.zeros(96 * mib, dtype=np.uint8)
+    for i, (at, nbytes, _) in enumerate(spec):
+        want[at:at + nbytes] |= oracle_par.filter_words(nbytes // 32, 8, 32, 8, 0 if i == 2 else i,
+                                                        keys[offsets[i]:offsets[i + 1]]).view(np.uint8)
+    try:
+        if forced:
+            filters[0].set_mapping(bf.BF_OP_ADD, strategy=bf.BF_STRATEGY_PARTITIONED)
+        plan = bf.BatchPlan(bf.BF_OP_ADD, filters, to_device(keys), offsets)
+        try:
+            info = plan.info()
+            assert info.strategy == bf.BF_STRATEGY_PARTITIONED
+            assert info.ntiles > 0, "the keys of entries that overlap an owner"
+            getattr(plan, mode)()
+            assert np.array_equal(words.cpu().numpy(), want)
+        finally:
+            plan.close()
+    finally:
+        for i in (0, 1, 3):
+            filters[i].close()
