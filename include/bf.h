@@ -248,15 +248,15 @@ bf_status bf_tuned_mapping(int op, uint64_t num_blocks, uint32_t words_per_block
  * every bf.h call does).  Each device holds one array, loaded with the
  * library's code on the first call there and kept until the process ends.
  * An add the automatic rule builds directly (one atomic OR group per key)
- * needs no workspace and is bf_add itself.  A partitioned add must fit one
- * pass of the array (at most 2^28 records; the workspace is about 6 bytes
- * per key into a filter of at most 64 MiB, which is partitioned in one
- * pass, so up to about 43 M keys, and 14-22 bytes per key into a larger
- * one, the most for few keys into a large filter, so about 12 M into a
- * 1 GiB filter):
- * larger adds give BF_ESCRATCH with nothing enqueued.  Calls on one device
- * share the array, which keeps the last call's contents (the kernels clear
- * the counters they need): outside graph capture the library orders them
+ * needs no workspace and is bf_add itself.  A partitioned add is taken up to
+ * a fixed number of keys: at most 2^28 records, and about 43 M keys into a
+ * filter of at most 64 MiB (accounted at 6 bytes per key), fewer into a larger
+ * one (14-22 bytes per key, the most for few keys into a large filter: about
+ * 12 M into 1 GiB).  It runs in as many passes over the array as its records
+ * need (the words are the same); larger adds give BF_ESCRATCH with nothing
+ * enqueued.  Calls on one device share the array, which keeps the last call's
+ * contents (no kernel reads what its own call has not
+ * written): outside graph capture the library orders them
  * with one event per device, so they never overlap; calls captured into
  * graphs are ordered by their caller, and captured calls that overlap on
  * one device race on the array.  The current device must be the filter's

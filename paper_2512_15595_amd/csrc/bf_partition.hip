@@ -379,25 +379,34 @@ uint64_t max_pass_keys(const bf_filter* f) { return std::max<uint64_t>((1ull << 
 
 }  // namespace
 
-// The accounted size decides what is taken; an add whose real workspace is
+// The keys of a pass of an add of n keys over ws_bytes: n, halved until the
+// workspace of a pass fits, and that of the shorter last pass too (a geometry
+// of fewer keys can need more: fewer second-pass items hold more batches).
+// 0 if there is none.
+uint64_t pass_keys_in(const bf_filter* f, uint64_t n, uint64_t ws_bytes) {
+  auto fits = [&](uint64_t keys) {
+    PartArgs a{};
+    PartLayout L{};
+    return keys == 0 || (single_geometry(f, keys, a, L) && L.total <= ws_bytes);
+  };
+  for (uint64_t pass = n; pass > 0; pass = pass > 1 ? (pass + 1) / 2 : 0)
+    if (fits(pass) && fits(n % pass)) return pass;
+  return 0;
+}
+
+// accounted_bytes decides what is taken; an add whose real workspace is
 // larger than ws_bytes (few keys into a large filter, or a table of many
 // digits) runs in several passes over it, which give the same words.
 bf_status partitioned_add_in(bf_filter* f, const uint64_t* keys, uint64_t n, hipStream_t stream,
                              void* ws, uint64_t ws_bytes) {
   if (n == 0 || n > max_pass_keys(f)) return BF_EINVAL;
   if (accounted_bytes(f, n) > ws_bytes) return BF_ESCRATCH;
-  PartArgs a{};
-  PartLayout L{};
-  uint64_t pass = n;
-  for (;; pass = (pass + 1) / 2) {
-    a = PartArgs{};
-    if (!single_geometry(f, pass, a, L) || !part_runs(a, part_kernels(f, a))) return BF_EUNSUPPORTED;
-    if (L.total <= ws_bytes) break;
-    if (pass == 1) return BF_ESCRATCH;
-  }
+  const uint64_t pass = pass_keys_in(f, n, ws_bytes);
+  if (pass == 0) return BF_ESCRATCH;
   for (uint64_t off = 0; off < n; off += pass) {
-    a = PartArgs{};
-    single_geometry(f, std::min(pass, n - off), a, L);
+    PartArgs a{};
+    PartLayout L{};
+    if (!single_geometry(f, std::min(pass, n - off), a, L) || !part_runs(a, part_kernels(f, a))) return BF_EUNSUPPORTED;
     const bf_status st = partitioned_pass_in(f, keys + off, stream, a, L, ws);
     if (st != BF_OK) return st;
   }

@@ -168,3 +168,25 @@ def test_noalloc_calls_on_two_streams_do_not_overlap():
     finally:
         fa.close()
         fb.close()
+
+
+def test_noalloc_of_several_passes_equals_bf_add():
+    """42,500,003 keys into 64 MiB are taken but their records exceed the
+    array: two passes over it, the second one key shorter."""
+    bf = _bf()
+    lib = _lib()
+    nb, n = (64 << 20) // 32, 42_500_003
+    d = _dev(workloads.uniform_keys(n, 41))
+    f_na = bf.BloomFilter(nb, 8, 32, 8, 15)
+    f_ref = bf.BloomFilter(nb, 8, 32, 8, 15)
+    try:
+        for f in (f_na, f_ref):
+            f.set_mapping(bf.BF_OP_ADD, strategy=bf.BF_STRATEGY_PARTITIONED)
+        log(f"noalloc in several passes: {n} keys into 64 MiB")
+        assert lib.bf_add_noalloc(f_na.handle, d.data_ptr(), n, torch.cuda.current_stream().cuda_stream) == 0
+        f_ref.add(d)
+        torch.cuda.synchronize()
+        assert torch.equal(f_na.words(), f_ref.words())
+    finally:
+        f_na.close()
+        f_ref.close()
