@@ -82,6 +82,30 @@ int bfb_fill_mixed_queries(uint64_t *d_out, uint64_t n, uint64_t src_seed, uint6
                            uint32_t src_count, uint64_t fresh_seed, uint64_t fresh_first,
                            uint32_t hit_q32, uint64_t mix_seed, void *stream);
 
+/* How the library runs one call of bf.h (for reports and tests; host only,
+ * touches no device): the route that bf_add / bf_contains of n keys takes on
+ * a filter of these parameters with the default mapping, outside graph
+ * capture, and the memory it takes. */
+#define BFB_ROUTE_DIRECT 0      /* one kernel, a memory access per key and block */
+#define BFB_ROUTE_PARTITIONED 1 /* add: keys partitioned by filter chunk, chunks updated in LDS */
+#define BFB_ROUTE_LDS 2         /* the whole filter in LDS */
+#define BFB_ROUTE_GROUPED 3     /* contains: keys grouped by filter chunk, chunks tested in LDS */
+typedef struct {
+  uint32_t route;
+  uint32_t reserved;
+  uint64_t workspace_bytes;   /* taken from the device's workspace pool at a time */
+  uint64_t noalloc_pass_keys; /* add: keys per pass of bf_add_noalloc over its array (0: refused,
+                                 or an add that takes no workspace) */
+  uint64_t noalloc_pass_bytes; /* ... and the most that one of its passes uses of the array */
+} bfb_call_t;
+
+/* layout: BF_LAYOUT_SECTORIZED, BF_LAYOUT_CLASSIC or BF_LAYOUT_CACHE_SECTORIZED
+ * (bf.h); size: blocks, or bits of the classic layout (which ignores
+ * words_per_block and word_bits); groups: z of the cache-sectorized layout;
+ * strategy: BF_STRATEGY_* of an add.  BFB_EINVAL for other values. */
+int bfb_call_plan(uint32_t layout, uint64_t size, uint32_t words_per_block, uint32_t word_bits,
+                  uint32_t groups, uint32_t k, uint32_t strategy, int op, uint64_t n, bfb_call_t *out);
+
 /* Streaming copy of `bytes` (a multiple of 16) from src to dst. */
 int bfb_copy(void *d_dst, const void *d_src, uint64_t bytes, void *stream);
 

@@ -2,11 +2,13 @@
 // mapping selection and kernel launch.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <map>
 #include <mutex>
 #include <new>
 
 #include "../../include/bf.h"
+#include "../../include/bf_bench.h"
 #include "bf_hash.hpp"
 #include "bf_kernels.hpp"
 #include "bf_registry.hpp"
@@ -195,17 +197,36 @@ bool default_mapping(const bf_mapping_t& m) {
          !m.atomic_bits && m.strategy == BF_STRATEGY_AUTO;
 }
 
-// Whether a bf_contains of n keys is grouped: with the default mapping (a
-// caller's mapping selects a direct kernel), and not while the stream is
-// being captured (a graph of the lookup then holds no allocation).
-bool groups_lookup(const bf_filter* f, uint64_t n, hipStream_t stream) {
-  if (!lookup_groups(f, n) || !default_mapping(f->mapping[BF_OP_CONTAINS])) return false;
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(stream, &cap) != hipSuccess) {
-    (void)hipGetLastError();
-    return false;
+// The route of a bf_add / bf_contains of n keys.  A caller's mapping selects a
+// direct kernel, or with an add's strategy the construction.
+enum class Route { kDirect, kPartitioned, kLds, kGrouped };
+Route route_of(const bf_filter* f, int op, uint64_t n) {
+  const bool tuned = default_mapping(f->mapping[op]);
+  if (op == BF_OP_ADD) {
+    if (tuned && add_fits_lds(f, n) && resident_runs(f, op)) return Route::kLds;
+    return add_partitions(f, n) ? Route::kPartitioned : Route::kDirect;
   }
-  return cap == hipStreamCaptureStatusNone;
+  if (tuned && lookup_groups(f, n) && lookup_workspace_bytes(f, n) != 0) return Route::kGrouped;
+  return tuned && lookup_fits_lds(f, n) && resident_runs(f, op) ? Route::kLds : Route::kDirect;
+}
+
+bool capturing(hipStream_t stream) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &cap) == hipSuccess) return cap != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
+}
+
+// One bf_add / bf_contains by its route.  A lookup is not grouped while the
+// stream is being captured: a graph of the lookup then holds no allocation.
+bf_status run_routed(bf_filter* f, int op, const uint64_t* keys, uint64_t n, uint8_t* out, hipStream_t stream,
+                     CallMark* mark) {
+  const Route route = route_of(f, op, n);
+  bool taken = false;
+  bf_status st = BF_OK;
+  if (route == Route::kGrouped && !capturing(stream)) st = grouped_lookup(f, keys, n, out, stream, &taken);
+  if (route == Route::kLds) st = resident_call(f, op, keys, n, out, stream, mark, &taken);
+  return taken ? st : launch(f, op, keys, n, out, stream, mark);
 }
 
 bf_status clear_words(void* p, uint64_t nbytes, hipStream_t stream, CallMark* mark = nullptr) {
@@ -489,14 +510,8 @@ bf_status bf_add(bf_filter* f, const uint64_t* d_keys, uint64_t n, void* stream)
   if (d_keys == nullptr || reinterpret_cast<uintptr_t>(d_keys) % 8 != 0) return BF_EINVAL;
   hipStream_t s = static_cast<hipStream_t>(stream);
   const Access access = add_partitions(f, n) ? Access::kOwner : Access::kDirect;
-  return ordered_call(f, s, access, [&](CallMark& mark) {
-    if (add_fits_lds(f, n) && default_mapping(f->mapping[BF_OP_ADD])) {
-      bool taken = false;
-      const bf_status st = resident_call(f, BF_OP_ADD, d_keys, n, nullptr, s, &mark, &taken);
-      if (taken) return st;
-    }
-    return launch(f, BF_OP_ADD, d_keys, n, nullptr, stream, &mark);
-  });
+  return ordered_call(f, s, access,
+                      [&](CallMark& mark) { return run_routed(f, BF_OP_ADD, d_keys, n, nullptr, s, &mark); });
 }
 
 bf_status bf_contains(const bf_filter* f, const uint64_t* d_keys, uint64_t n, uint8_t* d_out,
@@ -507,19 +522,8 @@ bf_status bf_contains(const bf_filter* f, const uint64_t* d_keys, uint64_t n, ui
     return BF_EINVAL;
   bf_filter* g = const_cast<bf_filter*>(f);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  return ordered_call(g, s, Access::kUse, [&](CallMark& mark) {
-    if (groups_lookup(g, n, s)) {
-      bool taken = false;
-      const bf_status st = grouped_lookup(g, d_keys, n, d_out, s, &taken);
-      if (taken) return st;
-    }
-    if (lookup_fits_lds(g, n) && default_mapping(g->mapping[BF_OP_CONTAINS])) {
-      bool taken = false;
-      const bf_status st = resident_call(g, BF_OP_CONTAINS, d_keys, n, d_out, s, &mark, &taken);
-      if (taken) return st;
-    }
-    return launch(g, BF_OP_CONTAINS, d_keys, n, d_out, stream, &mark);
-  });
+  return ordered_call(g, s, Access::kUse,
+                      [&](CallMark& mark) { return run_routed(g, BF_OP_CONTAINS, d_keys, n, d_out, s, &mark); });
 }
 
 bf_status bf_clear(bf_filter* f, void* stream) {
@@ -597,6 +601,54 @@ bf_status bf_tuned_mapping(int op, uint64_t num_blocks, uint32_t words_per_block
                                : BF_STRATEGY_AUTO;
   *out = m;
   return BF_OK;
+}
+
+int bfb_call_plan(uint32_t layout, uint64_t size, uint32_t words_per_block, uint32_t word_bits, uint32_t groups,
+                  uint32_t k, uint32_t strategy, int op, uint64_t n, bfb_call_t* out) {
+  const uint32_t s = words_per_block;
+  if (out == nullptr || (op != BF_OP_ADD && op != BF_OP_CONTAINS) || n == 0) return BFB_EINVAL;
+  if (strategy > BF_STRATEGY_PARTITIONED || (op == BF_OP_CONTAINS && strategy != BF_STRATEGY_AUTO)) return BFB_EINVAL;
+  if (k < 1 || k > static_cast<uint32_t>(kMaxK)) return BFB_EINVAL;
+  bf_filter f{};  // host-side description only: no words
+  f.layout = layout;
+  f.k = k;
+  f.mapping[BF_OP_ADD].strategy = strategy;
+  if (layout == BF_LAYOUT_CLASSIC) {
+    if (size == 0 || size % 64 != 0 || size > (1ull << 40)) return BFB_EINVAL;
+    f.word_bits = 32;
+    f.num_bits = size;
+    f.nbytes = size / 8;
+  } else if (layout == BF_LAYOUT_SECTORIZED || layout == BF_LAYOUT_CACHE_SECTORIZED) {
+    if (!(is_pow2(s) && s <= 16) || !(word_bits == 32 || word_bits == 64)) return BFB_EINVAL;
+    if (size < 1 || size > (1ull << 32)) return BFB_EINVAL;
+    if (layout == BF_LAYOUT_SECTORIZED && k < s) return BFB_EINVAL;
+    if (layout == BF_LAYOUT_CACHE_SECTORIZED && !(is_pow2(groups) && groups <= s && k % groups == 0)) return BFB_EINVAL;
+    f.num_blocks = size;
+    f.s = s;
+    f.word_bits = word_bits;
+    f.groups = layout == BF_LAYOUT_CACHE_SECTORIZED ? groups : 0;
+    f.nbytes = size * s * (word_bits / 8);
+    f.num_bits = f.nbytes * 8;
+  } else {
+    return BFB_EINVAL;
+  }
+  ensure_registry();
+  bfb_call_t c{};
+  const Route route = route_of(&f, op, n);
+  c.route = route == Route::kPartitioned ? BFB_ROUTE_PARTITIONED
+            : route == Route::kLds       ? BFB_ROUTE_LDS
+            : route == Route::kGrouped   ? BFB_ROUTE_GROUPED
+                                         : BFB_ROUTE_DIRECT;
+  if (route == Route::kPartitioned) c.workspace_bytes = partition_workspace_bytes(&f, n);
+  if (route == Route::kGrouped) c.workspace_bytes = lookup_workspace_bytes(&f, n);
+  if (op == BF_OP_ADD && add_partitions(&f, n)) {
+    c.noalloc_pass_keys = noalloc_pass_keys(&f, n, BF_NOALLOC_SCRATCH_BYTES);
+    if (c.noalloc_pass_keys != 0)
+      c.noalloc_pass_bytes = std::max(partition_pass_bytes(&f, c.noalloc_pass_keys),
+                                      partition_pass_bytes(&f, n % c.noalloc_pass_keys));
+  }
+  *out = c;
+  return BFB_OK;
 }
 
 bf_status bf_set_mapping_ex(bf_filter* f, int op, const bf_mapping_t* m) {

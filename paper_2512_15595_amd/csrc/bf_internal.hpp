@@ -70,13 +70,15 @@ struct PartKernels {
   uint32_t threads1;    // workgroup size of the first pass
 };
 bool partition_applicable(const bf_filter* f, uint64_t n);
-// Workspace bytes a partitioned add of n keys is accounted at (0 if the
-// filter cannot be partitioned).
+// Workspace bytes a partitioned add of n keys takes from the device pool at a
+// time (0 if the filter cannot be partitioned).
 uint64_t partition_workspace_bytes(const bf_filter* f, uint64_t n);
 bf_status partitioned_add(bf_filter* f, const uint64_t* keys, uint64_t n, hipStream_t stream);
-// A partitioned add of n keys (at most 2^28 records) over a caller-given
-// workspace of ws_bytes: BF_ESCRATCH if it is accounted at more, BF_EINVAL
-// beyond 2^28 records.  Enqueues the kernels only (no allocation).
+// Keys per pass of a partitioned add of n keys over a caller-given workspace of
+// ws_bytes (0: not taken), and the add: BF_ESCRATCH if it is not taken,
+// BF_EINVAL beyond 2^28 records.  Enqueues the kernels only (no allocation).
+uint64_t noalloc_pass_keys(const bf_filter* f, uint64_t n, uint64_t ws_bytes);
+uint64_t partition_pass_bytes(const bf_filter* f, uint64_t n);  // workspace of one pass
 bf_status partitioned_add_in(bf_filter* f, const uint64_t* keys, uint64_t n, hipStream_t stream,
                              void* ws, uint64_t ws_bytes);
 uint32_t part_chunk_shift(uint32_t words_per_block, uint32_t word_bits);
@@ -99,6 +101,8 @@ hipMemPool_t workspace_pool(int device);
 // enqueued, where it has no kernel or no workspace: the caller looks up
 // directly).
 bool lookup_groups(const bf_filter* f, uint64_t n);
+// Workspace bytes of a grouped lookup (0 if it has no kernel).
+uint64_t lookup_workspace_bytes(const bf_filter* f, uint64_t n);
 bf_status grouped_lookup(const bf_filter* f, const uint64_t* keys, uint64_t n, uint8_t* out, hipStream_t stream,
                          bool* taken);
 
@@ -107,6 +111,7 @@ bf_status grouped_lookup(const bf_filter* f, const uint64_t* keys, uint64_t n, u
 struct CallMark;
 bool lookup_fits_lds(const bf_filter* f, uint64_t n);
 bool add_fits_lds(const bf_filter* f, uint64_t n);
+bool resident_runs(const bf_filter* f, int op);  // whether the layout has the kernels
 bf_status resident_call(const bf_filter* f, int op, const uint64_t* keys, uint64_t n, uint8_t* out,
                         hipStream_t stream, CallMark* mark, bool* taken);
 

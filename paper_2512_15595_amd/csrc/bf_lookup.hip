@@ -202,6 +202,11 @@ bool add_fits_lds(const bf_filter* f, uint64_t n) {
   return f->layout == BF_LAYOUT_SECTORIZED && f->nbytes <= kResidentBytes[1] && n >= 8 * f->nbytes;
 }
 
+bool resident_runs(const bf_filter* f, int op) {
+  const int idx = batch_index(op, static_cast<int>(f->word_bits), static_cast<int>(f->s), k_index(f->k));
+  return kernel_table(f->salts == kSaltsParquet).resident_fn[f->nbytes > kResidentBytes[0]][idx] != nullptr;
+}
+
 bf_status resident_call(const bf_filter* f, int op, const uint64_t* keys, uint64_t n, uint8_t* out,
                         hipStream_t stream, CallMark* mark, bool* taken) {
   *taken = false;
@@ -232,19 +237,38 @@ bf_status resident_call(const bf_filter* f, int op, const uint64_t* keys, uint64
              : BF_EDEVICE;
 }
 
+namespace {
+
+struct LookupKernels {
+  const void *group, *regroup, *test, *ret;
+};
+
+// The geometry of a pass of n keys and its kernels; false if there are none.
+bool plan_lookup(const bf_filter* f, uint64_t n, Lookup& x, LookupKernels& k) {
+  const int idx = batch_index(kOpContains, static_cast<int>(f->word_bits), static_cast<int>(f->s), k_index(f->k));
+  x.two = ceil_div(f->num_blocks, 1ull << chunk_shift(f, false)) > static_cast<uint64_t>(kLookupDigits);
+  layout(f, n, nullptr, x);
+  const Registry& r = kernel_table(f->salts == kSaltsParquet);
+  k = {group_keys_fn(x.g.digits, !x.two, false, true), x.two ? regroup_fn(x.r.digits, true) : nullptr,
+       r.lookup_fn[x.two ? 1 : 0][idx], r.return_fn[idx]};
+  return k.group != nullptr && k.test != nullptr && k.ret != nullptr && (!x.two || k.regroup != nullptr);
+}
+
+}  // namespace
+
+uint64_t lookup_workspace_bytes(const bf_filter* f, uint64_t n) {
+  Lookup x{};
+  LookupKernels k;
+  return plan_lookup(f, std::min(n, kMaxPass), x, k) ? x.total : 0;
+}
+
 bf_status grouped_lookup(const bf_filter* f, const uint64_t* keys, uint64_t n, uint8_t* out, hipStream_t stream,
                          bool* taken) {
   *taken = false;
-  const int idx = batch_index(kOpContains, static_cast<int>(f->word_bits), static_cast<int>(f->s), k_index(f->k));
   Lookup x{};
-  x.two = ceil_div(f->num_blocks, 1ull << chunk_shift(f, false)) > static_cast<uint64_t>(kLookupDigits);
+  LookupKernels k;
   const uint64_t pass = std::min(n, kMaxPass);
-  layout(f, pass, nullptr, x);
-  const void* group = group_keys_fn(x.g.digits, !x.two, false, true);
-  const void* regroup = x.two ? regroup_fn(x.r.digits, true) : nullptr;
-  const void* test = kernel_table(f->salts == kSaltsParquet).lookup_fn[x.two ? 1 : 0][idx];
-  const void* ret = kernel_table(f->salts == kSaltsParquet).return_fn[idx];
-  if (group == nullptr || test == nullptr || ret == nullptr || (x.two && regroup == nullptr)) return BF_OK;
+  if (!plan_lookup(f, pass, x, k)) return BF_OK;
   hipMemPool_t pool = workspace_pool(f->device);
   void* ws = nullptr;
   if (pool == nullptr || hipMallocFromPoolAsync(&ws, x.total, pool, stream) != hipSuccess) {
@@ -273,15 +297,15 @@ bf_status grouped_lookup(const bf_filter* f, const uint64_t* keys, uint64_t n, u
       void* args[] = {arg};
       if (e == hipSuccess) e = hipLaunchKernel(fn, dim3(static_cast<uint32_t>(grid)), dim3(threads), args, 0, stream);
     };
-    run(group, ceil_div(x.g.steps, x.g.wg_steps), kGroupThreads, &x.g);
+    run(k.group, ceil_div(x.g.steps, x.g.wg_steps), kGroupThreads, &x.g);
     if (x.two) {
       run(regroup_plan_fn(), x.r.items, kPlanThreads, &x.r);
       run(regroup_scan_fn(), 1, kScanThreads, &x.r);
-      run(regroup, x.r.items, kGroupThreads, &x.r);
+      run(k.regroup, x.r.items, kGroupThreads, &x.r);
     }
-    run(test, x.chunks * x.t.split, kTestThreads, &x.t);
+    run(k.test, x.chunks * x.t.split, kTestThreads, &x.t);
     if (x.two) run(reinterpret_cast<const void*>(&return_slots_kernel), x.steps2, kReturnThreads, &x.slots);
-    run(ret, x.g.steps, kReturnThreads, &x.keys);
+    run(k.ret, x.g.steps, kReturnThreads, &x.keys);
   }
   if (hipFreeAsync(ws, stream) != hipSuccess && e == hipSuccess) e = hipErrorUnknown;
   return e == hipSuccess ? BF_OK : BF_EDEVICE;

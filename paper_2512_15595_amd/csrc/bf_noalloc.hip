@@ -60,11 +60,8 @@ extern "C" bf_status bf_add_noalloc(bf_filter* f, const uint64_t* d_keys, uint64
   if (d_keys == nullptr || reinterpret_cast<uintptr_t>(d_keys) % 8 != 0) return BF_EINVAL;
   // a direct add uses no workspace: it is bf_add itself
   if (!add_partitions(f, n)) return bf_add(f, d_keys, n, stream);
-  // one pass whose workspace fits the array, checked before anything is
-  // enqueued
-  const uint64_t per_key = f->layout == BF_LAYOUT_CLASSIC ? f->k : 1;
-  if (n > (uint64_t{1} << 28) / per_key || partition_workspace_bytes(f, n) > kScratchBytes)
-    return BF_ESCRATCH;
+  // whether the add is taken is known before anything is enqueued
+  if (noalloc_pass_keys(f, n, kScratchBytes) == 0) return BF_ESCRATCH;
   int device = -1;
   if (hipGetDevice(&device) != hipSuccess || device != f->device) return BF_EINVAL;
   DeviceScratch* d = nullptr;

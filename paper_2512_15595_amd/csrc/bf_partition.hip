@@ -256,16 +256,17 @@ bool single_geometry(const bf_filter* f, uint64_t n, PartArgs& a, PartLayout& L)
   return true;
 }
 
-// The workspace bytes at which a partitioned add is accounted (a server's
-// memory budget, the limit of bf_add_noalloc): 14-22 bytes per key, about 6
-// into a filter that takes one pass.  The sum is that of buckets holding the
-// expected load of uniformly hashed keys plus six standard deviations.
+// The size at which bf_add_noalloc accounts an add of n keys: 14-22 bytes per
+// key, about 6 into a filter that takes one pass.  It is the size of buckets
+// for the expected load of uniformly hashed keys plus six standard
+// deviations, not what a pass takes: it only sets the number of keys that
+// call accepts, which callers rely on, whatever the geometry.
 uint64_t capacity(double mean, uint64_t margin, uint64_t align) {
   const double c = mean + 6.0 * std::sqrt(mean) + static_cast<double>(margin);
   return (static_cast<uint64_t>(std::ceil(c)) + align - 1) / align * align;
 }
 
-uint64_t accounted_bytes(const bf_filter* f, uint64_t n) {
+uint64_t noalloc_bytes(const bf_filter* f, uint64_t n) {
   uint32_t shift;
   const uint64_t chunks = filter_chunks(f, &shift);
   const uint64_t per_key = records_per_key(f), records = n * per_key;
@@ -379,29 +380,29 @@ uint64_t max_pass_keys(const bf_filter* f) { return std::max<uint64_t>((1ull << 
 
 }  // namespace
 
-// The keys of a pass of an add of n keys over ws_bytes: n, halved until the
-// workspace of a pass fits, and that of the shorter last pass too (a geometry
-// of fewer keys can need more: fewer second-pass items hold more batches).
-// 0 if there is none.
-uint64_t pass_keys_in(const bf_filter* f, uint64_t n, uint64_t ws_bytes) {
-  auto fits = [&](uint64_t keys) {
-    PartArgs a{};
-    PartLayout L{};
-    return keys == 0 || (single_geometry(f, keys, a, L) && L.total <= ws_bytes);
-  };
+uint64_t partition_pass_bytes(const bf_filter* f, uint64_t n) {
+  PartArgs a{};
+  PartLayout L{};
+  return n > 0 && single_geometry(f, n, a, L) ? L.total : 0;
+}
+
+// noalloc_bytes decides what is taken; an add whose real workspace is larger
+// than ws_bytes (few keys into a large filter, or a table of many digits)
+// runs in several passes over it, which give the same words: of n keys,
+// halved until the workspace of a pass fits, and that of the shorter last
+// pass too (a geometry of fewer keys can need more: fewer second-pass items
+// hold more batches).
+uint64_t noalloc_pass_keys(const bf_filter* f, uint64_t n, uint64_t ws_bytes) {
+  if (!partition_applicable(f, n) || n > max_pass_keys(f) || noalloc_bytes(f, n) > ws_bytes) return 0;
   for (uint64_t pass = n; pass > 0; pass = pass > 1 ? (pass + 1) / 2 : 0)
-    if (fits(pass) && fits(n % pass)) return pass;
+    if (std::max(partition_pass_bytes(f, pass), partition_pass_bytes(f, n % pass)) <= ws_bytes) return pass;
   return 0;
 }
 
-// accounted_bytes decides what is taken; an add whose real workspace is
-// larger than ws_bytes (few keys into a large filter, or a table of many
-// digits) runs in several passes over it, which give the same words.
 bf_status partitioned_add_in(bf_filter* f, const uint64_t* keys, uint64_t n, hipStream_t stream,
                              void* ws, uint64_t ws_bytes) {
   if (n == 0 || n > max_pass_keys(f)) return BF_EINVAL;
-  if (accounted_bytes(f, n) > ws_bytes) return BF_ESCRATCH;
-  const uint64_t pass = pass_keys_in(f, n, ws_bytes);
+  const uint64_t pass = noalloc_pass_keys(f, n, ws_bytes);
   if (pass == 0) return BF_ESCRATCH;
   for (uint64_t off = 0; off < n; off += pass) {
     PartArgs a{};
@@ -413,8 +414,10 @@ bf_status partitioned_add_in(bf_filter* f, const uint64_t* keys, uint64_t n, hip
   return BF_OK;
 }
 
-// Passes of at most 2^28 records keep the workspace under ~4.5 GB; each pass
-// after the first reads and writes the touched chunks once more.
+// Passes of at most 2^28 records bound the workspace (4.1 GiB into 1 GiB, 4.7
+// into 4 GiB, 8.4 into 32 GiB; 5.1, 5.9 and, at 16 GiB, 7.6 for the classic
+// filter: the shorter the first pass's runs, the emptier their last units);
+// each pass after the first reads and writes the touched chunks once more.
 bf_status partitioned_add(bf_filter* f, const uint64_t* keys, uint64_t n, hipStream_t stream) {
   const uint64_t max_keys = max_pass_keys(f);
   for (uint64_t off = 0; off < n; off += max_keys) {
@@ -425,8 +428,10 @@ bf_status partitioned_add(bf_filter* f, const uint64_t* keys, uint64_t n, hipStr
 }
 
 uint64_t partition_workspace_bytes(const bf_filter* f, uint64_t n) {
-  n = std::min(n, max_pass_keys(f));
-  return partition_applicable(f, n) ? accounted_bytes(f, n) : 0;
+  if (!partition_applicable(f, n)) return 0;
+  const uint64_t most = max_pass_keys(f), rest = n % most;
+  // the passes' workspaces follow one another
+  return std::max(partition_pass_bytes(f, std::min(n, most)), n > most ? partition_pass_bytes(f, rest) : 0);
 }
 
 }  // namespace bfhip
