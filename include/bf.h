@@ -93,8 +93,8 @@ typedef struct bf_filter bf_filter; /* opaque handle, owns the device words */
  *   strategy        add only: BF_STRATEGY_*.  The partitioned strategy
  *                   radix-partitions the keys by 64 KiB filter chunk and
  *                   updates each chunk in LDS, so a bulk add performs no
- *                   global atomics; it takes a workspace of 14-22 bytes per key
- *                   (about 6 for a filter of at most 1024 chunks, 64 MiB,
+ *                   global atomics; it takes a workspace of 15-21 bytes per key,
+ *                   of at most 2^28 keys at a time (about 6 for a filter of at most 1024 chunks, 64 MiB,
  *                   which is partitioned in one pass)
  *                   from a per-device stream-ordered memory pool and returns
  *                   it at its end on the same stream (no device
@@ -223,8 +223,10 @@ bf_status bf_set_mapping_ex(bf_filter *f, int op, const bf_mapping_t *m);
  * add mapping: BF_STRATEGY_DIRECT or BF_STRATEGY_PARTITIONED, the automatic
  * choice resolved by the measured crossover (partitioned from about 1.5 M
  * keys + filter bytes / 80; for the classic layout n counts k records per
- * key).  For callers that plan workspace memory (14-22 bytes per key for a
- * partitioned add, about 6 into a filter of at most 64 MiB).  Host only:
+ * key).  For callers that plan workspace memory (15-21 bytes per key for a
+ * partitioned add, about 6 into a filter of at most 64 MiB; with the default
+ * mapping an add of 8 keys per filter byte or more into up to 160 KiB runs in
+ * LDS without workspace, whichever strategy this reports).  Host only:
  * enqueues nothing and touches no device.
  * BF_EINVAL if f or out is NULL. */
 bf_status bf_add_strategy(const bf_filter *f, uint64_t n, uint32_t *out);
@@ -255,8 +257,7 @@ bf_status bf_tuned_mapping(int op, uint64_t num_blocks, uint32_t words_per_block
  * 12 M into 1 GiB).  It runs in as many passes over the array as its records
  * need (the words are the same); larger adds give BF_ESCRATCH with nothing
  * enqueued.  Calls on one device share the array, which keeps the last call's
- * contents (no kernel reads what its own call has not
- * written): outside graph capture the library orders them
+ * contents (no result depends on them): outside graph capture the library orders them
  * with one event per device, so they never overlap; calls captured into
  * graphs are ordered by their caller, and captured calls that overlap on
  * one device race on the array.  The current device must be the filter's

@@ -238,7 +238,7 @@ bf_status plan_partitioned(bf_batch* b, bf_filter* const* filters, uint32_t nfil
   if (strategy == BF_STRATEGY_AUTO && !(dense_chunks >= 512 && n_dense >= (1ull << 21))) return BF_OK;
   PartArgs a{};
   PartLayout L{};
-  if (!part_digits(chunks, shift, a)) return BF_OK;
+  if (!part_digits(chunks, shift, kMaxDigits2, a)) return BF_OK;
   const uint64_t f2 = a.r.digits, f1 = a.g.digits;
   // First-pass ranges: at most range1 keys of one dense filter each (the
   // keys of direct filters are not read), whose steps are numbered in filter

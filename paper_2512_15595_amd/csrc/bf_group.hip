@@ -8,8 +8,9 @@ namespace bfhip {
 
 namespace {
 
-// The number of output steps of every item: its units, kStepUnits to a step,
+// The number of output steps of every item: its units, kStep / UNIT to a step,
 // a batch of kRegroupRuns runs at a time.
+template <int UNIT>
 __global__ __launch_bounds__(kPlanThreads) void regroup_plan_kernel(RegroupArgs a) {
   __shared__ uint32_t wave_sum[kPlanThreads / 64];
   const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
@@ -19,7 +20,7 @@ __global__ __launch_bounds__(kPlanThreads) void regroup_plan_kernel(RegroupArgs 
   for (uint32_t base = it.t0; base < it.t1; base += kRegroupRuns) {
     uint32_t sum = 0;
     for (uint32_t i = tid; i < kRegroupRuns && base + i < it.t1; i += kPlanThreads)
-      sum += (run_len(entries[base + i]) + kUnit - 1) / kUnit;
+      sum += (run_len(entries[base + i]) + UNIT - 1) / UNIT;
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) sum += __shfl_down(sum, off, 64);
     if (lane == 0) wave_sum[wave] = sum;
@@ -27,7 +28,7 @@ __global__ __launch_bounds__(kPlanThreads) void regroup_plan_kernel(RegroupArgs 
     uint32_t total = 0;
 #pragma unroll
     for (int w = 0; w < kPlanThreads / 64; ++w) total += wave_sum[w];
-    steps += (total + kStepUnits - 1) / kStepUnits;
+    steps += (total + kStep / UNIT - 1) / (kStep / UNIT);
     __syncthreads();
   }
   if (tid == 0) a.item_count[blockIdx.x] = steps;
@@ -82,20 +83,28 @@ const void* group_keys_fn(uint32_t digits, bool split, bool multi, bool place) {
   return nullptr;
 }
 
-const void* regroup_fn(uint32_t digits, bool place) {
-  if (digits <= 128)
-    return place ? reinterpret_cast<const void*>(&regroup_kernel<128, 16, true>)
-                 : reinterpret_cast<const void*>(&regroup_kernel<128, 16, false>);
-  if (digits <= 256)
-    return place ? reinterpret_cast<const void*>(&regroup_kernel<256, 16, true>)
-                 : reinterpret_cast<const void*>(&regroup_kernel<256, 16, false>);
-  if (digits <= 512)
-    return place ? reinterpret_cast<const void*>(&regroup_kernel<512, 8, true>)
-                 : reinterpret_cast<const void*>(&regroup_kernel<512, 8, false>);
-  return nullptr;
+// Short units: a filter of 256 first digits or more (then 128 second digits
+// or more).  Places: a lookup's second digits are at most 256.
+const void* regroup_fn(uint32_t digits, bool place, bool short_units) {
+  if (place)
+    return digits <= 128   ? reinterpret_cast<const void*>(&regroup_kernel<128, 16, true, kUnit>)
+           : digits <= 256 ? reinterpret_cast<const void*>(&regroup_kernel<256, 16, true, kUnit>)
+                           : nullptr;
+  if (short_units)
+    return digits <= 256    ? reinterpret_cast<const void*>(&regroup_kernel<256, 16, false, kShortUnit>)
+           : digits <= 512  ? reinterpret_cast<const void*>(&regroup_kernel<512, 8, false, kShortUnit>)
+           : digits <= 1024 ? reinterpret_cast<const void*>(&regroup_kernel<1024, 8, false, kShortUnit>)
+                            : nullptr;
+  return digits <= 128   ? reinterpret_cast<const void*>(&regroup_kernel<128, 16, false, kUnit>)
+         : digits <= 256 ? reinterpret_cast<const void*>(&regroup_kernel<256, 16, false, kUnit>)
+         : digits <= 512 ? reinterpret_cast<const void*>(&regroup_kernel<512, 8, false, kUnit>)
+                         : nullptr;
 }
 
-const void* regroup_plan_fn() { return reinterpret_cast<const void*>(&regroup_plan_kernel); }
+const void* regroup_plan_fn(bool short_units) {
+  return short_units ? reinterpret_cast<const void*>(&regroup_plan_kernel<kShortUnit>)
+                     : reinterpret_cast<const void*>(&regroup_plan_kernel<kUnit>);
+}
 const void* regroup_scan_fn() { return reinterpret_cast<const void*>(&regroup_scan_kernel); }
 
 }  // namespace bfhip

@@ -425,8 +425,9 @@ __global__ __launch_bounds__(kGroupThreads) void group_keys_kernel(GroupArgs a) 
 // ---------------------------------------------------------------------------
 // Second pass: group the records of one first-pass digit by the next digit.
 // ---------------------------------------------------------------------------
-constexpr int kUnit = 16;                      // slots per unit of the second pass
-constexpr int kStepUnits = kStep / kUnit;      // units per step
+constexpr int kUnit = 16;                      // slots per unit of the second pass ...
+constexpr int kShortUnit = 8;                  // ... where the first pass's runs are short
+constexpr int kStepUnits = kStep / kUnit;      // units per step of a lookup
 constexpr int kRegroupRuns = 1024;             // runs per batch
 
 // One workgroup's work: the runs of digit d1 in steps [t0, t1).
@@ -474,19 +475,21 @@ __device__ __forceinline__ PartItem regroup_item(const RegroupArgs& a, uint32_t 
 constexpr int kPlanThreads = 256;   // counting every item's output steps
 constexpr int kScanThreads = 1024;  // ... and their prefix sums (one workgroup)
 
-template <int D, int ROWS>
+template <int D, int ROWS, int UNIT>
 struct RegroupLds {
   GroupLds<D, ROWS> g;
   uint32_t run[kRegroupRuns];
   uint32_t pre[kRegroupRuns];          // units before each run of the batch
-  uint32_t list[2][kStepUnits];        // the step's units, of even and odd steps
+  uint32_t list[2][kStep / UNIT];      // the step's units, of even and odd steps
   uint32_t wave_sum[kGroupThreads / 64];
 };
 
-template <int D, int ROWS, bool PLACE>
+template <int D, int ROWS, bool PLACE, int UNIT>
 __global__ __launch_bounds__(kGroupThreads) void regroup_kernel(RegroupArgs a) {
   static_assert(kRegroupRuns == kGroupThreads, "a thread per run of a batch");
-  __shared__ __attribute__((aligned(16))) RegroupLds<D, ROWS> l;
+  static_assert(!PLACE || UNIT == kUnit, "the return of a lookup's results reads units of kUnit slots");
+  constexpr int kUnits = kStep / UNIT;
+  __shared__ __attribute__((aligned(16))) RegroupLds<D, ROWS, UNIT> l;
   const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
   for (uint32_t d = tid; d < D; d += kGroupThreads) l.g.cnt[d] = 0;
   const uint32_t item = regroup_item_of(a, blockIdx.x);
@@ -497,7 +500,7 @@ __global__ __launch_bounds__(kGroupThreads) void regroup_kernel(RegroupArgs a) {
   const uint32_t* entries = a.table1 + it.d1 * a.stride1;
   for (uint32_t base = it.t0; base < it.t1; base += kRegroupRuns) {
     const uint32_t e = base + tid < it.t1 ? entries[base + tid] : 0u;
-    const uint32_t units = (run_len(e) + kUnit - 1) / kUnit;
+    const uint32_t units = (run_len(e) + UNIT - 1) / UNIT;
     uint32_t incl = units;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
@@ -519,10 +522,10 @@ __global__ __launch_bounds__(kGroupThreads) void regroup_kernel(RegroupArgs a) {
     if (total == 0) continue;
     // unit u of the batch is in the last run r with pre[r] <= u
     auto find = [&](uint32_t w) {
-      if (tid < kStepUnits) {
-        const uint32_t u = w * kStepUnits + tid;
+      if (tid < kUnits) {
+        const uint32_t u = w * kUnits + tid;
         uint32_t v = 0xffffffffu;
-        if (u < total) v = find_unit<kUnit, kRegroupRuns>(l.pre, l.run, u);
+        if (u < total) v = find_unit<UNIT, kRegroupRuns>(l.pre, l.run, u);
         l.list[w & 1u][tid] = v;
       }
     };
@@ -533,13 +536,13 @@ __global__ __launch_bounds__(kGroupThreads) void regroup_kernel(RegroupArgs a) {
       next_ok = 0;
 #pragma unroll
       for (int j = 0; j < kGroupPer; ++j) {
-        const uint32_t v = l.list[w & 1u][(tid + j * kGroupThreads) / kUnit];
-        const bool ok = v != 0xffffffffu && tid % kUnit <= (v & 15u);
-        next[j] = src[ok ? (v >> 4) + tid % kUnit : 0u];
+        const uint32_t v = l.list[w & 1u][(tid + j * kGroupThreads) / UNIT];
+        const bool ok = v != 0xffffffffu && tid % UNIT <= (v & 15u);
+        next[j] = src[ok ? (v >> 4) + tid % UNIT : 0u];
         next_ok |= static_cast<uint32_t>(ok) << j;
       }
     };
-    const uint32_t windows = (total + kStepUnits - 1) / kStepUnits;
+    const uint32_t windows = (total + kUnits - 1) / kUnits;
     find(0);
     __syncthreads();
     load(0);
@@ -564,9 +567,9 @@ __global__ __launch_bounds__(kGroupThreads) void regroup_kernel(RegroupArgs a) {
           a.place[step * kStep + tid + j * kGroupThreads] = static_cast<uint16_t>(rank[j] < a.clip ? pos : kNoPlace);
       }
       if constexpr (PLACE) {
-        if (tid < kStepUnits) {
+        if (tid < kUnits) {
           const uint32_t v = l.list[w & 1u][tid];
-          a.units[step * kStepUnits + tid] = v == 0xffffffffu ? v : v + (base * kStep << 4);
+          a.units[step * kUnits + tid] = v == 0xffffffffu ? v : v + (base * kStep << 4);
         }
       }
       __syncthreads();
@@ -582,8 +585,8 @@ __global__ __launch_bounds__(kGroupThreads) void regroup_kernel(RegroupArgs a) {
 // (nullptr for an unsupported number), the second pass and its
 // two planning kernels.
 const void* group_keys_fn(uint32_t digits, bool split, bool multi, bool place);
-const void* regroup_fn(uint32_t digits, bool place);
-const void* regroup_plan_fn();
+const void* regroup_fn(uint32_t digits, bool place, bool short_units);
+const void* regroup_plan_fn(bool short_units);
 const void* regroup_scan_fn();
 
 }  // namespace bfhip

@@ -82,7 +82,7 @@ uint64_t partition_pass_bytes(const bf_filter* f, uint64_t n);  // workspace of 
 bf_status partitioned_add_in(bf_filter* f, const uint64_t* keys, uint64_t n, hipStream_t stream,
                              void* ws, uint64_t ws_bytes);
 uint32_t part_chunk_shift(uint32_t words_per_block, uint32_t word_bits);
-bool part_digits(uint64_t chunks, uint32_t chunk_shift, PartArgs& a);
+bool part_digits(uint64_t chunks, uint32_t chunk_shift, uint32_t most_digits2, PartArgs& a);
 void part_layout_two(PartArgs& a, PartLayout& L, uint64_t steps, uint64_t items, uint64_t batches, uint64_t runs,
                      uint64_t records);
 void part_bind(PartArgs& a, const PartLayout& L, void* base);

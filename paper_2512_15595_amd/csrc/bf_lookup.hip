@@ -249,7 +249,7 @@ bool plan_lookup(const bf_filter* f, uint64_t n, Lookup& x, LookupKernels& k) {
   x.two = ceil_div(f->num_blocks, 1ull << chunk_shift(f, false)) > static_cast<uint64_t>(kLookupDigits);
   layout(f, n, nullptr, x);
   const Registry& r = kernel_table(f->salts == kSaltsParquet);
-  k = {group_keys_fn(x.g.digits, !x.two, false, true), x.two ? regroup_fn(x.r.digits, true) : nullptr,
+  k = {group_keys_fn(x.g.digits, !x.two, false, true), x.two ? regroup_fn(x.r.digits, true, false) : nullptr,
        r.lookup_fn[x.two ? 1 : 0][idx], r.return_fn[idx]};
   return k.group != nullptr && k.test != nullptr && k.ret != nullptr && (!x.two || k.regroup != nullptr);
 }
@@ -299,7 +299,7 @@ bf_status grouped_lookup(const bf_filter* f, const uint64_t* keys, uint64_t n, u
     };
     run(k.group, ceil_div(x.g.steps, x.g.wg_steps), kGroupThreads, &x.g);
     if (x.two) {
-      run(regroup_plan_fn(), x.r.items, kPlanThreads, &x.r);
+      run(regroup_plan_fn(false), x.r.items, kPlanThreads, &x.r);
       run(regroup_scan_fn(), 1, kScanThreads, &x.r);
       run(k.regroup, x.r.items, kGroupThreads, &x.r);
     }

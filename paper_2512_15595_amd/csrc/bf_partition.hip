@@ -46,9 +46,9 @@ uint32_t part_chunk_shift(uint32_t words_per_block, uint32_t word_bits) {
 // Digits balanced between the passes: f2 ~ sqrt(chunks).  Both passes write
 // whole steps, so their cost hardly depends on the digits; what does is the
 // length of the runs that the next pass reads.
-bool part_digits(uint64_t chunks, uint32_t chunk_shift, PartArgs& a) {
+bool part_digits(uint64_t chunks, uint32_t chunk_shift, uint32_t most_digits2, PartArgs& a) {
   const uint64_t root = static_cast<uint64_t>(std::ceil(std::sqrt(static_cast<double>(chunks))));
-  const uint32_t f2 = std::min<uint32_t>(ceil_pow2(std::max<uint64_t>(root, 1)), kMaxDigits2);
+  const uint32_t f2 = std::min<uint32_t>(ceil_pow2(std::max<uint64_t>(root, 1)), most_digits2);
   const uint64_t f1 = ceil_div(chunks, f2);
   if (chunks == 0 || f1 > static_cast<uint64_t>(kMaxDigits)) return false;
   a.p.chunk_shift = chunk_shift;
@@ -64,7 +64,7 @@ bool part_digits(uint64_t chunks, uint32_t chunk_shift, PartArgs& a) {
 
 // The two-pass buffers for `steps` first-pass steps, `items` second-pass
 // items of `batches` batches in all, at most `runs` non-empty runs of the
-// first table and `records` records.  A run of c records is ceil(c / kUnit)
+// first table and `records` records.  A run of c records is ceil(c / unit)
 // units and only a batch's last output step is partial, which bounds the
 // second pass's steps whatever the keys are.
 void part_layout_two(PartArgs& a, PartLayout& L, uint64_t steps, uint64_t items, uint64_t batches, uint64_t runs,
@@ -75,8 +75,9 @@ void part_layout_two(PartArgs& a, PartLayout& L, uint64_t steps, uint64_t items,
   a.r.stride1 = a.g.stride;
   a.r.steps1 = a.g.steps;
   a.r.items = static_cast<uint32_t>(items);
-  const uint64_t units = records / kUnit + std::min(runs, records);
-  const uint64_t steps2 = units / kStepUnits + batches;
+  const uint64_t unit = a.short_units ? kShortUnit : kUnit;
+  const uint64_t units = records / unit + std::min(runs, records);
+  const uint64_t steps2 = units / (kStep / unit) + batches;
   a.r.stride2 = ceil_div(steps2, 16) * 16;
   uint64_t off = 0;
   auto take = [&off](uint64_t bytes) {
@@ -176,9 +177,9 @@ PartKernels part_kernels(const bf_filter* f, const PartArgs& a) {
   }
   if (f->layout != BF_LAYOUT_CLASSIC) k.group = group_keys_fn(a.g.digits, a.one_pass, a.g.ranges != nullptr, false);
   if (!a.one_pass) {
-    k.plan = regroup_plan_fn();
+    k.plan = regroup_plan_fn(a.short_units);
     k.scan = regroup_scan_fn();
-    k.regroup = regroup_fn(a.r.digits, false);
+    k.regroup = regroup_fn(a.r.digits, false, a.short_units);
   }
   return k;
 }
@@ -243,7 +244,13 @@ bool single_geometry(const bf_filter* f, uint64_t n, PartArgs& a, PartLayout& L)
     one_pass_geometry(chunks, shift, steps, a, L);
     return true;
   }
-  if (!part_digits(chunks, shift, a)) return false;
+  if (chunks > static_cast<uint64_t>(kMaxChunks) || !part_digits(chunks, shift, kWideDigits2, a)) return false;
+  // The fewer records a first-pass run has (32 of a step of 256 digits), the
+  // more of its last unit is empty, and the second pass's buffers must hold
+  // that for any keys: units of 8 slots and 1,024 second digits instead of 512
+  // keep the workspace of 2^28 keys into 32 GiB at 5.3 GiB, not 8.4, and into
+  // 4 GiB at 4.3, not 4.7.
+  a.short_units = a.g.digits >= 256;
   // Second-pass items of about 64 Ki records (8 steps), and at least about
   // 512 of them where every item still has a full step.
   const uint64_t per_bucket = ceil_div(records, a.g.digits);
@@ -276,7 +283,7 @@ uint64_t noalloc_bytes(const bf_filter* f, uint64_t n) {
   uint64_t off = 0, fills = chunks;
   if (two) {
     PartArgs a{};
-    if (!part_digits(chunks, shift, a)) return 0;
+    if (!part_digits(chunks, shift, kMaxDigits2, a)) return 0;
     const uint64_t keys = step_keys(per_key);
     const uint64_t range = std::max(ceil_div(ceil_div(n, 1024), keys) * keys, keys);
     const uint64_t g1 = std::max<uint64_t>(ceil_div(n, range), 1);
@@ -414,8 +421,8 @@ bf_status partitioned_add_in(bf_filter* f, const uint64_t* keys, uint64_t n, hip
   return BF_OK;
 }
 
-// Passes of at most 2^28 records bound the workspace (4.1 GiB into 1 GiB, 4.7
-// into 4 GiB, 8.4 into 32 GiB; 5.1, 5.9 and, at 16 GiB, 7.6 for the classic
+// Passes of at most 2^28 records bound the workspace (4.1 GiB into 1 GiB, 4.3
+// into 4 GiB, 5.3 into 32 GiB; 5.1, 5.3 and, at 16 GiB, 6.5 for the classic
 // filter: the shorter the first pass's runs, the emptier their last units);
 // each pass after the first reads and writes the touched chunks once more.
 bf_status partitioned_add(bf_filter* f, const uint64_t* keys, uint64_t n, hipStream_t stream) {

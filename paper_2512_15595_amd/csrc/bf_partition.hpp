@@ -43,6 +43,8 @@ constexpr int kApplyList = 1536;                    // unit entries listed at on
 constexpr int kChunkBytes = 64 * 1024;              // LDS bytes owned per chunk
 constexpr int kMaxDigits = 1024;                    // digit fan-out limit of the first pass
 constexpr int kMaxDigits2 = 512;                    // ... and of the second (chunks per high digit)
+constexpr int kMaxChunks = kMaxDigits * kMaxDigits2;  // of a partitioned filter
+constexpr int kWideDigits2 = 1024;                  // second digits of one filter beyond 16 GiB
 constexpr int kChunkDigits = kMaxDigits;            // chunks up to which the first pass sorts by chunk
 constexpr int kVecPerThread = kChunkBytes / 16 / kApplyThreads;  // 16-byte chunk vectors per apply thread
 static_assert(kVecPerThread * 16 * kApplyThreads == kChunkBytes, "apply covers a chunk exactly");
@@ -90,6 +92,7 @@ struct PartArgs {
   uint32_t nranges;  // plans: first-pass workgroups
   uint32_t nwork;    // plans: apply workgroups
   bool one_pass;
+  bool short_units;  // second pass in units of kShortUnit slots
 };
 
 template <typename W>

@@ -73,14 +73,15 @@ def _two_pass_bytes(chunks, n, k):
 
     steps = -(-n // (STEP if k == 1 else 512 * (STEP // 512 // k)))  # classic: whole keys of 512 threads
     records = n * k
-    digits2 = min(1 << math.isqrt(chunks - 1).bit_length(), 512)
+    digits2 = 1 << math.isqrt(chunks - 1).bit_length()
     digits1 = -(-chunks // digits2)
     share = -(-records // digits1)
     per_digit = max(-(-share // 65536), min(-(-512 // digits1), share // STEP), 1)
     items = digits1 * per_digit
     batches = items * -(-(-(-steps // per_digit)) // 1024)
-    # a run of c records takes ceil(c / 16) units of 16 slots; every batch ends with a partial step
-    steps2 = (records // 16 + min(steps * digits1, records)) // (STEP // 16) + batches
+    # a run of c records takes ceil(c / unit) units; every batch ends with a partial step
+    unit = 8 if digits1 >= 256 else 16
+    steps2 = (records // unit + min(steps * digits1, records)) // (STEP // unit) + batches
     parts = [8 * steps * STEP, 4 * digits1 * up(steps, 16), 4 * steps2 * STEP, 2 * steps2 * STEP,
              4 * digits2 * up(steps2, 16), 4 * items, 4 * (items + 1)]
     return sum(up(p, 256) for p in parts)

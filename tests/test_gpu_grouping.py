@@ -162,3 +162,33 @@ def test_partitioned_add_at_step_edges(chunks, kind):
             assert np.array_equal(f.words().cpu().numpy(), ref.bytes), f"{n} keys"
     finally:
         f.close()
+
+
+@pytest.mark.parametrize("kind", ["uniform", "repeated"])
+@pytest.mark.parametrize("gib", [4, 9, 17])
+def test_partitioned_add_into_large_filters(gib, kind):
+    """256 first digits and more: the second pass in units of 8 slots, with
+    256, 512 and 1,024 second digits.  The words equal those of direct adds,
+    which the oracle pins elsewhere; sampled blocks against the oracle."""
+    bf = _bf()
+    nb, n = (gib << 30) // 32 - 1001, (1 << 22) + 77
+    keys = _keys(n, kind, gib)
+    if kind == "repeated":  # direct adds of one key one after another are slow
+        keys[keys == 77] = np.arange(int((keys == 77).sum()), dtype=np.uint64) % 4096
+        keys[keys == 2**63] = np.arange(int((keys == 2**63).sum()), dtype=np.uint64) % 512
+    log(f"partitioned add, {kind} keys: {gib} GiB, {n} keys")
+    d = to_device(keys)
+    f, g = bf.BloomFilter(nb, 8, 32, 8, 5), bf.BloomFilter(nb, 8, 32, 8, 5)
+    try:
+        f.set_mapping(bf.BF_OP_ADD, strategy=bf.BF_STRATEGY_PARTITIONED)
+        g.set_mapping(bf.BF_OP_ADD, strategy=bf.BF_STRATEGY_DIRECT)
+        f.add(d)
+        g.add(d)
+        words = f.words()
+        assert torch.equal(words.view(torch.int64), g.words().view(torch.int64))
+        sel = workloads.rng(gib).choice(nb, size=256, replace=False).astype(np.uint64)
+        got = words.view(nb, 32)[torch.from_numpy(sel.astype(np.int64)).to("cuda")].cpu().numpy()
+        assert np.array_equal(got, oracle.block_words(nb, 8, 32, 8, 5, keys, sel))
+    finally:
+        f.close()
+        g.close()
