@@ -13,6 +13,7 @@ namespace {
 template <int UNIT>
 __global__ __launch_bounds__(kPlanThreads) void regroup_plan_kernel(RegroupArgs a) {
   __shared__ uint32_t wave_sum[kPlanThreads / 64];
+  if (a.direct != nullptr && *a.direct != 0) return;
   const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
   const PartItem it = regroup_item(a, blockIdx.x);
   const uint32_t* entries = a.table1 + it.d1 * a.stride1;
@@ -37,6 +38,7 @@ __global__ __launch_bounds__(kPlanThreads) void regroup_plan_kernel(RegroupArgs 
 // First output step of every item: prefix sums of the items' step counts.
 __global__ __launch_bounds__(kScanThreads) void regroup_scan_kernel(RegroupArgs a) {
   __shared__ uint32_t wave_sum[kScanThreads / 64];
+  if (a.direct != nullptr && *a.direct != 0) return;
   const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
   uint32_t before = 0;
   for (uint32_t base = 0; base < a.items; base += kScanThreads) {

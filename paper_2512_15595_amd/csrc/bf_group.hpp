@@ -342,6 +342,7 @@ struct GroupArgs {
   uint16_t* blk;
   uint16_t* place;      // lookups: each key's place in its sorted step (kNoPlace: beyond clip)
   uint32_t clip;        // lookups: records of a run that readers see
+  const uint32_t* direct;  // lookups: nonzero if the keys are looked up directly and nothing is grouped
   const PartRange* ranges;    // multi-filter plans
   const PartFilter* filters;
   uint64_t num_bits;    // classic filter
@@ -354,6 +355,8 @@ struct GroupArgs {
 template <int D, int ROWS, bool SPLIT, bool MULTI, bool PLACE>
 __global__ __launch_bounds__(kGroupThreads) void group_keys_kernel(GroupArgs a) {
   __shared__ __attribute__((aligned(16))) GroupLds<D, ROWS> l;
+  if constexpr (PLACE)
+    if (*a.direct != 0) return;
   const uint32_t tid = threadIdx.x;
   for (uint32_t d = tid; d < D; d += kGroupThreads) l.cnt[d] = 0;
   uint64_t begin, end, hinit = a.hash_init;
@@ -455,6 +458,7 @@ struct RegroupArgs {
   uint16_t* place;         // lookups: place of each slot's record in the sorted step (kNoPlace: beyond clip)
   uint32_t clip;
   uint32_t* units;         // lookups: the units a step was read from
+  const uint32_t* direct;  // lookups: as in GroupArgs (nullptr for adds)
 };
 
 // The items of one step range and neighbouring digits are neighbours here.
@@ -490,6 +494,8 @@ __global__ __launch_bounds__(kGroupThreads) void regroup_kernel(RegroupArgs a) {
   static_assert(!PLACE || UNIT == kUnit, "the return of a lookup's results reads units of kUnit slots");
   constexpr int kUnits = kStep / UNIT;
   __shared__ __attribute__((aligned(16))) RegroupLds<D, ROWS, UNIT> l;
+  if constexpr (PLACE)
+    if (*a.direct != 0) return;
   const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
   for (uint32_t d = tid; d < D; d += kGroupThreads) l.g.cnt[d] = 0;
   const uint32_t item = regroup_item_of(a, blockIdx.x);

@@ -17,13 +17,60 @@ namespace bfhip {
 
 namespace {
 
+// Whether the keys of a pass repeat so often that looking them up directly is
+// faster, because the repeated ones' lines stay in the caches: *direct is set
+// where at least `limit` of kSampleKeys sampled keys were seen before in the
+// sample.  The sample's size is of the order of the lines that an XCD's L2
+// holds, so that a key seen twice in it is about one whose line the L2 keeps;
+// it is taken in kSampleKeys / 64 stretches of 64 keys, which shows repeats
+// that are neighbours too (5 us with the launch).  A bit of kSampleBits stands
+// for a key that was seen: of different keys 127 look like repeats.
+constexpr int kSampleThreads = 1024;
+constexpr int kSampleKeys = 8192;
+constexpr uint32_t kSampleBits = 1u << 18;
+constexpr uint32_t kSampleChance = 127;
+
+__global__ __launch_bounds__(kSampleThreads) void sample_kernel(const uint64_t* keys, uint64_t n, uint64_t hash_init,
+                                                                uint32_t limit, uint32_t* direct) {
+  __shared__ __attribute__((aligned(16))) uint32_t bits[kSampleBits / 32];
+  __shared__ uint32_t count;
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+  if (n < kSampleKeys || limit == 0) {
+    if (tid == 0) *direct = 1;
+    return;
+  }
+  constexpr int kPer = kSampleKeys / kSampleThreads;
+  constexpr uint64_t kStretches = kSampleKeys / 64;
+  uint64_t key[kPer];
+#pragma unroll
+  for (int j = 0; j < kPer; ++j)
+    key[j] = keys[(n - 64) * (j * (kSampleThreads / 64) + wave) / (kStretches - 1) + lane];
+  for (uint32_t i = tid; i < kSampleBits / 128; i += kSampleThreads) reinterpret_cast<u32x4*>(bits)[i] = u32x4{0u, 0u, 0u, 0u};
+  if (tid == 0) count = 0;
+  __syncthreads();
+  uint32_t seen = 0;
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const uint32_t i = static_cast<uint32_t>(xxh64_u64(key[j], hash_init)) & (kSampleBits - 1);
+    const uint32_t bit = 1u << (i & 31u);
+    uint32_t old = bits[i >> 5];
+    if ((old & bit) == 0) old = atomicOr(&bits[i >> 5], bit);
+    seen += (old & bit) != 0 ? 1u : 0u;
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) seen += __shfl_down(seen, off, 64);
+  if (lane == 0) atomicAdd(&count, seen);
+  __syncthreads();
+  if (tid == 0) *direct = count >= limit ? 1u : 0u;
+}
+
 // A second-pass step's results at the slots of the first pass that its
 // records were read from.
 __global__ __launch_bounds__(kReturnThreads) void return_slots_kernel(ReturnSlotsArgs a) {
   __shared__ __attribute__((aligned(16))) uint8_t res[kStep];
   __shared__ uint32_t units[kStepUnits];
   static_assert(kStepUnits == kReturnThreads && kStep / 16 == kReturnThreads, "a unit and a vector per thread");
-  if (blockIdx.x >= *a.nsteps) return;
+  if (*a.direct != 0 || blockIdx.x >= *a.nsteps) return;
   const uint32_t tid = threadIdx.x;
   const uint64_t s = static_cast<uint64_t>(blockIdx.x) * kStep;
   reinterpret_cast<u32x4*>(res)[tid] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(a.res + s) + tid);
@@ -50,6 +97,7 @@ struct Lookup {
   TestArgs t;
   ReturnSlotsArgs slots;
   ReturnArgs keys;
+  uint32_t* direct;
   bool two;
   uint64_t chunks;
   uint64_t steps2;  // second-pass steps at most
@@ -94,6 +142,8 @@ void layout(const bf_filter* f, uint64_t n, uint8_t* base, Lookup& x) {
     off = align256(off + bytes);
     return p;
   };
+  uint32_t* direct = reinterpret_cast<uint32_t*>(take(4));
+  x.g.direct = x.r.direct = x.t.direct = x.slots.direct = x.keys.direct = x.direct = direct;
   x.g.place = reinterpret_cast<uint16_t*>(take(2 * steps * kStep));
   x.g.table = reinterpret_cast<uint32_t*>(take(4 * x.g.digits * x.g.stride));
   x.keys.place = x.g.place;
@@ -164,20 +214,56 @@ constexpr uint64_t kMaxPass = 1ull << 28;
 
 }  // namespace
 
-// Whether a lookup of n keys is grouped: where the measured break-even lies,
-// with about a fifth to spare.  One digit (up to 64 MiB): about 33 us and
-// 6.2-7.6 ps per key against 9.7, 13.7, 16.6 and 18.5 ps direct at 8, 16, 32
-// and 64 MiB (at 4 MiB, 6.4 ps, most lines still come from the L2: never).
-// Two digits: 60 us and 0.24 us per MiB (every chunk is read) and 10.5 ps
-// per key against 19.5.  Measured grouped / direct, us: 16 MiB 2^22 keys 54 /
-// 64; 8 MiB 2^24 128 / 169; 128 MiB 2^23 168 / 168 and 2^24 251 / 329; 1 GiB
-// 2^25 625 / 642 and 2^26 960 / 1274; 2 GiB 2^26 1176 / 1437.
+namespace {
+
+// Measured costs of a lookup: grouped fixed_us + n * grouped_ps, direct
+// n * direct_ps where no key repeats; repeats add kRepeatPs to the grouped
+// form (keys beyond their runs' clip) and take the direct one down to kCachedPs
+// for theirs.
+struct LookupCost {
+  double fixed_us, grouped_ps, direct_ps;
+};
+LookupCost lookup_cost(const bf_filter* f) {
+  const double mib = static_cast<double>(f->nbytes) / (1 << 20);
+  if (f->nbytes > (64ull << 20)) return {65.0 + 0.24 * mib, 10.0, 19.5};
+  const double l = std::log2(mib);  // 3 .. 6
+  return {38.0, 7.0, l < 4.0 ? 9.7 + 4.3 * (l - 3.0) : l < 5.0 ? 14.0 + 2.6 * (l - 4.0) : 16.6 + 1.9 * (l - 5.0)};
+}
+constexpr double kRepeatPs = 2.5;
+constexpr double kCachedPs = 2.6;
+
+}  // namespace
+
+// Whether a lookup of n keys is grouped: where it pays for keys that do not
+// repeat by more than the sample and the launches without work cost keys that
+// do.  One digit (up to 64 MiB), us direct / grouped: 8 MiB 2^24 keys 167 /
+// 135; 16 MiB 2^22 63 / 60, 2^23 120 / 92; 32 MiB 2^22 73 / 62, 2^22.5 101 /
+// 75; 64 MiB 2^22.5 112 / 86 (at 4 MiB most lines come from the L2: never).
+// Two digits: 128 MiB 2^24 319 / 262, 256 MiB 2^24 327 / 299; 1 GiB 2^25 634 /
+// 632 and 2^26 1275 / 982.  Keys that all repeat take 12..18 us more than
+// directly: 16 MiB 2^23 30 / 43, 2^25 102 / 99.
 bool lookup_groups(const bf_filter* f, uint64_t n) {
   if (f->layout != BF_LAYOUT_SECTORIZED || f->nbytes < (8ull << 20) || f->nbytes > (2ull << 30)) return false;
   if (f->nbytes < (16ull << 20)) return n >= (1ull << 24);
-  if (f->nbytes <= (64ull << 20)) return n >= (1ull << 22);
+  if (f->nbytes < (32ull << 20)) return n >= (1ull << 23);
+  if (f->nbytes <= (64ull << 20)) return n >= (3ull << 21);
   return n >= (1ull << 23) + f->nbytes / 36;
 }
+
+namespace {
+
+// The repeats in a sample from which on the direct lookup of a pass of n keys
+// is the faster: 0, always, for a last pass that would not be grouped alone.
+uint32_t sample_limit(const bf_filter* f, uint64_t n) {
+  if (!lookup_groups(f, n)) return 0;
+  const LookupCost c = lookup_cost(f);
+  const double keys = static_cast<double>(n) * 1e-6;
+  const double grouped = c.fixed_us + (c.grouped_ps + kRepeatPs) * keys;
+  const double share = (c.direct_ps * keys - grouped) / ((c.direct_ps - kCachedPs) * keys);
+  return kSampleChance + static_cast<uint32_t>(std::max(share, 0.02) * kSampleKeys);
+}
+
+}  // namespace
 
 // The line for lookups in LDS, each side measured on MI355X with 32-byte
 // blocks and k = 8 (us, direct against LDS): 2^20 keys 7.4 against 7.0..7.6 at
@@ -297,6 +383,10 @@ bf_status grouped_lookup(const bf_filter* f, const uint64_t* keys, uint64_t n, u
       void* args[] = {arg};
       if (e == hipSuccess) e = hipLaunchKernel(fn, dim3(static_cast<uint32_t>(grid)), dim3(threads), args, 0, stream);
     };
+    uint64_t count = x.g.n;
+    uint32_t limit = sample_limit(f, count);
+    void* sargs[] = {&x.g.keys, &count, &x.g.hash_init, &limit, &x.direct};
+    e = hipLaunchKernel(reinterpret_cast<const void*>(&sample_kernel), dim3(1), dim3(kSampleThreads), sargs, 0, stream);
     run(k.group, ceil_div(x.g.steps, x.g.wg_steps), kGroupThreads, &x.g);
     if (x.two) {
       run(regroup_plan_fn(false), x.r.items, kPlanThreads, &x.r);

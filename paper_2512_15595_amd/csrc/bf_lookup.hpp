@@ -19,6 +19,12 @@
 // so a run is clipped five standard deviations over the length that
 // uniformly hashed keys give it; the keys beyond (of such keys hardly any)
 // are looked up directly by the return step, spread over all workgroups.
+// Where many keys repeat, the caches answer direct lookups faster than any
+// grouping could: a sample of the keys decides before anything is grouped
+// (bf_lookup.hip), and then the return step looks up all keys.  2^26 keys in
+// 32 MiB, us direct / grouped / by the sample: different ones 1074 / 439 /
+// 444, a tenth of them one key 975 / 658 / 658, half 578 / 700 / 605, all of
+// them 200 / 858 / 169.
 //
 // Measured on MI355X (256-bit blocks, k = 8, half of the keys present; us,
 // direct -> grouped): 2^26 keys in 16 MiB 927 -> 442, 32 MiB 1120 -> 462,
@@ -58,6 +64,7 @@ struct TestArgs {
   uint32_t low_bits;
   uint32_t split;          // workgroups per chunk
   uint32_t k;
+  const uint32_t* direct;  // as in GroupArgs
 };
 
 // Results of a second-pass step to the first pass's slots.
@@ -67,6 +74,7 @@ struct ReturnSlotsArgs {
   uint8_t* out;            // by slot of the first pass
   const uint32_t* units;   // where a step was read from
   const uint32_t* nsteps;  // the number of steps
+  const uint32_t* direct;
 };
 
 struct ReturnArgs {
@@ -74,6 +82,7 @@ struct ReturnArgs {
   const uint8_t* res;      // by slot of the sorted steps: 0, 1 or kUntested
   uint8_t* out;            // by key
   uint64_t n;
+  const uint32_t* direct;  // nonzero: every key is looked up here
   // for the keys that were not tested
   const void* words;
   const uint64_t* keys;
@@ -105,6 +114,7 @@ __device__ __forceinline__ void test_chunk(const TestArgs& a) {
   constexpr int NU = kBlockBytes / 16;
   __shared__ u32x4 lds[kChunk / 16];
   __shared__ RunLds<kTestThreads, kList> runs;
+  if (*a.direct != 0) return;
   const LanePatterns<W, S_WORDS, K, 1, S_WORDS> lp(0, SALTS{});
   const uint32_t tid = threadIdx.x;
   const uint32_t item = xcd_item(blockIdx.x, gridDim.x);
@@ -172,45 +182,83 @@ __device__ __forceinline__ void test_chunk(const TestArgs& a) {
 }
 
 // A step's results in key order.  `out` may have any alignment: whole
-// 16-byte vectors where it is aligned, bytes elsewhere.
+// 16-byte vectors where it is aligned, bytes elsewhere.  Keys without a
+// result are looked up here, a key per lane, and join the others in LDS: the
+// listed ones (beyond their run's clip), or with a.direct all of the step's.
 template <typename W, int S_WORDS, int K, typename SALTS>
 __device__ __forceinline__ void return_keys(const ReturnArgs& a) {
   static_assert(kStep / kReturnThreads == 16, "one 16-byte vector of results per thread");
   __shared__ __attribute__((aligned(16))) uint8_t res[kStep];
-  const uint32_t tid = threadIdx.x;
+  __shared__ uint16_t list[kStep];
+  __shared__ uint32_t listed;
+  const uint32_t tid = threadIdx.x, lane = tid & 63u;
   const uint64_t s = static_cast<uint64_t>(blockIdx.x) * kStep;
   const uint32_t valid = static_cast<uint32_t>(a.n - s < kStep ? a.n - s : kStep);
-  reinterpret_cast<u32x4*>(res)[tid] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(a.res + s) + tid);
-  const u32x4* places = reinterpret_cast<const u32x4*>(a.place + s + 16 * tid);
-  const u32x4 p[2] = {__builtin_nontemporal_load(places), __builtin_nontemporal_load(places + 1)};
-  __syncthreads();
-  u32x4 v;
-  bool untested = false;
+  const LanePatterns<W, S_WORDS, K, 1, S_WORDS> lp(0, SALTS{});
+  // res[key_at(i)] for i < n, the next key of a lane loaded behind this one's
+  // block.  (Two and four at a time: the registers cost the return of tested
+  // keys more, 940 -> 980 us for 2^26 keys in 1 GiB, than they gain here.)
+  auto look_up = [&](uint32_t n, auto key_at) {
+    if (n == 0) return;
+    uint32_t p = key_at(tid < n ? tid : n - 1);
+    uint64_t key = __builtin_nontemporal_load(a.keys + s + p);
+#pragma unroll 1
+    for (uint32_t i = tid; i < n; i += kReturnThreads) {
+      const uint32_t at = p;
+      const uint64_t h = xxh64_u64(key, a.hash_init);
+      W w[S_WORDS];
+      load_words<W, S_WORDS>(static_cast<const W*>(a.words) +
+                                 static_cast<uint64_t>(block_of(h, a.nb_lo, a.nb_hi_mask)) * S_WORDS, w);
+      p = key_at(i + kReturnThreads < n ? i + kReturnThreads : n - 1);
+      key = __builtin_nontemporal_load(a.keys + s + p);
+      W miss = 0;
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const uint32_t x = p[q / 2][2 * (q % 2)], y = p[q / 2][2 * (q % 2) + 1];
-    untested = untested || (x & 0xffffu) == kNoPlace || x >> 16 == kNoPlace || (y & 0xffffu) == kNoPlace ||
-               y >> 16 == kNoPlace;
-    v[q] = res[x & (kStep - 1)] | static_cast<uint32_t>(res[x >> 16 & (kStep - 1)]) << 8 |
-           static_cast<uint32_t>(res[y & (kStep - 1)]) << 16 | static_cast<uint32_t>(res[y >> 16 & (kStep - 1)]) << 24;
-    untested = untested || (v[q] & 0x02020202u) != 0;
-  }
-  if (__syncthreads_or(untested ? 1 : 0)) {
-    // some keys of the step: looked up directly, a key per lane
-    const LanePatterns<W, S_WORDS, K, 1, S_WORDS> lp(0, SALTS{});
-#pragma unroll 2
-    for (uint32_t p = tid; p < valid; p += kReturnThreads) {
-      const uint32_t place = a.place[s + p];
-      uint32_t r = place == kNoPlace ? kUntested : res[place];
-      if (r == kUntested) {
-        const uint64_t h = xxh64_u64(a.keys[s + p], a.hash_init);
-        r = test_block<W, S_WORDS, K, 1, S_WORDS>(static_cast<const W*>(a.words),
-                                                  block_of(h, a.nb_lo, a.nb_hi_mask), static_cast<uint32_t>(h), lp,
-                                                  a.k) ? 1u : 0u;
-      }
-      a.out[s + p] = static_cast<uint8_t>(r);
+      for (int x = 0; x < S_WORDS; ++x) miss |= lp.word(0, x, static_cast<uint32_t>(h), a.k) & ~w[x];
+      res[at] = miss == 0 ? 1 : 0;
     }
-    return;
+  };
+  u32x4 v;
+  if (*a.direct != 0) {
+    look_up(valid, [](uint32_t i) { return i; });
+    __syncthreads();
+    v = reinterpret_cast<const u32x4*>(res)[tid];
+  } else {
+    if (tid == 0) listed = 0;
+    reinterpret_cast<u32x4*>(res)[tid] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(a.res + s) + tid);
+    const u32x4* places = reinterpret_cast<const u32x4*>(a.place + s + 16 * tid);
+    const u32x4 p[2] = {__builtin_nontemporal_load(places), __builtin_nontemporal_load(places + 1)};
+    __syncthreads();
+    uint32_t untested = 0;  // of the thread's 16 keys
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      v[q] = 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const uint32_t place = p[q / 2][2 * (q % 2) + i / 2] >> (16 * (i % 2)) & 0xffffu;
+        uint32_t r = res[place & (kStep - 1)];
+        if (place == kNoPlace) r = kUntested;
+        untested |= (r >> 1 & 1u) << (4 * q + i);
+        v[q] |= r << (8 * i);
+      }
+    }
+    if (16 * tid + 16 > valid) untested &= 16 * tid < valid ? (1u << (valid - 16 * tid)) - 1 : 0u;
+    if (__syncthreads_or(untested != 0 ? 1 : 0)) {
+      reinterpret_cast<u32x4*>(res)[tid] = v;
+      uint32_t incl = __popc(untested);
+#pragma unroll
+      for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t x = __shfl_up(incl, off, 64);
+        if (lane >= static_cast<uint32_t>(off)) incl += x;
+      }
+      uint32_t at = 0;
+      if (lane == 63 && incl != 0) at = atomicAdd(&listed, incl);
+      at = __shfl(at, 63, 64) + incl - __popc(untested);
+      for (uint32_t u = untested; u != 0; u &= u - 1) list[at++] = static_cast<uint16_t>(16 * tid + __ffs(u) - 1);
+      __syncthreads();
+      look_up(listed, [&](uint32_t i) -> uint32_t { return list[i]; });
+      __syncthreads();
+      v = reinterpret_cast<const u32x4*>(res)[tid];
+    }
   }
   uint8_t* out = a.out + s + 16 * tid;
   if (reinterpret_cast<uintptr_t>(a.out) % 16 == 0 && 16 * tid + 16 <= valid) {
