@@ -456,7 +456,7 @@ struct RegroupArgs {
   uint32_t* table2;
   uint64_t stride2;
   uint16_t* place;         // lookups: place of each slot's record in the sorted step (kNoPlace: beyond clip)
-  uint32_t clip;
+  uint32_t clip, clip_last;  // (its last first digit may have fewer second digits, so longer runs)
   uint32_t* units;         // lookups: the units a step was read from
   const uint32_t* direct;  // lookups: as in GroupArgs (nullptr for adds)
 };
@@ -502,6 +502,8 @@ __global__ __launch_bounds__(kGroupThreads) void regroup_kernel(RegroupArgs a) {
   const PartItem it = regroup_item(a, item);
   const uint32_t first = a.slot0[item];
   uint32_t row = 0;  // steps written
+  uint32_t clip = kNoClip;
+  if constexpr (PLACE) clip = it.d1 + 1 == a.items / a.per_digit ? a.clip_last : a.clip;
   const uint32_t mask = a.digits - 1, local_mask = (1u << a.shift) - 1;
   const uint32_t* entries = a.table1 + it.d1 * a.stride1;
   for (uint32_t base = it.t0; base < it.t1; base += kRegroupRuns) {
@@ -562,7 +564,7 @@ __global__ __launch_bounds__(kGroupThreads) void regroup_kernel(RegroupArgs a) {
         dg[j] = static_cast<uint32_t>(r[j] >> 32) >> a.shift & mask;
       }
       auto in = [&](int j) { return (ok >> j & 1u) != 0; };
-      group_positions(l.g, dg, in, row % ROWS, PLACE ? a.clip : kNoClip, rank, [&] { if (w + 1 < windows) find(w + 1); },
+      group_positions(l.g, dg, in, row % ROWS, clip, rank, [&] { if (w + 1 < windows) find(w + 1); },
                       [&] { if (w + 1 < windows) load(w + 1); });
       const uint64_t step = first + row;
 #pragma unroll
@@ -570,7 +572,7 @@ __global__ __launch_bounds__(kGroupThreads) void regroup_kernel(RegroupArgs a) {
         const uint32_t pos = l.g.start[dg[j]] + rank[j];
         if (in(j)) l.g.stage[pos] = r[j];
         if constexpr (PLACE)
-          a.place[step * kStep + tid + j * kGroupThreads] = static_cast<uint16_t>(rank[j] < a.clip ? pos : kNoPlace);
+          a.place[step * kStep + tid + j * kGroupThreads] = static_cast<uint16_t>(rank[j] < clip ? pos : kNoPlace);
       }
       if constexpr (PLACE) {
         if (tid < kUnits) {

@@ -113,9 +113,10 @@ uint32_t chunk_shift(const bf_filter* f, bool two) {
 }
 
 // Records of a run that its reader sees: five standard deviations over the
-// mean of uniformly hashed keys.
-uint32_t run_clip(uint32_t digits) {
-  const double mean = static_cast<double>(kStep) / digits;
+// mean of uniformly hashed keys, of which a digit of `blocks` blocks among
+// `of` gets its share of a step.
+uint32_t run_clip(uint64_t blocks, uint64_t of) {
+  const double mean = static_cast<double>(kStep) * static_cast<double>(blocks) / static_cast<double>(of);
   return static_cast<uint32_t>(mean + 5.0 * std::sqrt(mean) + 8.0);
 }
 
@@ -135,7 +136,8 @@ void layout(const bf_filter* f, uint64_t n, uint8_t* base, Lookup& x) {
   x.g.local_mask = (1u << shift) - 1;
   x.g.digits = static_cast<uint32_t>(ceil_div(x.chunks, 1ull << low));
   x.g.stride = ceil_div(steps, 16) * 16;
-  x.g.clip = run_clip(x.g.digits);
+  const uint64_t digit = 1ull << x.g.shift;  // blocks of a first digit (the last one has the rest)
+  x.g.clip = run_clip(std::min(digit, f->num_blocks), f->num_blocks);
   uint64_t off = 0;
   auto take = [&off, base](uint64_t bytes) {
     uint8_t* p = base + off;
@@ -152,7 +154,9 @@ void layout(const bf_filter* f, uint64_t n, uint8_t* base, Lookup& x) {
   if (x.two) {
     x.r.shift = shift;
     x.r.digits = 1u << low;
-    x.r.clip = run_clip(x.r.digits);
+    const uint64_t last = f->num_blocks - (x.g.digits - 1) * digit;
+    x.r.clip = run_clip(1, x.r.digits);
+    x.r.clip_last = run_clip(std::min<uint64_t>(1ull << shift, last), last);
     const uint64_t per_bucket = ceil_div(n, x.g.digits);
     x.r.per_digit = static_cast<uint32_t>(std::max<uint64_t>(
         std::max(ceil_div(per_bucket, 65536), std::min<uint64_t>(ceil_div(512, x.g.digits), per_bucket / kStep)), 1));

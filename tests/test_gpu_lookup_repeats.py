@@ -156,3 +156,19 @@ def test_grouped_lookups_on_two_streams():
     finally:
         fa.close()
         fb.close()
+
+
+@pytest.mark.parametrize("nbytes", [64 * MIB + 64 * 1024, 66 * MIB, 130 * MIB])
+def test_lookups_with_a_partial_last_high_digit(nbytes):
+    """1 chunk of 64 in the last high digit, and halves: its runs are longer
+    than those of the other digits and are clipped by a length of their own."""
+    n = 13_000_003
+    assert call_plan(nbytes, CONTAINS, n).route == GROUPED
+    keys = _repeated(n, 0.0, 1, nbytes)
+    log(f"partial last high digit: {nbytes} bytes, {n} keys")
+    f, words, nb = _filter(nbytes)
+    try:
+        got = f.contains(to_device(keys)).cpu().numpy()
+        assert np.array_equal(got, oracle_par.contains(words, nb, 8, 32, 8, 5, keys))
+    finally:
+        f.close()
