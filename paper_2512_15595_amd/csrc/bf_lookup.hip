@@ -227,11 +227,42 @@ namespace {
 struct LookupCost {
   double fixed_us, grouped_ps, direct_ps;
 };
+// Blocks of 64 and 128 bytes and many bits per key cost the test more, a k that
+// is not compiled in costs both forms more (measured with 2^22.7..2^28 keys:
+// 8 x 32 bits with k = 8 and 9, 1 x 32, 1 x 64, 4 x 64, 8 x 64 and 16 x 64; two
+// digits, 512 MiB, 2^26 keys, us direct / grouped: k = 8 1290 / 830, k = 9 1254
+// / 1059, 16 x 64 1239 / 1023).
 LookupCost lookup_cost(const bf_filter* f) {
   const double mib = static_cast<double>(f->nbytes) / (1 << 20);
-  if (f->nbytes > (64ull << 20)) return {65.0 + 0.24 * mib, 10.0, 19.5};
+  const uint64_t block = static_cast<uint64_t>(f->s) * f->word_bits / 8;
+  const bool generic = k_index(f->k) == 0, wide = block > 64, mid = block > 32 || f->k >= 16;
+  if (f->nbytes > (64ull << 20)) {
+    const double beyond = std::max(mib / 1024.0 - 1.0, 0.0);  // GiB
+    LookupCost c{65.0 + 0.24 * mib, 9.8 + 0.8 * beyond, 18.8 + 1.9 * beyond};
+    if (generic) {
+      c.fixed_us += 0.05 * mib;
+      c.grouped_ps += 3.4;
+      if (mib > 768.0) c.direct_ps += 1.7;
+    } else if (wide) {
+      c.fixed_us += 0.13 * mib;
+      c.grouped_ps += 2.8;
+    } else if (mid) {
+      c.grouped_ps += 1.0;
+    }
+    return c;
+  }
   const double l = std::log2(mib);  // 3 .. 6
-  return {38.0, 7.0, l < 4.0 ? 9.7 + 4.3 * (l - 3.0) : l < 5.0 ? 14.0 + 2.6 * (l - 4.0) : 16.6 + 1.9 * (l - 5.0)};
+  const bool more = l >= 4.0;       // 128 chunks and more: short runs
+  LookupCost c{38.0, 7.0, l < 4.0 ? 9.7 + 4.3 * (l - 3.0) : l < 5.0 ? 14.0 + 2.6 * (l - 4.0) : 16.6 + 1.9 * (l - 5.0)};
+  if (generic) {
+    c.grouped_ps += more ? 5.0 : 1.5;
+    c.direct_ps = std::max(c.direct_ps, wide ? 21.0 : block > 32 ? 12.9 : 10.5);
+  } else if (wide) {
+    c.grouped_ps += more ? 3.5 : 0.7;
+  } else if (mid) {
+    c.grouped_ps += more ? 2.0 : 0.5;
+  }
+  return c;
 }
 constexpr double kRepeatPs = 2.5;
 constexpr double kCachedPs = 2.6;
@@ -248,10 +279,15 @@ constexpr double kCachedPs = 2.6;
 // directly: 16 MiB 2^23 30 / 43, 2^25 102 / 99.
 bool lookup_groups(const bf_filter* f, uint64_t n) {
   if (f->layout != BF_LAYOUT_SECTORIZED || f->nbytes < (8ull << 20) || f->nbytes > (2ull << 30)) return false;
-  if (f->nbytes < (16ull << 20)) return n >= (1ull << 24);
-  if (f->nbytes < (32ull << 20)) return n >= (1ull << 23);
-  if (f->nbytes <= (64ull << 20)) return n >= (3ull << 21);
-  return n >= (1ull << 23) + f->nbytes / 36;
+  const uint64_t least = f->nbytes < (16ull << 20)    ? 1ull << 24
+                         : f->nbytes < (32ull << 20)  ? 1ull << 23
+                         : f->nbytes <= (64ull << 20) ? 3ull << 21
+                                                      : (1ull << 23) + f->nbytes / 36;
+  if (n < least) return false;
+  // ... and where the costs of the layout give the grouped form a twentieth
+  const LookupCost c = lookup_cost(f);
+  const double keys = static_cast<double>(n) * 1e-6;
+  return c.direct_ps * keys > 1.05 * (c.fixed_us + c.grouped_ps * keys);
 }
 
 namespace {
@@ -276,9 +312,10 @@ uint32_t sample_limit(const bf_filter* f, uint64_t n) {
 // against 13.9, 15.4 against 15.2, 18.3 against 15.2, 19.7 against 16.0; 2^26
 // keys 243 against 207, 222 against 178, 277 against 174, 293 against 205.
 // 4-byte blocks lose 0.3 us at 2^21 keys in 16 KiB, hence the two lines.
+// A k that is not compiled in loses 0.9 us of 18 at 2^21 keys in 160 KiB.
 bool lookup_fits_lds(const bf_filter* f, uint64_t n) {
-  return f->layout == BF_LAYOUT_SECTORIZED && f->nbytes <= kResidentBytes[1] &&
-         n >= (f->nbytes > (16u << 10) ? 1ull << 21 : 1ull << 22);
+  const bool small = f->nbytes <= (16u << 10) || (f->nbytes > kResidentBytes[0] && k_index(f->k) == 0);
+  return f->layout == BF_LAYOUT_SECTORIZED && f->nbytes <= kResidentBytes[1] && n >= (small ? 1ull << 22 : 1ull << 21);
 }
 
 // Adds in LDS: a workgroup merges its image into the filter, which pays from

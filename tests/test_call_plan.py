@@ -126,3 +126,19 @@ def test_noalloc_limits_and_passes():
         else:
             s, bits = rng.choice([(1, 64), (2, 32), (8, 32), (4, 64), (16, 64)])
             noalloc(nbytes, rng.randrange(1, 45_000_000), s=s, bits=bits, k=16)
+
+
+@pytest.mark.parametrize("s,bits,k,nbytes,n,route", [
+    # where the grouped form was measured slower than the direct one, and faster
+    (16, 64, 16, 1030 * MIB, 39_000_000, DIRECT), (16, 64, 16, GIB, 1 << 27, GROUPED),
+    (16, 64, 16, 66 * MIB, 11_000_000, DIRECT), (16, 64, 16, 128 * MIB, 1 << 25, GROUPED),
+    (8, 32, 9, 66 * MIB, 11_000_000, DIRECT), (8, 32, 9, 128 * MIB, 1 << 25, GROUPED),
+    (8, 32, 9, 2000 * MIB, 68_000_000, DIRECT), (8, 32, 9, 2000 * MIB, 1 << 27, GROUPED),
+    (8, 32, 9, 20 * MIB, 9_000_000, DIRECT), (8, 32, 9, 20 * MIB, 1 << 26, GROUPED),
+    (4, 64, 16, 260 * MIB, 15_900_000, DIRECT), (4, 64, 16, GIB, 1 << 26, GROUPED),
+    # a k that is not compiled in, blocks of 64 bytes and more: two digits have no kernel
+    (16, 32, 20, GIB, 1 << 28, DIRECT),
+    (8, 32, 9, 160 * KIB, 1 << 21, DIRECT), (8, 32, 9, 160 * KIB, 1 << 22, LDS), (8, 32, 9, 64 * KIB, 1 << 21, LDS),
+])
+def test_lookup_routes_of_other_layouts(s, bits, k, nbytes, n, route):
+    assert call_plan(nbytes, CONTAINS, n, s=s, bits=bits, k=k).route == route
