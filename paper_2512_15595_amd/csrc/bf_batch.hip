@@ -145,30 +145,41 @@ uint64_t resident_keys_of(const bf_batch* b, bf_filter* const* filters, uint32_t
 }
 
 // Whether the plan is faster with its small filters in LDS.  A lookup plan's
-// tiles of one filter stay on one XCD, which tests about 12 keys per ns; the
-// launches in LDS test 330 and cost 15 us.  So plans whose largest filter
-// does not fit the LDS and bounds them gain nothing (256 filters, 2^24 keys,
-// a fifth of them in one: 254 us from the caches, 282 with LDS), nor do small
-// ones (1,024 filters, 2^21 keys: 33 us, 43); 2^23 keys take 103 us and 99,
-// 2^24 205 and 184.  Add plans gain from 1.5 M such keys on (1,024 filters of
-// Zipf counts: 2^21 keys 133 us without, 141 with; 2^22 keys 296, 202).
+// tiles of one filter stay on one XCD, so its time is that of the fullest XCD:
+// 12 keys per ns in filters beyond 160 KiB, in smaller ones 18, 15 with blocks
+// of 32 bytes and more, 9 with a k that is not compiled in (k = 16: 9.6 and 15.8).  The launches in
+// LDS cost 17 us and test 240 keys per ns over all CUs with k = 8, fewer with
+// more bits per key.  So plans whose largest filter does not fit the LDS and
+// bounds them gain nothing, nor do plans of few keys.  Measured, us from the
+// caches / in LDS: 1,024 filters of 32 KiB and 8,192 keys 71 / 44 (4 x 64 bits,
+// k = 16: 63 / 51; k = 9: 101 / 70), 300 of 16 KiB and 30,000 keys 67 / 52,
+// 512 of 128 KiB and 8,192 keys 47 / 46 (1 x 32 bits: 40 / 44; 4 x 64: 42 / 50),
+// 64 of Zipf counts, 2^24 keys 288 / 212 (4 x 64: 251 / 270), 1,024 of Zipf counts, 2^22 keys 57 / 58 (1 x 32: 49 / 55), 2^23 109 / 97.
+// Add plans gain from 1.5 M such keys on (1,024 filters of Zipf counts: 2^21
+// keys 133 us without, 141 with; 2^22 keys 296, 202).
 bool resides_pays(const bf_batch* b, bf_filter* const* filters, uint32_t nfilters, const uint64_t* h_offsets) {
   const uint64_t keys = resident_keys_of(b, filters, nfilters, h_offsets);
   if (b->op == BF_OP_ADD) return keys >= 3u << 19;
   if (keys == 0) return false;
-  std::vector<std::pair<uint64_t, bool>> counts(nfilters);
+  const bf_filter* f0 = filters[0];
+  const bool generic = k_index(f0->k) == 0;
+  const double small = generic ? 9.0 : f0->k >= 16 ? 15.8 : f0->s * f0->word_bits >= 256 ? 15.0 : 18.0;
+  const double large = generic ? 9.0 : f0->k >= 16 ? 9.6 : 12.0;
+  const double lds = 240.0 / (generic ? 2.3 : 0.75 + f0->k / 32.0);
+  std::vector<std::pair<double, bool>> costs(nfilters);  // ns on one XCD, and whether in LDS
   for (uint32_t i = 0; i < nfilters; ++i) {
     const uint64_t n = h_offsets[i + 1] - h_offsets[i];
-    counts[i] = {n, resides(b, filters[i], n)};
+    const bool in_lds = resides(b, filters[i], n);
+    costs[i] = {static_cast<double>(n) / (in_lds ? small : large), in_lds};
   }
-  std::sort(counts.begin(), counts.end(), [](const auto& x, const auto& y) { return x.first > y.first; });
-  uint64_t all[kXcds] = {}, rest[kXcds] = {};
-  for (const auto& [n, in_lds] : counts) {
-    *std::min_element(all, all + kXcds) += n;
-    if (!in_lds) *std::min_element(rest, rest + kXcds) += n;
+  std::sort(costs.begin(), costs.end(), [](const auto& x, const auto& y) { return x.first > y.first; });
+  double all[kXcds] = {}, rest[kXcds] = {};
+  for (const auto& [ns, in_lds] : costs) {
+    *std::min_element(all, all + kXcds) += ns;
+    if (!in_lds) *std::min_element(rest, rest + kXcds) += ns;
   }
-  const double caches = *std::max_element(all, all + kXcds) / 12.0;
-  return *std::max_element(rest, rest + kXcds) / 12.0 + keys / 330.0 + 15000.0 < caches;
+  const double caches = *std::max_element(all, all + kXcds);
+  return *std::max_element(rest, rest + kXcds) + static_cast<double>(keys) / lds + 20000.0 < caches;
 }
 
 // A chunk of a partitioned construction is read, updated in LDS and written

@@ -233,3 +233,36 @@ def test_partitioned_plan_over_overlapping_words(mode, forced):
     finally:
         for i in (0, 1, 3):
             filters[i].close()
+
+
+@pytest.mark.parametrize("s,S,k,nbytes,per,count,lds", [
+    (1, 32, 4, 128 * KIB, 8_192, 512, False), (4, 64, 16, 128 * KIB, 8_192, 512, False),
+    (8, 32, 9, 64 * KIB, 2_100, 2000, False), (8, 32, 8, 32 * KIB, 8_192, 1024, True),
+    (4, 64, 16, 32 * KIB, 8_192, 1024, True), (1, 64, 8, 32 * KIB, 8_192, 1024, True)])
+def test_lookup_plans_take_lds_where_it_pays(s, S, k, nbytes, per, count, lds):
+    """The rule follows the layout; the result does not depend on it.  Tiles
+    hold 256 or 512 keys, items at least 4,096."""
+    from paper_2512_15595_amd import bf
+
+    block = s * S // 8
+    total = per * count
+    words = torch.randint(0, 256, (count * nbytes,), dtype=torch.uint8, device="cuda")
+    filters = [bf.BloomFilterView(words[i * nbytes:(i + 1) * nbytes], nbytes // block, s, S, k, i) for i in range(count)]
+    keys = torch.randint(-2**63, 2**63 - 1, (total,), dtype=torch.int64, device="cuda")
+    out = torch.empty(total, dtype=torch.uint8, device="cuda")
+    log(f"lookup plan rule s={s} S={S} k={k}: {count} filters of {nbytes} bytes, {per} keys each")
+    try:
+        plan = bf.BatchPlan(bf.BF_OP_CONTAINS, filters, keys, [i * per for i in range(count + 1)], out)
+        try:
+            tiles = sum(plan.info().tiles_per_class)
+            assert (tiles < total // 2048) == lds, tiles
+            plan.launch()
+            for i in (0, 1, count // 2, count - 1):
+                want = oracle_par.contains(words[i * nbytes:(i + 1) * nbytes].cpu().numpy(), nbytes // block, s, S, k, i,
+                                           keys[i * per:(i + 1) * per].cpu().numpy().view(np.uint64))
+                assert np.array_equal(out[i * per:(i + 1) * per].cpu().numpy(), want)
+        finally:
+            plan.close()
+    finally:
+        for f in filters:
+            f.close()
