@@ -17,14 +17,16 @@
  *
  * An add plan with enough keys on filters that are dense (at least their
  * bytes / 80 keys each: the per-filter form of the BF_STRATEGY_AUTO rule in
- * bf.h) and at least 512 chunks among them is instead planned as one
+ * bf.h; and about 1,600 keys, as a filter's keys take whole steps of 8,192
+ * records and 120 KiB of the plan's memory each) and at least 512 chunks among them is instead planned as one
  * partitioned construction over the dense filters: the filters' blocks are
  * laid end to end in one block space, one radix partition groups their keys
  * by 64 KiB chunk, and each chunk is updated in LDS (five kernels in the
  * graph); the keys of the sparse filters go to the tiled launch, recorded
  * after them, so no sparse filter's words are streamed.  Filter 0's add
  * strategy (bf_set_mapping_ex) can force BF_STRATEGY_DIRECT (tiles only) or
- * BF_STRATEGY_PARTITIONED (every filter partitioned).  A plan may name a
+ * BF_STRATEGY_PARTITIONED (every filter partitioned; BF_ENOMEM where the
+ * automatic plan, without memory for the construction, runs in tiles).  A plan may name a
  * filter more than once and its filters' words may overlap: one of such
  * entries at most is partitioned, the others' keys go to the tiled launch,
  * whose atomic ORs merge.  Launches of a plan

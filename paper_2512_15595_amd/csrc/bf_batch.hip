@@ -202,6 +202,18 @@ void leave_overlaps_direct(bf_filter* const* filters, std::vector<PartFilter>& p
   }
 }
 
+// Whether a dense filter's n keys are worth a step of a plan's construction.
+// A step holds one filter's keys and is stored whole, 42 ns over all CUs and
+// 64 KiB of workspace however few they are, where the direct launch takes
+// d - c ps more per key (the layout's measured costs).  Plans of 20,000 filters,
+// us and MB of the plan, partitioned against direct: 4 KiB and 110 keys each 851
+// and 1,344 against 97 and 2, 32 KiB and 600 keys 1,072 and 1,434 against 546
+// and 2, 1,500 keys 1,176 and 1,550 against 1,137 and 2.
+bool fills_step(const CrossoverRow* r, const bf_filter* f, uint64_t n) {
+  const double gain = r != nullptr ? r->d_ps[size_class_of(f->nbytes)] - r->c_ps : 26.0;
+  return n >= static_cast<uint64_t>(kStep) || static_cast<double>(n) * gain > 42000.0;
+}
+
 // Partitioned construction for an add plan: the filters' blocks are laid
 // end to end in one global block space (each filter starting on a chunk
 // boundary), so one radix partition groups every key of every filter by
@@ -235,7 +247,8 @@ bf_status plan_partitioned(bf_batch* b, bf_filter* const* filters, uint32_t nfil
     pf[i].key_begin = h_offsets[i] - h_offsets[0];
     pf[i].key_end = h_offsets[i + 1] - h_offsets[0];
     const uint64_t ni = pf[i].key_end - pf[i].key_begin;
-    pf[i].direct = !forced && (!dense_enough(xr, f->nbytes, ni, true) || resides(b, f, ni)) ? 1u : 0u;
+    const bool left = !dense_enough(xr, f->nbytes, ni, true) || !fills_step(xr, f, ni) || resides(b, f, ni);
+    pf[i].direct = !forced && left ? 1u : 0u;
     chunks += (f->num_blocks + bpc - 1) / bpc;
   }
   leave_overlaps_direct(filters, pf);
@@ -359,7 +372,7 @@ bf_status plan_partitioned(bf_batch* b, bf_filter* const* filters, uint32_t nfil
   const PartKernels k = part_kernels(f0, a);
   if (!part_runs(a, k)) return BF_OK;
   b->part_scratch = lib_alloc(b->device, total, &b->pooled_scratch);
-  if (b->part_scratch == nullptr) return BF_ENOMEM;
+  if (b->part_scratch == nullptr) return forced ? BF_ENOMEM : BF_OK;  // no memory for it: tiles need little
   uint8_t* base = static_cast<uint8_t*>(b->part_scratch);
   for (const Table& t : tables)
     if (hipMemcpy(base + t.at, t.src, t.bytes, hipMemcpyHostToDevice) != hipSuccess) return BF_EDEVICE;

@@ -266,3 +266,71 @@ def test_lookup_plans_take_lds_where_it_pays(s, S, k, nbytes, per, count, lds):
     finally:
         for f in filters:
             f.close()
+
+
+def _plan_of(shapes, seed):
+    """An add plan over filters (bytes, keys) of 32-byte blocks in one buffer."""
+    from paper_2512_15595_amd import bf
+
+    ends = np.concatenate([[0], np.cumsum([nbytes for nbytes, _ in shapes])])
+    offsets = np.concatenate([[0], np.cumsum([n for _, n in shapes])])
+    words = torch.zeros(int(ends[-1]), dtype=torch.uint8, device="cuda")
+    filters = [bf.BloomFilterView(words[int(ends[i]):int(ends[i + 1])], nbytes // 32, 8, 32, 8, i)
+               for i, (nbytes, _) in enumerate(shapes)]
+    keys = workloads.rng(seed).integers(0, 2**64, size=int(offsets[-1]), dtype=np.uint64)
+    d_keys = to_device(keys)
+    free = torch.cuda.mem_get_info()[0]
+    plan = bf.BatchPlan(bf.BF_OP_ADD, filters, d_keys, offsets)
+    torch.cuda.synchronize()
+    return plan, filters, words, ends, offsets, keys, free - torch.cuda.mem_get_info()[0]
+
+
+def _check_plan(plan, filters, words, ends, offsets, keys, sample):
+    plan.launch()
+    for i in sample:
+        want = oracle_par.filter_words((int(ends[i + 1]) - int(ends[i])) // 32, 8, 32, 8, i, keys[offsets[i]:offsets[i + 1]])
+        assert np.array_equal(words[int(ends[i]):int(ends[i + 1])].cpu().numpy(), want.view(np.uint8)), f"filter {i}"
+
+
+@pytest.mark.parametrize("count,nbytes,per", [(20_000, 4 * KIB, 110), (8_000, 32 * KIB, 600)])
+def test_plans_of_many_filters_with_few_keys(count, nbytes, per):
+    """A step of the construction holds one filter's keys and is stored whole:
+    such plans go to tiles, which take a few bytes per key."""
+    from paper_2512_15595_amd import bf
+
+    log(f"add plan of {count} filters of {nbytes} bytes, {per} keys each")
+    plan, *rest, taken = _plan_of([(nbytes, per)] * count, 5)
+    try:
+        assert plan.info().strategy == bf.BF_STRATEGY_DIRECT
+        assert taken < 64 << 20
+        _check_plan(plan, *rest, (0, 1, 77, count - 1))
+    finally:
+        plan.close()
+        for f in rest[0]:
+            f.close()
+
+
+def test_plan_without_memory_for_the_construction_runs_in_tiles():
+    """20,000 filters of 32 KiB and 2,000 keys want 1.6 GB; with less than that
+    left the plan is made all the same."""
+    from paper_2512_15595_amd import bf
+
+    shapes = [(32 * KIB, 2_000)] * 20_000
+    log("add plan with 1.6 GB of construction workspace and 1 GB of memory")
+    plan, filters, words, ends, offsets, keys, _ = _plan_of(shapes, 6)
+    assert plan.info().strategy == bf.BF_STRATEGY_PARTITIONED
+    plan.close()
+    d_keys = to_device(keys)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    hold = torch.empty(torch.cuda.mem_get_info()[0] - (1 << 30), dtype=torch.uint8, device="cuda")
+    try:
+        plan = bf.BatchPlan(bf.BF_OP_ADD, filters, d_keys, offsets)
+        assert plan.info().strategy == bf.BF_STRATEGY_DIRECT
+        _check_plan(plan, filters, words, ends, offsets, keys, (0, 19_999))
+    finally:
+        del hold
+        torch.cuda.empty_cache()
+        plan.close()
+        for f in filters:
+            f.close()
