@@ -4,6 +4,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <functional>
 #include <new>
 #include <mutex>
 #include <numeric>
@@ -214,6 +215,36 @@ bool fills_step(const CrossoverRow* r, const bf_filter* f, uint64_t n) {
   return n >= static_cast<uint64_t>(kStep) || static_cast<double>(n) * gain > 42000.0;
 }
 
+// The costs of a plan's dense filters, in us: those that fit the LDS there and
+// the others (not `direct`) in tiles, whose atomics the device takes at d ps
+// per key and one XCD, which has all tiles of a filter, at 76; or all of them
+// in one construction.  Measured, us: 2,048 filters of 64 KiB with 2^24 keys and
+// one of 16 MiB with 2^22 430 against 364 together, 512 of 128 KiB with 2^23 and
+// four of 4 MiB with 2^22 274 against 194; apart 186 with one of 1 MiB and 2^20,
+// and with 100 of 256 KiB and 2 M (together about 200).
+double lds_and_tiles_us(const CrossoverRow* r, bf_filter* const* filters, const std::vector<PartFilter>& pf,
+                        uint64_t in_lds) {
+  const double generic = k_index(filters[0]->k) == 0 ? 2.0 : 1.0;  // a k that is not compiled in
+  std::vector<uint64_t> counts;
+  double device = 0.0;
+  for (size_t i = 0; i < pf.size(); ++i) {
+    if (pf[i].direct) continue;
+    counts.push_back(pf[i].key_end - pf[i].key_begin);
+    device += static_cast<double>(counts.back()) * (r != nullptr ? r->d_ps[size_class_of(filters[i]->nbytes)] : 37.0);
+  }
+  std::sort(counts.begin(), counts.end(), std::greater<uint64_t>());
+  uint64_t load[kXcds] = {};
+  for (uint64_t c : counts) *std::min_element(load, load + kXcds) += c;
+  const double xcd = static_cast<double>(*std::max_element(load, load + kXcds)) * 76.0;
+  return 25.0 + 5e-6 * static_cast<double>(in_lds) + generic * std::max(device, xcd) * 1e-6;
+}
+
+double construction_us(const CrossoverRow* r, uint64_t n, uint64_t chunks) {
+  const double mib = static_cast<double>(chunks) / 16.0;
+  return r != nullptr ? r->a_us + r->b_us_per_mib * mib + r->c_ps * 1e-6 * static_cast<double>(n)
+                      : 40.0 + 0.43 * mib + 10.8e-6 * static_cast<double>(n);
+}
+
 // Partitioned construction for an add plan: the filters' blocks are laid
 // end to end in one global block space (each filter starting on a chunk
 // boundary), so one radix partition groups every key of every filter by
@@ -229,7 +260,6 @@ bf_status plan_partitioned(bf_batch* b, bf_filter* const* filters, uint32_t nfil
   const uint32_t strategy = f0->mapping[BF_OP_ADD].strategy;
   if (strategy == BF_STRATEGY_DIRECT) return BF_OK;
   const bool forced = strategy == BF_STRATEGY_PARTITIONED;
-  uint64_t n_dense = 0, dense_chunks = 0;
   const uint32_t shift = part_chunk_shift(f0->s, f0->word_bits);
   const uint64_t bpc = 1ull << shift;
   std::vector<PartFilter> pf(nfilters);
@@ -247,19 +277,41 @@ bf_status plan_partitioned(bf_batch* b, bf_filter* const* filters, uint32_t nfil
     pf[i].key_begin = h_offsets[i] - h_offsets[0];
     pf[i].key_end = h_offsets[i + 1] - h_offsets[0];
     const uint64_t ni = pf[i].key_end - pf[i].key_begin;
-    const bool left = !dense_enough(xr, f->nbytes, ni, true) || !fills_step(xr, f, ni) || resides(b, f, ni);
-    pf[i].direct = !forced && left ? 1u : 0u;
     chunks += (f->num_blocks + bpc - 1) / bpc;
-  }
-  leave_overlaps_direct(filters, pf);
-  for (uint32_t i = 0; i < nfilters; ++i) {
-    if (pf[i].direct) continue;
-    n_dense += pf[i].key_end - pf[i].key_begin;
-    dense_chunks += (pf[i].num_blocks + bpc - 1) / bpc;
   }
   const uint64_t n = h_offsets[nfilters] - h_offsets[0];
   if (n == 0 || chunks * bpc > (1ull << 32)) return BF_OK;  // global blocks must fit 32 bits
-  if (strategy == BF_STRATEGY_AUTO && !(dense_chunks >= 512 && n_dense >= (1ull << 21))) return BF_OK;
+  uint64_t n_dense = 0, dense_chunks = 0;
+  auto choose = [&] {  // the filters that take part
+    n_dense = dense_chunks = 0;
+    for (uint32_t i = 0; i < nfilters; ++i) {
+      const bf_filter* f = filters[i];
+      const uint64_t ni = pf[i].key_end - pf[i].key_begin;
+      const bool left = !dense_enough(xr, f->nbytes, ni, true) || !fills_step(xr, f, ni) || resides(b, f, ni);
+      pf[i].direct = !forced && left ? 1u : 0u;
+    }
+    leave_overlaps_direct(filters, pf);
+    for (uint32_t i = 0; i < nfilters; ++i) {
+      if (pf[i].direct) continue;
+      n_dense += pf[i].key_end - pf[i].key_begin;
+      dense_chunks += (pf[i].num_blocks + bpc - 1) / bpc;
+    }
+    return forced || (dense_chunks >= 512 && n_dense >= (1ull << 21));
+  };
+  if (!choose()) {
+    // Too little for a construction is left beside the filters in LDS: it
+    // would go to tiles.  Together they may be enough, and cheaper.
+    const uint64_t in_lds = resident_keys_of(b, filters, nfilters, h_offsets);
+    if (in_lds == 0) return BF_OK;
+    const double apart = lds_and_tiles_us(xr, filters, pf, in_lds);
+    const void* fns[2] = {b->resident[0].fn, b->resident[1].fn};
+    b->resident[0].fn = b->resident[1].fn = nullptr;
+    if (!choose() || construction_us(xr, n_dense, dense_chunks) >= apart) {
+      b->resident[0].fn = fns[0];
+      b->resident[1].fn = fns[1];
+      return BF_OK;
+    }
+  }
   PartArgs a{};
   PartLayout L{};
   if (!part_digits(chunks, shift, kMaxDigits2, a)) return BF_OK;

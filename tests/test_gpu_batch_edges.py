@@ -324,7 +324,15 @@ def test_plan_without_memory_for_the_construction_runs_in_tiles():
     torch.cuda.synchronize()
     torch.cuda.empty_cache()
     hold = torch.empty(torch.cuda.mem_get_info()[0] - (1 << 30), dtype=torch.uint8, device="cuda")
+    fillers = []  # what the library's pool still holds, but for 1 GB
     try:
+        while True:
+            try:
+                fillers.append(bf.BloomFilter((256 << 20) // 32, 8, 32, 8, 0))
+            except bf.BfError:
+                break
+        for f in fillers[-4:]:
+            f.close()
         plan = bf.BatchPlan(bf.BF_OP_ADD, filters, d_keys, offsets)
         assert plan.info().strategy == bf.BF_STRATEGY_DIRECT
         _check_plan(plan, filters, words, ends, offsets, keys, (0, 19_999))
@@ -332,5 +340,25 @@ def test_plan_without_memory_for_the_construction_runs_in_tiles():
         del hold
         torch.cuda.empty_cache()
         plan.close()
-        for f in filters:
+        for f in filters + fillers[:-4]:
+            f.close()
+
+
+@pytest.mark.parametrize("small,large,partitioned", [((64 * KIB, 8_192, 2048), (16 << 20, 1 << 22, 1), True),
+                                                     ((128 * KIB, 16_384, 512), (4 << 20, 1 << 20, 4), True),
+                                                     ((128 * KIB, 16_384, 512), (1 << 20, 1 << 20, 1), False)])
+def test_small_filters_join_the_construction_where_it_pays(small, large, partitioned):
+    """Beside many small filters that fit the LDS, a few large ones are too
+    little for a construction of their own and slow in tiles."""
+    from paper_2512_15595_amd import bf
+
+    shapes = [(small[0], small[1])] * small[2] + [(large[0], large[1])] * large[2]
+    log(f"add plan of {small} and {large} (bytes, keys, filters)")
+    plan, *rest, _ = _plan_of(shapes, 8)
+    try:
+        assert (plan.info().strategy == bf.BF_STRATEGY_PARTITIONED) == partitioned
+        _check_plan(plan, *rest, (0, small[2] - 1, small[2], len(shapes) - 1))
+    finally:
+        plan.close()
+        for f in rest[0]:
             f.close()
