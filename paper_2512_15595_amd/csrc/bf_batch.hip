@@ -203,6 +203,13 @@ void leave_overlaps_direct(bf_filter* const* filters, std::vector<PartFilter>& p
   }
 }
 
+// ps per key of a plan's adds into f in tiles; the rows are measured with a k
+// that is compiled in (1,024 filters of Zipf counts, 2^21 keys: k = 8 140 us,
+// k = 9 787).
+double tile_add_ps(const CrossoverRow* r, const bf_filter* f) {
+  return (r != nullptr ? r->d_ps[size_class_of(f->nbytes)] : 37.0) * (k_index(f->k) == 0 ? 5.6 : 1.0);
+}
+
 // Whether a dense filter's n keys are worth a step of a plan's construction.
 // A step holds one filter's keys and is stored whole, 42 ns over all CUs and
 // 64 KiB of workspace however few they are, where the direct launch takes
@@ -211,7 +218,7 @@ void leave_overlaps_direct(bf_filter* const* filters, std::vector<PartFilter>& p
 // and 1,344 against 97 and 2, 32 KiB and 600 keys 1,072 and 1,434 against 546
 // and 2, 1,500 keys 1,176 and 1,550 against 1,137 and 2.
 bool fills_step(const CrossoverRow* r, const bf_filter* f, uint64_t n) {
-  const double gain = r != nullptr ? r->d_ps[size_class_of(f->nbytes)] - r->c_ps : 26.0;
+  const double gain = tile_add_ps(r, f) - (r != nullptr ? r->c_ps : 10.8);
   return n >= static_cast<uint64_t>(kStep) || static_cast<double>(n) * gain > 42000.0;
 }
 
@@ -224,19 +231,18 @@ bool fills_step(const CrossoverRow* r, const bf_filter* f, uint64_t n) {
 // and with 100 of 256 KiB and 2 M (together about 200).
 double lds_and_tiles_us(const CrossoverRow* r, bf_filter* const* filters, const std::vector<PartFilter>& pf,
                         uint64_t in_lds) {
-  const double generic = k_index(filters[0]->k) == 0 ? 2.0 : 1.0;  // a k that is not compiled in
   std::vector<uint64_t> counts;
   double device = 0.0;
   for (size_t i = 0; i < pf.size(); ++i) {
     if (pf[i].direct) continue;
     counts.push_back(pf[i].key_end - pf[i].key_begin);
-    device += static_cast<double>(counts.back()) * (r != nullptr ? r->d_ps[size_class_of(filters[i]->nbytes)] : 37.0);
+    device += static_cast<double>(counts.back()) * tile_add_ps(r, filters[i]);
   }
   std::sort(counts.begin(), counts.end(), std::greater<uint64_t>());
   uint64_t load[kXcds] = {};
   for (uint64_t c : counts) *std::min_element(load, load + kXcds) += c;
   const double xcd = static_cast<double>(*std::max_element(load, load + kXcds)) * 76.0;
-  return 25.0 + 5e-6 * static_cast<double>(in_lds) + generic * std::max(device, xcd) * 1e-6;
+  return 25.0 + 5e-6 * static_cast<double>(in_lds) + std::max(device, xcd) * 1e-6;
 }
 
 double construction_us(const CrossoverRow* r, uint64_t n, uint64_t chunks) {
