@@ -93,14 +93,16 @@ typedef struct bf_filter bf_filter; /* opaque handle, owns the device words */
  *   strategy        add only: BF_STRATEGY_*.  The partitioned strategy
  *                   radix-partitions the keys by 64 KiB filter chunk and
  *                   updates each chunk in LDS, so a bulk add performs no
- *                   global atomics; it takes a workspace of 15-21 bytes per key,
- *                   of at most 2^28 keys at a time (about 6 for a filter of at most 1024 chunks, 64 MiB,
- *                   which is partitioned in one pass)
- *                   from a per-device stream-ordered memory pool and returns
- *                   it at its end on the same stream (no device
- *                   synchronization; the pool keeps its peak size reserved
- *                   for later adds); the library orders it against the
- *                   filter's other adds on any stream (see Concurrency).
+ *                   global atomics; it takes a workspace of 15-22 bytes per key,
+ *                   of at most 2^28 keys at a time (about 6 for a filter of
+ *                   at most 1024 chunks, 64 MiB, which is partitioned in one
+ *                   pass, and up to 31 where few keys go into 16 GiB and
+ *                   more), from a per-device stream-ordered memory pool and
+ *                   returns it at its end on the same stream (no device
+ *                   synchronization; the pool keeps the memory for later
+ *                   calls, see bf_release_workspace); the library orders it
+ *                   against the filter's other adds on any stream (see
+ *                   Concurrency).
  *                   Mapping fields other than strategy do not apply to it.
  *                   Results are identical;
  *   workgroup_threads threads per workgroup of the launch: 64, 128 or 256
@@ -182,17 +184,26 @@ bf_status bf_add(bf_filter *f, const uint64_t *d_keys, uint64_t n, void *stream)
 
 /* Bulk lookup: d_out[i] = 1 if keys[i] may be in the filter, 0 if it is
  * certainly absent (Sec. II-A-1).  d_out is a device array of n bytes.
- * A large lookup (from 4 M keys) of a sectorized filter beyond the L2 (8 MiB
- * to 2 GiB) with the default mapping groups its keys by filter chunk and
- * tests every chunk in LDS; it takes 10 (filters up to 64 MiB) to 20 bytes
- * of workspace per key from the device's stream-ordered pool for the time of
- * the call, 2^28 keys at a time.  Where there is no such memory, while the
- * stream is being captured, and with a mapping set by bf_set_mapping, keys
- * are looked up one by one and nothing is allocated.  From 2 M keys on a
- * filter of up to 160 KiB (blocks of up to 32 bytes, default mapping) is
- * copied to LDS and tested there, without workspace.  Results are the same. */
+ * A large lookup (from 6 M keys, more in larger filters and for layouts that
+ * gain less) of a sectorized filter beyond the L2 (8 MiB to 2 GiB) with the
+ * default mapping groups its keys by filter chunk and tests every chunk in
+ * LDS, unless a sample shows that many of them repeat; it takes 9 (filters up
+ * to 64 MiB) to 22 bytes of workspace per key, 2^28 keys at a time, from the
+ * device's stream-ordered pool, and returns it to the pool at its end.  The
+ * pool keeps its memory (up to 5.8 GB of a lookup, per stream at work) for
+ * later calls, filters and plans; bf_release_workspace gives it back.  Where
+ * there is no such memory, while the stream is being captured, and with a
+ * mapping set by bf_set_mapping, keys are looked up one by one and nothing is
+ * allocated.  From 2 M keys on a filter of up to 160 KiB (blocks of up to 32
+ * bytes, default mapping) is copied to LDS and tested there, without
+ * workspace.  Results are the same. */
 bf_status bf_contains(const bf_filter *f, const uint64_t *d_keys, uint64_t n,
                       uint8_t *d_out, void *stream);
+
+/* Waits for the current device, then gives it back the workspace memory that
+ * its pool keeps for later partitioned adds and grouped lookups.  bf_create
+ * and its like and bf_batch_plan do the same where they find no memory. */
+bf_status bf_release_workspace(void);
 
 /* Sets every word to zero (a fill kernel on `stream`). */
 bf_status bf_clear(bf_filter *f, void *stream);
@@ -223,7 +234,7 @@ bf_status bf_set_mapping_ex(bf_filter *f, int op, const bf_mapping_t *m);
  * add mapping: BF_STRATEGY_DIRECT or BF_STRATEGY_PARTITIONED, the automatic
  * choice resolved by the measured crossover (partitioned from about 1.5 M
  * keys + filter bytes / 80; for the classic layout n counts k records per
- * key).  For callers that plan workspace memory (15-21 bytes per key for a
+ * key).  For callers that plan workspace memory (15-22 bytes per key for a
  * partitioned add, about 6 into a filter of at most 64 MiB; with the default
  * mapping an add of 8 keys per filter byte or more into up to 160 KiB runs in
  * LDS without workspace, whichever strategy this reports).  Host only:

@@ -100,6 +100,8 @@ _lib.bf_add.argtypes = [_vp, _vp, _u64, _vp]
 _lib.bf_add.restype = _i32
 _lib.bf_contains.argtypes = [_vp, _vp, _u64, _vp, _vp]
 _lib.bf_contains.restype = _i32
+_lib.bf_release_workspace.argtypes = []
+_lib.bf_release_workspace.restype = _i32
 _lib.bf_clear.argtypes = [_vp, _vp]
 _lib.bf_clear.restype = _i32
 _lib.bf_info.argtypes = [_vp, ctypes.POINTER(bf_info_t)]
@@ -314,6 +316,10 @@ def bf_add_noalloc(f, d_keys: int, n: int, stream: int = 0) -> int:
 
 def bf_contains(f, d_keys: int, n: int, d_out: int, stream: int = 0) -> int:
     return _lib.bf_contains(f, d_keys, n, d_out, stream)
+
+
+def bf_release_workspace() -> int:
+    return _lib.bf_release_workspace()
 
 
 def bf_clear(f, stream: int = 0) -> int:

@@ -308,23 +308,31 @@ WordsHome words_home(int device) {
 
 }  // namespace
 
-void* bfhip::lib_alloc(int device, uint64_t bytes, bool* pooled) {
-  *pooled = false;
-  void* p = nullptr;
-  const WordsHome home = words_home(device);
-  if (home.pool != nullptr) {
-    if (hipMallocFromPoolAsync(&p, bytes, home.pool, home.stream) == hipSuccess) {
-      if (hipStreamSynchronize(home.stream) == hipSuccess) {
-        *pooled = true;
-        return p;
-      }
-      (void)hipFreeAsync(p, home.stream);
-      return nullptr;
-    }
+namespace {
+
+// Memory from the pool on its stream, or, where that is not to be had, by
+// hipMalloc; on both again with what the workspace pool keeps given back.
+void* words_alloc(int device, uint64_t bytes, const WordsHome& home, bool* pooled) {
+  for (int turn = 0; turn < 2; ++turn) {
+    void* p = nullptr;
+    *pooled = home.pool != nullptr && hipMallocFromPoolAsync(&p, bytes, home.pool, home.stream) == hipSuccess;
+    if (*pooled) return p;
     (void)hipGetLastError();
+    if (hipMalloc(&p, bytes) == hipSuccess) return p;
+    (void)hipGetLastError();
+    if (!release_workspace(device)) break;
   }
-  if (hipMalloc(&p, bytes) != hipSuccess) {
-    (void)hipGetLastError();
+  return nullptr;
+}
+
+}  // namespace
+
+void* bfhip::lib_alloc(int device, uint64_t bytes, bool* pooled) {
+  const WordsHome home = words_home(device);
+  void* p = words_alloc(device, bytes, home, pooled);
+  if (p != nullptr && *pooled && hipStreamSynchronize(home.stream) != hipSuccess) {
+    (void)hipFreeAsync(p, home.stream);
+    *pooled = false;
     return nullptr;
   }
   return p;
@@ -346,19 +354,13 @@ bf_status bfhip::alloc_filter_words(bf_filter* f) {
     return BF_EDEVICE;
   }
   const WordsHome home = words_home(f->device);
-  hipStream_t s = home.stream;
-  f->pooled_words = home.pool != nullptr &&
-                    hipMallocFromPoolAsync(&f->d_words, f->nbytes, home.pool, s) == hipSuccess;
-  if (!f->pooled_words) {
-    // no pool on this device: plain allocation, zeroed on the null stream
-    (void)hipGetLastError();
-    s = nullptr;
-    if (hipMalloc(&f->d_words, f->nbytes) != hipSuccess) {
-      (void)hipGetLastError();
-      delete f;
-      return BF_ENOMEM;
-    }
+  f->d_words = words_alloc(f->device, f->nbytes, home, &f->pooled_words);
+  if (f->d_words == nullptr) {
+    delete f;
+    return BF_ENOMEM;
   }
+  // (words of a plain allocation are zeroed on the null stream)
+  hipStream_t s = f->pooled_words ? home.stream : nullptr;
   if (clear_words(f->d_words, f->nbytes, s) != BF_OK || hipStreamSynchronize(s) != hipSuccess) {
     if (f->pooled_words) {
       (void)hipFreeAsync(f->d_words, s);
@@ -524,6 +526,12 @@ bf_status bf_contains(const bf_filter* f, const uint64_t* d_keys, uint64_t n, ui
   hipStream_t s = static_cast<hipStream_t>(stream);
   return ordered_call(g, s, Access::kUse,
                       [&](CallMark& mark) { return run_routed(g, BF_OP_CONTAINS, d_keys, n, d_out, s, &mark); });
+}
+
+bf_status bf_release_workspace(void) {
+  int device = -1;
+  if (hipGetDevice(&device) != hipSuccess) return BF_EDEVICE;
+  return release_workspace(device) ? BF_OK : BF_EDEVICE;
 }
 
 bf_status bf_clear(bf_filter* f, void* stream) {

@@ -95,6 +95,10 @@ dim3 part_grid_apply(const PartArgs& a);
 // The construction and lookup workspaces' memory pool of a device (nullptr
 // where there is none).
 hipMemPool_t workspace_pool(int device);
+// Memory from it on `stream` (nullptr if there is none).
+void* workspace_alloc(int device, uint64_t bytes, hipStream_t stream);
+// Waits for the device, then gives back what the pool keeps.
+bool release_workspace(int device);
 
 // Grouped lookup (bf_lookup.hip): whether a lookup of n keys with the default
 // mapping is grouped, and the lookup itself (*taken false, and nothing

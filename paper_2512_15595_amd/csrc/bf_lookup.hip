@@ -396,12 +396,8 @@ bf_status grouped_lookup(const bf_filter* f, const uint64_t* keys, uint64_t n, u
   LookupKernels k;
   const uint64_t pass = std::min(n, kMaxPass);
   if (!plan_lookup(f, pass, x, k)) return BF_OK;
-  hipMemPool_t pool = workspace_pool(f->device);
-  void* ws = nullptr;
-  if (pool == nullptr || hipMallocFromPoolAsync(&ws, x.total, pool, stream) != hipSuccess) {
-    (void)hipGetLastError();
-    return BF_OK;  // no workspace: the direct lookup needs none
-  }
+  void* ws = workspace_alloc(f->device, x.total, stream);
+  if (ws == nullptr) return BF_OK;  // the direct lookup needs none
   *taken = true;
   hipError_t e = hipSuccess;
   for (uint64_t at = 0; at < n && e == hipSuccess; at += pass) {

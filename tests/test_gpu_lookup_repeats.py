@@ -172,3 +172,37 @@ def test_lookups_with_a_partial_last_high_digit(nbytes):
         assert np.array_equal(got, oracle_par.contains(words, nb, 8, 32, 8, 5, keys))
     finally:
         f.close()
+
+
+def test_workspace_kept_by_lookups_is_given_back_to_filters():
+    """The pool keeps a large lookup's workspace (5.8 GB) for the next one; a
+    filter that needs the memory gets it."""
+    from paper_2512_15595_amd import bf
+
+    n = 1 << 28
+    f = bf.BloomFilter((1 << 30) // 32, 8, 32, 8, 3)
+    keys = torch.zeros(n, dtype=torch.int64, device="cuda")
+    out = torch.empty(n, dtype=torch.uint8, device="cuda")
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    hold = torch.empty(torch.cuda.mem_get_info()[0] - (7 << 30), dtype=torch.uint8, device="cuda")
+    made = []
+    try:
+        log("lookup with 7 GiB of memory left, then a filter of 5 GiB")
+        f.contains(keys, out=out)
+        torch.cuda.synchronize()
+        made.append(bf.BloomFilter((5 << 30) // 32, 8, 32, 8, 4))
+        f.contains(keys, out=out)  # no memory for a workspace now: directly
+        assert not bool(out.any())
+        made.pop().close()
+        torch.cuda.synchronize()
+        f.contains(keys, out=out)
+        torch.cuda.synchronize()
+        kept = torch.cuda.mem_get_info()[0]
+        assert bf.bf_release_workspace() == bf.BF_OK
+        assert torch.cuda.mem_get_info()[0] > kept + (4 << 30)
+    finally:
+        del hold
+        torch.cuda.empty_cache()
+        for x in made + [f]:
+            x.close()
