@@ -751,9 +751,8 @@ bf_status bf_batch_launch_per_filter(bf_batch* b, void* stream) {
     if (n == 0) continue;
     const uint64_t off = b->offsets[i];
     bf_status st = b->op == BF_OP_ADD
-                       ? launch_unordered(b->filters[i], BF_OP_ADD, b->d_keys + off, n, nullptr, s)
-                       : launch_unordered(b->filters[i], BF_OP_CONTAINS, b->d_keys + off, n,
-                                          b->d_out + off, s);
+                       ? launch_routed(b->filters[i], BF_OP_ADD, b->d_keys + off, n, nullptr, s)
+                       : launch_routed(b->filters[i], BF_OP_CONTAINS, b->d_keys + off, n, b->d_out + off, s);
     if (st != BF_OK) return st;
   }
   return BF_OK;

@@ -133,10 +133,13 @@ void* lib_alloc(int device, uint64_t bytes, bool* pooled);
 void lib_free(int device, void* p, bool pooled);
 
 // bf_add / bf_contains work without the per-filter stream-order bookkeeping
-// (bf_api.hip), for plans and servers that order their own launches.
+// (bf_api.hip), for plans and servers that order their own launches: by the
+// direct kernels or the partitioned construction, as servers budget for, or by
+// the call's own route.
 struct CallMark;
 bf_status launch_unordered(bf_filter* f, int op, const uint64_t* keys, uint64_t n, uint8_t* out,
                            hipStream_t stream, CallMark* mark = nullptr);
+bf_status launch_routed(bf_filter* f, int op, const uint64_t* keys, uint64_t n, uint8_t* out, hipStream_t stream);
 
 // The measured construction costs of f's layout (bf_tuned.hpp rows; nullptr
 // if none) and the density rule built on them (bf_api.hip).

@@ -362,3 +362,43 @@ def test_small_filters_join_the_construction_where_it_pays(small, large, partiti
         plan.close()
         for f in rest[0]:
             f.close()
+
+
+@pytest.mark.parametrize("nbytes,n", [(32 << 20, 1 << 26), (64 * KIB, 1 << 24)])
+def test_per_filter_launches_take_the_route_of_single_calls(nbytes, n):
+    """bf_batch_launch_per_filter is a bf_add / bf_contains per filter: grouped
+    or in LDS where those are (2.4 and 1.6 times the direct kernels' rate), and
+    with their results."""
+    from paper_2512_15595_amd import bf
+
+    keys = torch.randint(-2**63, 2**63 - 1, (n,), dtype=torch.int64, device="cuda")
+    outs = [torch.empty(n, dtype=torch.uint8, device="cuda") for _ in range(2)]
+    f, g = bf.BloomFilter(nbytes // 32, 8, 32, 8, 3), bf.BloomFilter(nbytes // 32, 8, 32, 8, 3)
+    some = keys[:nbytes // 8].contiguous()
+    add = bf.BatchPlan(bf.BF_OP_ADD, [f], some, [0, some.numel()])
+    plan = bf.BatchPlan(bf.BF_OP_CONTAINS, [f], keys, [0, n], outs[0])
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+
+    def best(call):
+        times = []
+        for _ in range(8):
+            a.record()
+            call()
+            b.record()
+            b.synchronize()
+            times.append(a.elapsed_time(b))
+        return min(times)
+
+    try:
+        add.launch_per_filter()
+        g.add(some)
+        assert torch.equal(f.words(), g.words())
+        per_filter, single = best(plan.launch_per_filter), best(lambda: g.contains(keys, out=outs[1]))
+        log(f"{n} lookups in {nbytes} bytes: per filter {per_filter:.3f} ms, bf_contains {single:.3f}")
+        assert torch.equal(outs[0], outs[1])
+        assert per_filter < 1.25 * single
+    finally:
+        add.close()
+        plan.close()
+        f.close()
+        g.close()
