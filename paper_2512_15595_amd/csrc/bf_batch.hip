@@ -107,6 +107,7 @@ CallMark begin_launch(bf_batch* b, hipStream_t stream) {
     } else {
       (void)hipGetLastError();
       mark.event = nullptr;
+      mark.lost = true;
       b->unmarked = true;  // destroy waits for the device
     }
   }
@@ -116,7 +117,7 @@ CallMark begin_launch(bf_batch* b, hipStream_t stream) {
 // Records the mark where no kernel of the launch signals it.
 bf_status end_launch(bf_batch* b, hipStream_t stream, const CallMark& mark) {
   if (mark.signalled) return BF_OK;
-  if (mark.event == nullptr) return b->unmarked ? BF_EDEVICE : BF_OK;
+  if (mark.event == nullptr) return mark.lost ? BF_EDEVICE : BF_OK;
   if (hipEventRecord(mark.event, stream) != hipSuccess) {
     (void)hipGetLastError();
     b->unmarked = true;  // the work is enqueued: destroy must still wait for it

@@ -177,6 +177,7 @@ inline hipEvent_t new_event() {
 struct CallMark {
   hipEvent_t event = nullptr;  // null while the stream is being captured
   bool signalled = false;      // by a launch of the call
+  bool lost = false;           // no event could be made (plans)
 };
 
 // Launches `fn`; with a mark, as the call's only kernel, which signals it.
