@@ -253,7 +253,7 @@ LookupCost lookup_cost(const bf_filter* f) {
   }
   const double l = std::log2(mib);  // 3 .. 6
   const bool more = l >= 4.0;       // 128 chunks and more: short runs
-  LookupCost c{38.0, 7.0, l < 4.0 ? 9.7 + 4.3 * (l - 3.0) : l < 5.0 ? 14.0 + 2.6 * (l - 4.0) : 16.6 + 1.9 * (l - 5.0)};
+  LookupCost c{38.0, 7.0, l < 4.0 ? 10.0 + 4.0 * (l - 3.0) : l < 5.0 ? 14.0 + 2.6 * (l - 4.0) : 16.6 + 1.9 * (l - 5.0)};
   if (generic) {
     c.grouped_ps += more ? 5.0 : 1.5;
     c.direct_ps = std::max(c.direct_ps, wide ? 21.0 : block > 32 ? 12.9 : 10.5);

@@ -57,6 +57,8 @@ def test_arguments_are_checked():
     (GIB, ADD, 1 << 20, DIRECT), (GIB, ADD, 1 << 28, PARTITIONED),
     (64 * KIB, CONTAINS, (1 << 21) - 1, DIRECT), (64 * KIB, CONTAINS, 1 << 21, LDS),
     (16 * KIB, CONTAINS, 1 << 21, DIRECT), (16 * KIB, CONTAINS, 1 << 22, LDS),
+    (8 * MIB, CONTAINS, 1 << 24, GROUPED), (16 * MIB, CONTAINS, 1 << 23, GROUPED), (32 * MIB, CONTAINS, 3 << 21, GROUPED),
+    (128 * MIB, CONTAINS, 12_400_000, GROUPED), (GIB, CONTAINS, 40_000_000, GROUPED),
     (4 * MIB, CONTAINS, 1 << 26, DIRECT), (2 * GIB + 32, CONTAINS, 1 << 28, DIRECT),
     (32 * MIB, CONTAINS, 1 << 26, GROUPED), (GIB, CONTAINS, 1 << 28, GROUPED), (GIB, CONTAINS, 1 << 24, DIRECT),
 ])
