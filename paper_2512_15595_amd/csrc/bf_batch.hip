@@ -283,7 +283,6 @@ bf_status plan_partitioned(bf_batch* b, bf_filter* const* filters, uint32_t nfil
     pf[i].block_base = chunks * bpc;
     pf[i].key_begin = h_offsets[i] - h_offsets[0];
     pf[i].key_end = h_offsets[i + 1] - h_offsets[0];
-    const uint64_t ni = pf[i].key_end - pf[i].key_begin;
     chunks += (f->num_blocks + bpc - 1) / bpc;
   }
   const uint64_t n = h_offsets[nfilters] - h_offsets[0];

@@ -66,22 +66,30 @@ __global__ __launch_bounds__(kScanThreads) void regroup_scan_kernel(RegroupArgs 
 }
 
 template <int D, int ROWS>
-const void* keys_fn(bool split, bool multi, bool place) {
-  if (multi) return split || place ? nullptr : reinterpret_cast<const void*>(&group_keys_kernel<D, ROWS, false, true, false>);
-  if (split)
-    return place ? reinterpret_cast<const void*>(&group_keys_kernel<D, ROWS, true, false, true>)
-                 : reinterpret_cast<const void*>(&group_keys_kernel<D, ROWS, true, false, false>);
-  return place ? reinterpret_cast<const void*>(&group_keys_kernel<D, ROWS, false, false, true>)
+const void* keys_fn(bool split, bool multi) {
+  if (multi) return split ? nullptr : reinterpret_cast<const void*>(&group_keys_kernel<D, ROWS, false, true, false>);
+  return split ? reinterpret_cast<const void*>(&group_keys_kernel<D, ROWS, true, false, false>)
                : reinterpret_cast<const void*>(&group_keys_kernel<D, ROWS, false, false, false>);
+}
+
+// Lookups: split records of up to 512 digits (one pass), pairs of up to 128.
+const void* place_fn(uint32_t digits, bool split) {
+  if (!split)
+    return digits <= 128 ? reinterpret_cast<const void*>(&group_keys_kernel<128, 16, false, false, true>) : nullptr;
+  return digits <= 128   ? reinterpret_cast<const void*>(&group_keys_kernel<128, 16, true, false, true>)
+         : digits <= 256 ? reinterpret_cast<const void*>(&group_keys_kernel<256, 16, true, false, true>)
+         : digits <= 512 ? reinterpret_cast<const void*>(&group_keys_kernel<512, 16, true, false, true>)
+                         : nullptr;
 }
 
 }  // namespace
 
 const void* group_keys_fn(uint32_t digits, bool split, bool multi, bool place) {
-  if (digits <= 128) return keys_fn<128, 16>(split, multi, place);
-  if (digits <= 256) return keys_fn<256, 16>(split, multi, place);
-  if (digits <= 512) return keys_fn<512, 16>(split, multi, place);
-  if (digits <= 1024) return keys_fn<1024, 8>(split, multi, place);
+  if (place) return place_fn(digits, split);
+  if (digits <= 128) return keys_fn<128, 16>(split, multi);
+  if (digits <= 256) return keys_fn<256, 16>(split, multi);
+  if (digits <= 512) return keys_fn<512, 16>(split, multi);
+  if (digits <= 1024) return keys_fn<1024, 8>(split, multi);
   return nullptr;
 }
 
