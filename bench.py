@@ -171,6 +171,24 @@ def streaming_copy(torch, nbytes: int) -> float:
     return 2 * nbytes / (t.ms() * 1e-3) / 1e9
 
 
+def lookup_grouped(num_blocks: int, s: int, S: int, k: int, n: int) -> bool:
+    """Whether the library groups a lookup of n keys with the default mapping
+    (bfb_call_plan of include/bf_bench.h)."""
+    import ctypes
+
+    from paper_2512_15595_amd import bf as bfmod
+
+    class Call(ctypes.Structure):
+        _fields_ = [("route", ctypes.c_uint32), ("reserved", ctypes.c_uint32), ("bytes", ctypes.c_uint64 * 3)]
+
+    lib = ctypes.CDLL(bfmod.LIB_PATH)
+    u64, u32 = ctypes.c_uint64, ctypes.c_uint32
+    lib.bfb_call_plan.argtypes = [u32, u64, u32, u32, u32, u32, u32, ctypes.c_int, u64, ctypes.c_void_p]
+    call = Call()
+    status = lib.bfb_call_plan(0, num_blocks, s, S, 0, k, 0, bfmod.BF_OP_CONTAINS, n, ctypes.addressof(call))
+    return status == 0 and call.route == 3
+
+
 def committed_traffic(kernel: str, sample_keys: int):
     """HBM bytes per launch from a committed rocprofv3 counter summary, if it
     was taken on the current kernel sources; else None."""
@@ -1212,10 +1230,12 @@ def main() -> int:
         dom, per_key, dom_ms = "contains", 8 + block_bytes + 1, ms["contains"]
     achieved = per_key * n / (dom_ms * 1e-3) / 1e9
     traffic = committed_traffic(dom, n)
-    # the default lookup groups many keys in a filter of 8 MiB..2 GiB by chunk
-    grouped = dom == "contains" and not mc and (8 << 20) <= filter_bytes <= (2 << 30) and n >= (1 << 24) + filter_bytes // 36
-    roofline = {"bound": "hbm", "kernel": ("group_keys + regroup + lookup_test + return_slots + lookup_return" if grouped
-                                           else f"bf_{dom}_kernel"), "achieved": round(achieved, 1),
+    kernel = f"bf_{dom}_kernel"
+    if not mc and lookup_grouped(num_blocks, s, S, k, n) and dom == "contains":
+        one_digit = filter_bytes <= (64 << 20)
+        kernel = ("sample + group_keys + lookup_test + lookup_return" if one_digit else
+                  "sample + group_keys + plan + scan + regroup + lookup_test + return_slots + lookup_return")
+    roofline = {"bound": "hbm", "kernel": kernel, "achieved": round(achieved, 1),
                 "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": round(achieved / PEAK_HBM_GBS, 4),
                 "traffic": traffic, "algorithmic_bytes_per_key": per_key,
                 "avg_launch_ms": round(dom_ms, 4)}

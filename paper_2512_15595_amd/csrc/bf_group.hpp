@@ -15,8 +15,9 @@
 // digits, 1.48 for 128 and 1.93 for 512 into buckets, 0.89-0.90 for any
 // number of digits as whole steps.  What is left is the streaming of 16
 // bytes per key (0.83 ms at the rate of a 1 GiB copy, 5.2 TB/s) and the LDS
-// sort beside it (0.6 ms without any stores).  The price is paid by the
-// reader, in runs of 8192 / digits records on average.
+// sort beside it (0.6 ms without any stores); counters put the pass at the
+// copy's rate.  The price is paid by the reader, in runs of 8192 / digits
+// records on average.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -39,8 +40,8 @@ __device__ __forceinline__ uint32_t run_len(uint32_t e) { return e >> 16; }
 // Workgroups go to the 8 XCDs round-robin by index.  Readers of neighbouring
 // digits share the lines where their runs meet (a run is rarely a whole
 // number of 128-byte lines), so workgroup b takes the work item that puts 64
-// consecutive ones (fewer if there are few) on one XCD, whose L2 then fetches such a line once
-// (measured on MI355X: apply of 11.6 M keys into 512 chunks 72.8 -> 68.7 us;
+// consecutive ones (fewer if there are few) on one XCD, whose L2 then fetches
+// such a line once (measured on MI355X: apply of 11.6 M keys into 512 chunks 72.8 -> 68.7 us;
 // no difference at 16,384 chunks, whose lines the Infinity Cache serves).
 __device__ __forceinline__ uint32_t xcd_item(uint32_t b, uint32_t n) {
   const uint32_t G = n >= 512 ? 64 : n / 8;

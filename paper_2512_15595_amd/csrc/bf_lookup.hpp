@@ -26,10 +26,9 @@
 // 444, a tenth of them one key 975 / 658 / 658, half 578 / 700 / 605, all of
 // them 200 / 858 / 169.
 //
-// Measured on MI355X (256-bit blocks, k = 8, half of the keys present; us,
-// direct -> grouped): 2^26 keys in 16 MiB 927 -> 442, 32 MiB 1120 -> 462,
-// 64 MiB 1246 -> 529, 256 MiB 1336 -> 755, 1 GiB 1274 -> 960; 2^28 keys in
-// 1 GiB 5070 -> 2951.
+// Measured on MI355X (256-bit blocks, k = 8; us, direct -> grouped): 2^26 keys
+// in 16 MiB 904 -> 427, 32 MiB 1074 -> 444, 128 MiB 1254 -> 744, 512 MiB 1256 ->
+// 845, 1 GiB 1272 -> 983; 2^28 keys in 1 GiB 5116 -> 3140.
 #pragma once
 
 #include <hip/hip_runtime.h>
