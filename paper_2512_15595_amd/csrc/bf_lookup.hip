@@ -220,48 +220,46 @@ constexpr uint64_t kMaxPass = 1ull << 28;
 
 namespace {
 
-// Measured costs of a lookup: grouped fixed_us + n * grouped_ps, direct
-// n * direct_ps where no key repeats; repeats add kRepeatPs to the grouped
-// form (keys beyond their runs' clip) and take the direct one down to kCachedPs
-// for theirs.
+// Costs of a lookup: grouped fixed_us + n * grouped_ps, direct n * direct_ps
+// where no key repeats; repeats add kRepeatPs to the grouped form (keys beyond
+// their runs' clip) and take the direct one down to kCachedPs for theirs.
+//
+// Fitted to both forms of 21 layouts (s, S, k) at 14 sizes of 8 MiB..2,000 MiB
+// and 2^22.5..2^27 keys on MI355X.  The test costs by the bits per key, the
+// block and a k that is not compiled in; with one digit it runs in rounds of
+// 256 workgroups, the last of which may be short.  Measured slopes, ps per key:
+// 16 MiB 8 x 32 bits k = 8 5.8 and k = 9 8.8, 4 x 64 k = 16 7.0, 16 x 64 8.0;
+// 24 MiB (384 workgroups) 6.7, 10.8, 8.2, 9.6; 160 MiB 10.0, 12.9, 10.8, 11.6.
+// Direct: 10.2 at 8 MiB, 14.2 at 16, 16.4 at 32, 18.2 at 64, 19 up to 1 GiB, 21
+// at 2; 21.5 with 20 bits in blocks of 128 bytes.
 struct LookupCost {
   double fixed_us, grouped_ps, direct_ps;
 };
-// Blocks of 64 and 128 bytes and many bits per key cost the test more, a k that
-// is not compiled in costs both forms more (measured with 2^22.7..2^28 keys:
-// 8 x 32 bits with k = 8 and 9, 1 x 32, 1 x 64, 4 x 64, 8 x 64 and 16 x 64; two
-// digits, 512 MiB, 2^26 keys, us direct / grouped: k = 8 1290 / 830, k = 9 1254
-// / 1059, 16 x 64 1239 / 1023).
 LookupCost lookup_cost(const bf_filter* f) {
   const double mib = static_cast<double>(f->nbytes) / (1 << 20);
-  const uint64_t block = static_cast<uint64_t>(f->s) * f->word_bits / 8;
-  const bool generic = k_index(f->k) == 0, wide = block > 64, mid = block > 32 || f->k >= 16;
+  const double block = static_cast<double>(f->s) * f->word_bits / 8;
+  const bool generic = k_index(f->k) == 0;
   if (f->nbytes > (64ull << 20)) {
     const double beyond = std::max(mib / 1024.0 - 1.0, 0.0);  // GiB
-    LookupCost c{65.0 + 0.24 * mib, 9.8 + 0.8 * beyond, 18.8 + 1.9 * beyond};
+    LookupCost c{65.0 + 0.23 * mib, 9.5 + 0.04 * f->k + 0.012 * block + 0.7 * beyond,
+                 18.2 + std::min(0.8, (mib - 64.0) / 200.0) + 2.3 * beyond};
     if (generic) {
-      c.fixed_us += 0.05 * mib;
-      c.grouped_ps += 3.4;
-      if (mib > 768.0) c.direct_ps += 1.7;
-    } else if (wide) {
-      c.fixed_us += 0.13 * mib;
-      c.grouped_ps += 2.8;
-    } else if (mid) {
-      c.grouped_ps += 1.0;
+      c.fixed_us += 0.08 * mib;
+      c.grouped_ps += 2.3;
+      if (mib > 768.0 && block >= 32.0) c.direct_ps += 1.7;
+    } else if (block > 64.0) {
+      c.fixed_us += 0.14 * mib;
     }
     return c;
   }
   const double l = std::log2(mib);  // 3 .. 6
-  const bool more = l >= 4.0;       // 128 chunks and more: short runs
-  LookupCost c{38.0, 7.0, l < 4.0 ? 10.0 + 4.0 * (l - 3.0) : l < 5.0 ? 14.0 + 2.6 * (l - 4.0) : 16.6 + 1.9 * (l - 5.0)};
-  if (generic) {
-    c.grouped_ps += more ? 5.0 : 1.5;
-    c.direct_ps = std::max(c.direct_ps, wide ? 21.0 : block > 32 ? 12.9 : 10.5);
-  } else if (wide) {
-    c.grouped_ps += more ? 3.5 : 0.7;
-  } else if (mid) {
-    c.grouped_ps += more ? 2.0 : 0.5;
-  }
+  const double test = 5.0 + 0.07 * f->k + 0.013 * block + (generic ? 2.1 : 0.0);
+  const uint64_t chunks = ceil_div(f->num_blocks, 1ull << chunk_shift(f, false));
+  const uint64_t groups = chunks * ceil_div(256, chunks);
+  const double rounds = static_cast<double>(ceil_div(groups, 256)) * 256.0 / static_cast<double>(groups);
+  LookupCost c{43.0, test + (test - 3.8) * (rounds - 1.0) + std::max(0.0, mib - 32.0) / 32.0,
+               l < 4.0 ? 10.2 + 4.0 * (l - 3.0) : l < 5.0 ? 14.2 + 2.2 * (l - 4.0) : 16.4 + 1.8 * (l - 5.0)};
+  if (generic) c.direct_ps = std::max(c.direct_ps, block > 64.0 ? 21.5 : block > 32.0 ? 13.3 : 10.9);
   return c;
 }
 constexpr double kRepeatPs = 2.5;
@@ -280,14 +278,15 @@ constexpr double kCachedPs = 2.6;
 bool lookup_groups(const bf_filter* f, uint64_t n) {
   if (f->layout != BF_LAYOUT_SECTORIZED || f->nbytes < (8ull << 20) || f->nbytes > (2ull << 30)) return false;
   const uint64_t least = f->nbytes < (16ull << 20)    ? 1ull << 24
-                         : f->nbytes < (32ull << 20)  ? 1ull << 23
-                         : f->nbytes <= (64ull << 20) ? 3ull << 21
+                         : f->nbytes < (32ull << 20)  ? 3ull << 21
+                         : f->nbytes <= (64ull << 20) ? 5ull << 20
                                                       : (1ull << 23) + f->nbytes / 36;
   if (n < least) return false;
-  // ... and where the costs of the layout give the grouped form a twentieth
+  // ... and where the costs of the layout give the grouped form 3 %, the
+  // error of the fit
   const LookupCost c = lookup_cost(f);
   const double keys = static_cast<double>(n) * 1e-6;
-  return c.direct_ps * keys > 1.05 * (c.fixed_us + c.grouped_ps * keys);
+  return c.direct_ps * keys > 1.03 * (c.fixed_us + c.grouped_ps * keys);
 }
 
 namespace {
