@@ -184,7 +184,7 @@ bf_status bf_add(bf_filter *f, const uint64_t *d_keys, uint64_t n, void *stream)
 
 /* Bulk lookup: d_out[i] = 1 if keys[i] may be in the filter, 0 if it is
  * certainly absent (Sec. II-A-1).  d_out is a device array of n bytes.
- * A large lookup (from 6 M keys, more in larger filters and for layouts that
+ * A large lookup (from 5 M keys, more in larger filters and for layouts that
  * gain less) of a sectorized filter beyond the L2 (8 MiB to 2 GiB) with the
  * default mapping groups its keys by filter chunk and tests every chunk in
  * LDS, unless a sample shows that many of them repeat; it takes 9 (filters up
