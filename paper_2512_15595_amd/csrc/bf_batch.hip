@@ -260,7 +260,8 @@ double construction_us(const CrossoverRow* r, uint64_t n, uint64_t chunks) {
 // layout's measured costs (the crossover rows of bf_tuned.hpp, without the
 // fixed cost, which the plan shares), streaming its chunks would cost more
 // than its keys' atomics, and its chunks then get neither records nor
-// traffic.  Returns BF_OK and sets b->partitioned when taken.
+// traffic.  Returns BF_OK and sets b->partitioned when taken, and takes the
+// small filters out of the LDS launches where they join it.
 bf_status plan_partitioned(bf_batch* b, bf_filter* const* filters, uint32_t nfilters,
                            const uint64_t* d_keys, const uint64_t* h_offsets) {
   const bf_filter* f0 = filters[0];
@@ -310,13 +311,8 @@ bf_status plan_partitioned(bf_batch* b, bf_filter* const* filters, uint32_t nfil
     const uint64_t in_lds = resident_keys_of(b, filters, nfilters, h_offsets);
     if (in_lds == 0) return BF_OK;
     const double apart = lds_and_tiles_us(xr, filters, pf, in_lds);
-    const void* fns[2] = {b->resident[0].fn, b->resident[1].fn};
     b->resident[0].fn = b->resident[1].fn = nullptr;
-    if (!choose() || construction_us(xr, n_dense, dense_chunks) >= apart) {
-      b->resident[0].fn = fns[0];
-      b->resident[1].fn = fns[1];
-      return BF_OK;
-    }
+    if (!choose() || construction_us(xr, n_dense, dense_chunks) >= apart) return BF_OK;
   }
   PartArgs a{};
   PartLayout L{};
@@ -676,11 +672,14 @@ bf_status bf_batch_plan(int op, bf_filter* const* filters, uint32_t nfilters,
   b->device = f0->device;
 
   if (op == BF_OP_ADD) {
+    const void* fns[2] = {b->resident[0].fn, b->resident[1].fn};
     bf_status pst = plan_partitioned(b, filters, nfilters, d_keys, h_offsets);
     if (pst != BF_OK) {
       free_plan(b);
       return pst;
     }
+    // (small filters that would have joined a construction run in LDS)
+    for (int big = 0; big < 2 && !b->partitioned; ++big) b->resident[big].fn = fns[big];
   }
   // The tiled direct launch: every filter, or (partitioned plan) the filters
   // left to it that have keys.

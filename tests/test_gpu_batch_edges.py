@@ -364,6 +364,43 @@ def test_small_filters_join_the_construction_where_it_pays(small, large, partiti
             f.close()
 
 
+def test_joined_plan_without_memory_keeps_its_small_filters_in_lds():
+    """2,048 filters of 64 KiB join the construction of one of 16 MiB; where
+    its 0.4 GB are not to be had they run in LDS again, not in tiles."""
+    from paper_2512_15595_amd import bf
+
+    shapes = [(64 * KIB, 8_192)] * 2048 + [(16 << 20, 1 << 22)]
+    log("add plan whose small filters would join the construction, and 0.1 GB of memory")
+    plan, filters, words, ends, offsets, keys, _ = _plan_of(shapes, 9)
+    assert plan.info().strategy == bf.BF_STRATEGY_PARTITIONED
+    plan.close()
+    d_keys = to_device(keys)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    hold = torch.empty(torch.cuda.mem_get_info()[0] - (1 << 30), dtype=torch.uint8, device="cuda")
+    fillers = []
+    try:
+        while True:
+            try:
+                fillers.append(bf.BloomFilter((96 << 20) // 32, 8, 32, 8, 0))
+            except bf.BfError:
+                break
+        fillers.pop().close()
+        plan = bf.BatchPlan(bf.BF_OP_ADD, filters, d_keys, offsets)
+        info = plan.info()
+        assert info.strategy == bf.BF_STRATEGY_DIRECT
+        # the tiles (256 or 512 keys) of the one filter that the LDS cannot hold
+        assert sum(info.tiles_per_class) <= (1 << 22) // 256
+        del hold
+        _check_plan(plan, filters, words, ends, offsets, keys, (0, 2_047, 2_048))
+    finally:
+        hold = None
+        torch.cuda.empty_cache()
+        plan.close()
+        for f in filters + fillers:
+            f.close()
+
+
 @pytest.mark.parametrize("nbytes,n", [(32 << 20, 1 << 26), (64 * KIB, 1 << 24)])
 def test_per_filter_launches_take_the_route_of_single_calls(nbytes, n):
     """bf_batch_launch_per_filter is a bf_add / bf_contains per filter: grouped
