@@ -222,7 +222,9 @@ namespace {
 
 // Costs of a lookup: grouped fixed_us + n * grouped_ps, direct n * direct_ps
 // where no key repeats; repeats add kRepeatPs to the grouped form (keys beyond
-// their runs' clip) and take the direct one down to kCachedPs for theirs.
+// their runs' clip; 2^26 keys, 10 to 50 % of them one key: 2.2..2.4 at 16 MiB,
+// 3.2..3.7 at 32 MiB, 1.8..2 from 128 MiB on) and take the direct one down to
+// kCachedPs for theirs.
 //
 // Fitted to both forms of 21 layouts (s, S, k) at 14 sizes of 8 MiB..2,000 MiB
 // and 2^22.5..2^27 keys on MI355X.  The test costs by the bits per key, the
@@ -262,8 +264,17 @@ LookupCost lookup_cost(const bf_filter* f) {
   if (generic) c.direct_ps = std::max(c.direct_ps, block > 64.0 ? 21.5 : block > 32.0 ? 13.3 : 10.9);
   return c;
 }
-constexpr double kRepeatPs = 2.5;
+constexpr double kRepeatPs[2] = {3.5, 2.5};  // one digit, two
 constexpr double kCachedPs = 2.6;
+// The share of the keys that the caches serve is that of the sample's repeats
+// where one key repeats, and more where the keys are skewed, for most of them
+// are seen once in the sample.  Break-even shares of repeats, one key / skewed:
+// 16 MiB 2^26 keys 0.40 / 0.26, 32 MiB 0.41 / 0.25, 64 MiB 0.51 / 0.28, 128 MiB
+// 0.40 / 0.20, 512 MiB 0.36 / 0.18.  With 0.75 (limits 0.26..0.38 and 0.16..0.22)
+// no lookup of 130 measured ones is grouped that takes 15 % more than directly
+// before the sample came; those that go directly take 3..10 % more with 2^26 keys
+// and, for the sample and the launches, up to 23 % with 2^24 (128 MiB 131 -> 161 us).
+constexpr double kSeen = 0.75;
 
 }  // namespace
 
@@ -297,9 +308,9 @@ uint32_t sample_limit(const bf_filter* f, uint64_t n) {
   if (!lookup_groups(f, n)) return 0;
   const LookupCost c = lookup_cost(f);
   const double keys = static_cast<double>(n) * 1e-6;
-  const double grouped = c.fixed_us + (c.grouped_ps + kRepeatPs) * keys;
+  const double grouped = c.fixed_us + (c.grouped_ps + kRepeatPs[f->nbytes > (64ull << 20)]) * keys;
   const double share = (c.direct_ps * keys - grouped) / ((c.direct_ps - kCachedPs) * keys);
-  return kSampleChance + static_cast<uint32_t>(std::max(share, 0.02) * kSampleKeys);
+  return kSampleChance + static_cast<uint32_t>(std::max(kSeen * share, 0.02) * kSampleKeys);
 }
 
 }  // namespace
