@@ -76,14 +76,23 @@ def test_repeated_lookups_of_other_layouts(s, S, k, share, nbytes, n):
         f.close()
 
 
-@pytest.mark.parametrize("nbytes,n", [(32 * MIB, 1 << 26), (1024 * MIB, 1 << 26)])
-def test_repeated_keys_cost_what_direct_lookups_cost(nbytes, n):
+@pytest.mark.parametrize("nbytes,n,kind,most", [
+    (32 * MIB, 1 << 26, "one", 2.0), (1024 * MIB, 1 << 26, "one", 2.0),
+    # grouped they take 1.17 and 1.30 times as long as directly
+    (32 * MIB, 1 << 26, "half", 1.12), (32 * MIB, 1 << 26, "skewed", 1.15)])
+def test_repeated_keys_cost_what_direct_lookups_cost(nbytes, n, kind, most):
     """All keys equal: their line stays in the caches, and a direct lookup of
-    them takes a quarter of the time that grouping does."""
+    them takes a quarter of the time that grouping does.  Half of them equal, or
+    skewed: it is faster too."""
     from paper_2512_15595_amd import bf
 
     f, _, _ = _filter(nbytes)
     keys = torch.full((n,), 1234567, dtype=torch.int64, device="cuda")
+    if kind == "half":
+        keys[torch.rand(n, device="cuda") < 0.5] = 0
+        keys += torch.randint(1, 2**62, (n,), device="cuda") * (keys == 0)
+    elif kind == "skewed":
+        keys = (torch.rand(n, device="cuda", dtype=torch.float64).pow(8) * 1e6).long()
     out = torch.empty(n, dtype=torch.uint8, device="cuda")
     a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
 
@@ -101,8 +110,8 @@ def test_repeated_keys_cost_what_direct_lookups_cost(nbytes, n):
         ms = best()
         f.set_mapping(bf.BF_OP_CONTAINS, 1, 8, 2)
         direct = best()
-        log(f"one key {n} times in {nbytes >> 20} MiB: {ms:.3f} ms, direct {direct:.3f}")
-        assert ms < 2 * direct
+        log(f"{n} keys ({kind}) in {nbytes >> 20} MiB: {ms:.3f} ms, direct {direct:.3f}")
+        assert ms < most * direct
     finally:
         f.close()
 
